@@ -351,10 +351,11 @@ def work(case):
 
 
 def tolerance(case):
-    """Measured with the rows of every batch in another order, the loss, the update and the halo form of the convolutions by
-    other kernels, over two passes: training carries the last bits on, so a pass of many steps ends farther apart than one
-    sum does.  bfloat16 (a last bit of a sum moves a stored activation or weight by 2^-9): rel 0.005, max 0.08.  Single precision: rel 1e-5, max 1e-3; Adam divides by the root of the second moment, which lifts the noise of
-    small gradients to the size of an update: rel 7e-4, max 0.02."""
+    """Measured with the rows of every batch in another order and the loss, the update and the halo form of the convolutions
+    done by other kernels, over two passes: training carries the last bits on, so a pass of many steps ends farther apart
+    than one sum does.  bfloat16 (a last bit of a sum moves a stored activation or weight by 2^-9): rel 0.005, max 0.08.
+    Single precision: rel 1e-5, max 1e-3; Adam divides by the root of the second moment, which lifts the noise of small
+    gradients to the size of an update: rel 7e-4, max 0.02."""
     if case["dtype"] == "bf16":
         return {"rel": 0.02, "max": 0.3}
     return {"rel": 4e-3, "max": 0.1} if case["optimizer"] in ("adam", "mixed") else {"rel": 1e-4, "max": 4e-3}

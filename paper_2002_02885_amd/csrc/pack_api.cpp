@@ -17,8 +17,6 @@
 #include <map>
 #include <mutex>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <vector>
 
 using namespace packk;
@@ -89,6 +87,8 @@ struct ModelInfo {
     size_t arena_begin = 0, arena_end = 0;
     int* pred = nullptr;
     float* loss = nullptr;
+    size_t segs_off = 0;             // byte offset of the member's BlobSeg table in the descriptor buffer
+    int n_segs = 0;
     bool fused_head = false;         // classifier head (last linear layer, loss, its input gradient) runs in one kernel
     float* head_partial = nullptr;   // per-block loss sums of that kernel
 };
@@ -173,69 +173,33 @@ struct pack_ctx {
 
 namespace {
 
-// ---- counter-based initialisation: value = hash(seed, member, tensor, index) -> uniform ---------
-inline uint64_t splitmix64(uint64_t x) {
-    x += 0x9E3779B97F4A7C15ull;
-    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-    return x ^ (x >> 31);
-}
-inline float uniform_pm(uint64_t seed, uint64_t member, uint64_t tensor, uint64_t idx, float bound) {
-    const uint64_t h = splitmix64(splitmix64(splitmix64(seed ^ (member << 32)) ^ tensor) ^ idx);
-    const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);   // [0,1)
-    return (float)((2.0 * u - 1.0) * bound);
-}
-inline float round_to_bf16(float f) {
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return f;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    u &= 0xffff0000u;
-    std::memcpy(&f, &u, 4);
-    return f;
-}
-
-// ---- public blob <-> arena layout ----------------------------------------------------------------
-// linear: identical ([out][in]).  conv: blob [Cout][Cin][3][3]  <->  arena [Cout][3][3][Cin].
-void blob_to_arena(const ModelInfo& m, const float* blob, std::vector<float>& arena) {
-    arena.assign(m.arena_end - m.arena_begin, 0.f);
+// The tensors of a member's public blob and where they lie in the arenas.  linear: rows as they are.  conv: blob
+// [Cout][Cin][3][3], arena [Cout][3][3][Cin] (rows padded to `kp` for im2col convolutions; padding stays zero).
+std::vector<BlobSeg> blob_segments(const ModelInfo& m) {
+    std::vector<BlobSeg> segs;
+    int tensor = 0;
     for (const NodeInfo& nd : m.nodes) {
         if (nd.kind == NODE_GAP) continue;
-        float* W = arena.data() + (nd.w_off - m.arena_begin);
-        float* b = arena.data() + (nd.b_off - m.arena_begin);
-        const float* src = blob + nd.blob_off;
-        if (nd.kind == NODE_LINEAR) {
-            std::memcpy(W, src, nd.w_elems * sizeof(float));
-        } else {
-            const int cin = nd.fan_in / 9;
-            const size_t row = nd.kp ? (size_t)nd.kp : (size_t)nd.fan_in;   // padding stays zero
-            for (int o = 0; o < nd.out; ++o)
-                for (int c = 0; c < cin; ++c)
-                    for (int t = 0; t < 9; ++t)
-                        W[(size_t)o * row + (size_t)t * cin + c] = src[((size_t)o * cin + c) * 9 + t];
-        }
-        std::memcpy(b, src + nd.w_elems, (size_t)nd.out * sizeof(float));
+        BlobSeg w{};
+        w.blob_off = (long long)nd.blob_off;
+        w.arena_off = (long long)(nd.w_off - m.arena_begin);
+        w.inner = nd.fan_in;
+        w.ldw = nd.kp ? nd.kp : nd.fan_in;
+        w.conv = nd.kind == NODE_CONV;
+        w.cin = w.cpad = w.conv ? nd.fan_in / 9 : nd.fan_in;
+        w.tensor = tensor;
+        w.bound = std::sqrt(6.0f / (float)nd.fan_in);
+        BlobSeg b{};
+        b.blob_off = (long long)(nd.blob_off + nd.w_elems);
+        b.arena_off = (long long)(nd.b_off - m.arena_begin);
+        b.inner = b.ldw = b.cin = b.cpad = nd.out;
+        b.tensor = tensor + 1;
+        b.bound = 1.0f / std::sqrt((float)nd.fan_in);
+        segs.push_back(w);
+        segs.push_back(b);
+        tensor += 2;
     }
-}
-
-void arena_to_blob(const ModelInfo& m, const std::vector<float>& arena, float* blob) {
-    for (const NodeInfo& nd : m.nodes) {
-        if (nd.kind == NODE_GAP) continue;
-        const float* W = arena.data() + (nd.w_off - m.arena_begin);
-        const float* b = arena.data() + (nd.b_off - m.arena_begin);
-        float* dst = blob + nd.blob_off;
-        if (nd.kind == NODE_LINEAR) {
-            std::memcpy(dst, W, nd.w_elems * sizeof(float));
-        } else {
-            const int cin = nd.fan_in / 9;
-            const size_t row = nd.kp ? (size_t)nd.kp : (size_t)nd.fan_in;
-            for (int o = 0; o < nd.out; ++o)
-                for (int c = 0; c < cin; ++c)
-                    for (int t = 0; t < 9; ++t)
-                        dst[((size_t)o * cin + c) * 9 + t] = W[(size_t)o * row + (size_t)t * cin + c];
-        }
-        std::memcpy(dst + nd.w_elems, b, (size_t)nd.out * sizeof(float));
-    }
+    return segs;
 }
 
 // ---- parse one member's layer list -----------------------------------------------------------------
@@ -1145,17 +1109,12 @@ pack_status dev_alloc(void** ptr, size_t bytes, pack_ctx* p) {
 
 pack_status live_member(const pack_ctx* p, int32_t k);
 
+const BlobSeg* member_segs(const pack_ctx* p, int k) { return (const BlobSeg*)(p->desc + p->models[k].segs_off); }
+
 pack_status upload_weights(pack_ctx* p, int k, const float* blob) {
-    ModelInfo& m = p->models[k];
-    std::vector<float> arena;
-    blob_to_arena(m, blob, arena);
-    HIP_TRY(hipStreamSynchronize(p->stream), PACK_EDEVICE);
-    HIP_TRY(hipMemcpy(p->master + m.arena_begin, arena.data(), arena.size() * sizeof(float), hipMemcpyHostToDevice), PACK_EDEVICE);
-    if (p->bf16) {
-        HIP_TRY(launch_cast_bf16(p->master + m.arena_begin, (char*)p->shadow + m.arena_begin * 2,
-                                 (long long)arena.size(), p->stream), PACK_EDEVICE);
-        HIP_TRY(hipStreamSynchronize(p->stream), PACK_EDEVICE);
-    }
+    const ModelInfo& m = p->models[k];
+    void* const shadow = p->bf16 ? (void*)((char*)p->shadow + m.arena_begin * 2) : nullptr;
+    HIP_TRY(import_blob(p->device, p->stream, p->master + m.arena_begin, shadow, member_segs(p, k), m.n_segs, m.n_params, blob), PACK_EDEVICE);
     return PACK_OK;
 }
 
@@ -1163,12 +1122,9 @@ pack_status download(pack_ctx* p, int k, const float* dev_arena, float* host_dst
     if (!p || !host_dst) return fail(PACK_EINVAL, "null argument");
     pack_status st = live_member(p, k);
     if (st != PACK_OK) return st;
-    ModelInfo& m = p->models[k];
+    const ModelInfo& m = p->models[k];
     if (n_floats != m.n_params) return fail(PACK_EINVAL, "n_floats does not match pack_num_params");
-    std::vector<float> arena(m.arena_end - m.arena_begin);
-    HIP_TRY(hipStreamSynchronize(p->stream), PACK_EDEVICE);
-    HIP_TRY(hipMemcpy(arena.data(), dev_arena + m.arena_begin, arena.size() * sizeof(float), hipMemcpyDeviceToHost), PACK_EDEVICE);
-    arena_to_blob(m, arena, host_dst);
+    HIP_TRY(export_blob(p->device, p->stream, dev_arena + m.arena_begin, member_segs(p, k), m.n_segs, m.n_params, host_dst), PACK_EDEVICE);
     return PACK_OK;
 }
 
@@ -1291,6 +1247,11 @@ pack_status build_device(pack_ctx* p) {
     DescBuilder db;
     size_t need = 0;
     build_plan(p, db, need);
+    for (ModelInfo& m : p->models) {
+        const std::vector<BlobSeg> segs = blob_segments(m);
+        m.n_segs = (int)segs.size();
+        m.segs_off = db.add(segs.data(), segs.size() * sizeof(BlobSeg));
+    }
     p->workspace_bytes = need;
     if (need) TRY_ALLOC(p->workspace, need);
     TRY_ALLOC(p->desc, db.bytes.size());
@@ -1301,13 +1262,14 @@ pack_status build_device(pack_ctx* p) {
         return PACK_OK;
     }
 
+    // everything on the pack's stream, in front of whatever uses it
     hipError_t e = hipMemcpy(p->desc, db.bytes.data(), db.bytes.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(p->slab, 0, p->slab_bytes);
-    if (e == hipSuccess) e = hipMemset(p->grad, 0, p->arena_elems * 4);
-    if (e == hipSuccess) e = hipMemset(p->master, 0, p->arena_elems * 4);
-    if (e == hipSuccess && p->shadow) e = hipMemset(p->shadow, 0, p->arena_elems * 2);
-    if (e == hipSuccess && p->opt_m) e = hipMemset(p->opt_m, 0, p->arena_elems * 4);
-    if (e == hipSuccess && p->opt_v) e = hipMemset(p->opt_v, 0, p->arena_elems * 4);
+    if (e == hipSuccess) e = hipMemsetAsync(p->slab, 0, p->slab_bytes, p->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(p->grad, 0, p->arena_elems * 4, p->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(p->master, 0, p->arena_elems * 4, p->stream);
+    if (e == hipSuccess && p->shadow) e = hipMemsetAsync(p->shadow, 0, p->arena_elems * 2, p->stream);
+    if (e == hipSuccess && p->opt_m) e = hipMemsetAsync(p->opt_m, 0, p->arena_elems * 4, p->stream);
+    if (e == hipSuccess && p->opt_v) e = hipMemsetAsync(p->opt_v, 0, p->arena_elems * 4, p->stream);
     std::vector<long long> ends(K);
     for (int k = 0; k < K; ++k) ends[k] = (long long)p->models[k].arena_end;
     if (e == hipSuccess) e = hipMemcpy(p->seg_end, ends.data(), (size_t)K * sizeof(long long), hipMemcpyHostToDevice);
@@ -1324,45 +1286,13 @@ pack_status build_device(pack_ctx* p) {
     return PACK_OK;
 }
 
-// seeded initial weights of member k: uniform in +-sqrt(6/fan_in), biases in +-1/sqrt(fan_in)
+// seeded initial weights of member k: uniform in +-sqrt(6/fan_in), biases in +-1/sqrt(fan_in), drawn on the device
+// (enqueues only)
 pack_status seed_weights(pack_ctx* p, int k, uint64_t seed) {
-    ModelInfo& m = p->models[k];
-    std::vector<float> blob(m.n_params);
-    const bool bf16 = p->bf16;
-    // every value is a hash of (seed, member, tensor, index): the ranges can be filled by several threads
-    auto fill = [&](float* dst, size_t n, int tensor, float bound) {
-        const size_t per = 1u << 18;
-        const unsigned workers = (unsigned)std::min<size_t>(std::max(1u, std::min(16u, std::thread::hardware_concurrency())), (n + per - 1) / per);
-        auto work = [=](size_t lo, size_t hi) {
-            for (size_t i = lo; i < hi; ++i) {
-                const float v = uniform_pm(seed, k, tensor, i, bound);
-                dst[i] = bf16 ? round_to_bf16(v) : v;
-            }
-        };
-        if (workers <= 1) { work(0, n); return; }
-        std::vector<std::thread> pool;
-        const size_t step = (n + workers - 1) / workers;
-        size_t started = 0;   // elements handed to threads so far
-        try {
-            for (unsigned t = 0; t < workers; ++t) {
-                pool.emplace_back(work, std::min(n, t * step), std::min(n, (t + 1) * step));
-                started = std::min(n, (t + 1) * step);
-            }
-        } catch (const std::system_error&) {
-            // no more threads to be had: this thread fills the rest
-        }
-        work(started, n);
-        for (std::thread& t : pool) t.join();
-    };
-    int tensor = 0;
-    for (const NodeInfo& nd : m.nodes) {
-        if (nd.kind == NODE_GAP) continue;
-        const float bw = std::sqrt(6.0f / (float)nd.fan_in), bb = 1.0f / std::sqrt((float)nd.fan_in);
-        fill(blob.data() + nd.blob_off, nd.w_elems, tensor, bw);
-        fill(blob.data() + nd.blob_off + nd.w_elems, (size_t)nd.out, tensor + 1, bb);
-        tensor += 2;
-    }
-    return upload_weights(p, k, blob.data());
+    const ModelInfo& m = p->models[k];
+    void* const shadow = p->bf16 ? (void*)((char*)p->shadow + m.arena_begin * 2) : nullptr;
+    HIP_TRY(launch_seed_blob(p->master + m.arena_begin, shadow, member_segs(p, k), m.n_segs, (long long)m.n_params, seed, (unsigned long long)k, p->stream), PACK_EDEVICE);
+    return PACK_OK;
 }
 
 // What a slot of the pack shall hold after a change of membership or batch sizes.
@@ -1944,12 +1874,9 @@ pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec) 
     // starting state over the member's whole arena segment (alignment gaps included: their gradient
     // is always zero, and a positive Adagrad accumulator there keeps 0 / sqrt(acc) well defined)
     const ModelInfo& m = p->models[k];
-    const size_t seg = m.arena_end - m.arena_begin;
-    if (p->opt_m) {
-        std::vector<float> init(seg, o.kind == PACK_OPT_ADAGRAD ? o.acc0 : 0.f);
-        HIP_TRY(hipMemcpy(p->opt_m + m.arena_begin, init.data(), seg * 4, hipMemcpyHostToDevice), PACK_EDEVICE);
-    }
-    if (p->opt_v) HIP_TRY(hipMemset(p->opt_v + m.arena_begin, 0, seg * 4), PACK_EDEVICE);
+    const long long seg = (long long)(m.arena_end - m.arena_begin);
+    if (p->opt_m) HIP_TRY(launch_fill_value(p->opt_m + m.arena_begin, seg, o.kind == PACK_OPT_ADAGRAD ? o.acc0 : 0.f, p->stream), PACK_EDEVICE);
+    if (p->opt_v) HIP_TRY(launch_fill_value(p->opt_v + m.arena_begin, seg, 0.f, p->stream), PACK_EDEVICE);
     return PACK_OK;
 }
 
@@ -1977,19 +1904,10 @@ pack_status pack_write_opt_state(pack_t* p, int32_t k, int32_t slot, const float
     pack_status st = opt_slot(p, k, slot, &arena);
     if (st != PACK_OK) return st;
     if (!host_src || steps < 0) return fail(PACK_EINVAL, "null argument or negative step count");
-    ModelInfo& m = p->models[k];
+    const ModelInfo& m = p->models[k];
     if (n_floats != m.n_params) return fail(PACK_EINVAL, "n_floats does not match pack_num_params");
-    std::vector<float> seg;
-    blob_to_arena(m, host_src, seg);
-    if (p->opt[k].kind == PACK_OPT_ADAGRAD && slot == 0) {
-        // positions outside the blob (alignment gaps, padded columns) keep a positive accumulator
-        std::vector<float> ones(m.n_params, 1.f), mark;
-        blob_to_arena(m, ones.data(), mark);
-        for (size_t i = 0; i < seg.size(); ++i)
-            if (mark[i] == 0.f) seg[i] = p->opt[k].acc0;
-    }
-    HIP_TRY(hipStreamSynchronize(p->stream), PACK_EDEVICE);
-    HIP_TRY(hipMemcpy(arena + m.arena_begin, seg.data(), seg.size() * 4, hipMemcpyHostToDevice), PACK_EDEVICE);
+    // (positions outside the blob, alignment gaps and padded columns, keep the optimiser's starting value)
+    HIP_TRY(import_blob(p->device, p->stream, arena + m.arena_begin, nullptr, member_segs(p, k), m.n_segs, m.n_params, host_src), PACK_EDEVICE);
     p->opt_t[k] = steps;
     return PACK_OK;
 }

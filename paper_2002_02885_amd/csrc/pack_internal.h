@@ -156,6 +156,19 @@ struct Im2colProb {   // shared-input loader: x [B,H,W,C] -> xcol [B*Ho*Wo, Kp],
     int B, H, W, C, Ho, Wo, stride, Kp;
 };
 
+// One tensor of a member's public blob and where its elements lie in a parameter arena.  Element i of the tensor is
+// (row, j), row = i / inner; j is (channel, tap) for convolutions and (pixel, channel) for everything else (a bias is
+// one row of `out` channels), and lies at arena_off + row * ldw + tap-or-pixel * cpad + channel.
+struct BlobSeg {
+    long long blob_off;    // first element in the blob
+    long long arena_off;   // first element in the arena, counted from the member's first
+    int inner, ldw;        // blob elements per row, arena elements per row
+    int cin, cpad;         // channels, and the distance of taps / pixels in an arena row
+    int conv;
+    int tensor;            // number of the tensor within the member, for seeded initial weights
+    float bound;           // they are uniform in +-bound
+};
+
 struct TransposeProb {   // convolution weights [Cout][9][Cin] -> [Cin][9][Cout], both of the pack's operand type
     const void* src;
     void* dst;
@@ -200,7 +213,15 @@ hipError_t launch_opt(float* master, const float* grad, void* shadow_bf16, float
                       const long long* seg_end_dev, const OptStatic* params_dev, int K, const OptTable& tab, hipStream_t st);
 hipError_t launch_im2col(bool bf16, const Im2colProb& p, const void* x_dev, hipStream_t st);
 hipError_t launch_wtranspose(bool bf16, const TransposeProb* probs_dev, const int2* map_dev, int n_blocks, hipStream_t st);
-hipError_t launch_cast_bf16(const float* src, void* dst_bf16, long long n, hipStream_t st);
+// member state <-> blob (pack_state.hip): `arena` points at the member's first element, `shadow` at its first bf16
+// copy (or null), e0 .. e0 + n are blob elements, in / out are mapped host memory
+hipError_t launch_export_blob(const float* arena, const BlobSeg* segs, int n_segs, long long e0, int n, float* out, hipStream_t st);
+hipError_t launch_import_blob(float* arena, void* shadow, const BlobSeg* segs, int n_segs, long long e0, int n, const float* in, hipStream_t st);
+hipError_t launch_seed_blob(float* arena, void* shadow, const BlobSeg* segs, int n_segs, long long n, unsigned long long seed, unsigned long long member, hipStream_t st);
+hipError_t launch_fill_value(float* dst, long long n, float value, hipStream_t st);
+// whole blobs between pageable host memory and an arena (pack_transfer.cpp); both wait for the stream
+hipError_t export_blob(int device, hipStream_t st, const float* arena, const BlobSeg* segs, int n_segs, size_t n, float* host);
+hipError_t import_blob(int device, hipStream_t st, float* arena, void* shadow, const BlobSeg* segs, int n_segs, size_t n, const float* host);
 hipError_t launch_fill_zero(void* dst, long long bytes, hipStream_t st);
 // x_out[r] = data[idx[r]], labels_out[r] = labels_all[idx[r]] for r < rows; rows of row_bytes bytes (a multiple of 2)
 hipError_t launch_ceiling_copy(const void* src, void* dst, long long bytes, hipStream_t st);

@@ -2070,23 +2070,6 @@ hipError_t launch_wtranspose(bool bf16, const TransposeProb* probs_dev, const in
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void cast_bf16_kernel(const float* __restrict__ src, bf16_t* __restrict__ dst, long long n) {
-    const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n) return;
-    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(src + i);
-    uint2 pk;
-    pk.x = pack2bf(v.x, v.y);
-    pk.y = pack2bf(v.z, v.w);
-    *reinterpret_cast<uint2*>(dst + i) = pk;
-}
-
-hipError_t launch_cast_bf16(const float* src, void* dst, long long n, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    const int blocks = (int)((n / 4 + 255) / 256);
-    hipLaunchKernelGGL(cast_bf16_kernel, dim3(blocks), dim3(256), 0, st, src, (bf16_t*)dst, n);
-    return hipGetLastError();
-}
-
 // Batch assembly for epochs in which the shared batch is cut from an index list (Section 3.2: the
 // samples a member has not used yet): row r of the shared batch is sample idx[r] of a dataset
 // resident on the device.  One block copies V * 256 bytes of one row.  An index outside the dataset

@@ -1,0 +1,57 @@
+"""Member state in and out: the blob layout through the chunked transfer (sizes around its chunk and thread
+boundaries) and the seeded initial weights against their definition, value for value."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from paper_2002_02885_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def _pack(models, in_shape, dtype="f32", seed=0):
+    return binding.Pack(2, in_shape, dtype, models, seed=seed)
+
+
+# a linear layer alone has D * C + C parameters; a transfer moves chunks of 2^18 floats, two per thread and four threads
+@pytest.mark.parametrize("D,C", [(1, 1), (5, 3), (87381, 3), (131071, 2), (131072, 2), (524287, 2), (1048573, 2), (1300001, 2)])
+def test_blob_round_trip_around_chunk_boundaries(D, C):
+    pk = _pack([[("linear", C)]], (1, 1, D))
+    blob = np.random.default_rng(D).standard_normal(D * C + C).astype(np.float32)
+    pk.write_weights(0, blob)
+    assert np.array_equal(pk.read_weights(0), blob)
+    pk.set_optimizer(0, {"kind": "adagrad", "acc0": 0.25})
+    state, steps = pk.read_opt_state(0, 0)
+    assert steps == 0 and np.all(state == np.float32(0.25))
+    pk.write_opt_state(0, 0, np.abs(blob), 3)
+    state, steps = pk.read_opt_state(0, 0)
+    assert steps == 3 and np.array_equal(state, np.abs(blob)) and np.array_equal(pk.read_weights(0), blob)
+    pk.destroy()
+
+
+def _splitmix(x):
+    x = (x + np.uint64(0x9E3779B97F4A7C15))
+    x = (x ^ (x >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+    x = (x ^ (x >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+    return x ^ (x >> np.uint64(31))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_seeded_weights_follow_their_definition(dtype):
+    layers = [("conv3x3", 5, 2), ("relu",), ("conv3x3", 9, 1), ("relu",), ("linear", 7), ("tanh",), ("linear", 3)]
+    in_shape, seed = (6, 5, 3), 77
+    pk = _pack([[("linear", 4)], layers], in_shape, dtype, seed)
+    got, want, tensor = pk.read_weights(1), [], 0
+    with np.errstate(over="ignore"):
+        base = _splitmix(np.uint64(seed) ^ (np.uint64(1) << np.uint64(32)))
+        for _, ws, bs, fan_in in wl.param_shapes(layers, in_shape):
+            for shape, bound in ((ws, np.sqrt(np.float32(6.0) / np.float32(fan_in))), (bs, np.float32(1.0) / np.sqrt(np.float32(fan_in)))):
+                h = _splitmix(_splitmix(base ^ np.uint64(tensor)) ^ np.arange(int(np.prod(shape)), dtype=np.uint64))
+                u = (h >> np.uint64(11)).astype(np.float64) / 9007199254740992.0
+                want.append(((2.0 * u - 1.0) * np.float64(np.float32(bound))).astype(np.float32))
+                tensor += 1
+    want = np.concatenate(want)
+    if dtype == "bf16":
+        want = wl.to_bf16_representable(want)
+    assert np.array_equal(got, want)
+    pk.destroy()

@@ -24,6 +24,7 @@ thread_local std::vector<LoadRec>* g_log = nullptr;
 
 #define PACK_TID (::packk::g_tid)
 inline int pack_uniform(int v) { return v; }
+inline unsigned pack_umulhi(unsigned a, unsigned b) { return (unsigned)(((unsigned long long)a * b) >> 32); }
 inline u32x4_t buf_load16(const i32x4_t rsrc, unsigned voff, unsigned soff) {
     g_log->push_back(LoadRec{(unsigned long long)(unsigned)rsrc.x | ((unsigned long long)(unsigned)rsrc.y << 32), (unsigned)rsrc.z, voff, soff});
     return u32x4_t{0u, 0u, 0u, 0u};
@@ -124,7 +125,7 @@ std::string check_loads(const GemmProb& p, const std::vector<LoadRec>& log, int 
     return std::string();
 }
 
-template <int MODE, typename T, int BM, int BN>
+template <int MODE, typename T, int BM, int BN, bool GEN>
 std::string walk_tile(const GemmProb& p, const TileRef& tr, Span& sa, Span& sb, long long* loads) {
     constexpr int BK = ET<T>::BK;
     typedef TileGeom<T, BM, BK> GA;
@@ -137,8 +138,8 @@ std::string walk_tile(const GemmProb& p, const TileRef& tr, Span& sa, Span& sb, 
     g_log = &log;
     for (int tid = 0; tid < 256; ++tid) {
         g_tid = tid;
-        Fetcher<MODE, T, true, BM, BK, true> fa;
-        Fetcher<MODE, T, false, BN, BK, true> fb;
+        Fetcher<MODE, T, true, BM, BK, true, GEN> fa;
+        Fetcher<MODE, T, false, BN, BK, true, GEN> fb;
         fa.init(p, row0);
         fb.init(p, col0);
         u32x4_t ra[GA::NREG], rb[GB::NREG];
@@ -160,9 +161,17 @@ std::string walk_tile(const GemmProb& p, const TileRef& tr, Span& sa, Span& sb, 
 
 template <int MODE, typename T>
 std::string walk_shape(int bm, int bn, const GemmProb& p, const TileRef& tr, Span& sa, Span& sb, long long* loads) {
-    if (bm == 128 && bn == 128) return walk_tile<MODE, T, 128, 128>(p, tr, sa, sb, loads);
-    if (bm == 128 && bn == 64) return walk_tile<MODE, T, 128, 64>(p, tr, sa, sb, loads);
-    if (bm == 64 && bn == 64) return walk_tile<MODE, T, 64, 64>(p, tr, sa, sb, loads);
+    if constexpr (MODE == CONV_FWD || MODE == CONV_DX || MODE == CONV_DW) {
+        if (p.flags & F_GATHER) {
+            if (bm == 128 && bn == 128) return walk_tile<MODE, T, 128, 128, true>(p, tr, sa, sb, loads);
+            if (bm == 128 && bn == 64) return walk_tile<MODE, T, 128, 64, true>(p, tr, sa, sb, loads);
+            if (bm == 64 && bn == 64) return walk_tile<MODE, T, 64, 64, true>(p, tr, sa, sb, loads);
+            return "no aligned kernel has this tile shape";
+        }
+    }
+    if (bm == 128 && bn == 128) return walk_tile<MODE, T, 128, 128, false>(p, tr, sa, sb, loads);
+    if (bm == 128 && bn == 64) return walk_tile<MODE, T, 128, 64, false>(p, tr, sa, sb, loads);
+    if (bm == 64 && bn == 64) return walk_tile<MODE, T, 64, 64, false>(p, tr, sa, sb, loads);
     return "no aligned kernel has this tile shape";
 }
 

@@ -48,7 +48,8 @@ struct TensorInfo {
     int act_out = 0;         // ActKind the tensor was produced through: gradients written to it take its derivative
     bool needs_grad = false;
     bool grad_written = false;
-    int ld_dz = 0;           // leading dimension of dz when padded (logits), 0 = c
+    int pitch = 0;           // channels a pixel is stored with: c rounded up to 8 (the padding zero), c itself for the input and the logits
+    int ld_dz = 0;           // leading dimension of dz when padded (logits), 0 = pitch
     // planning state: the gradient that reaches this tensor through a residual shortcut and is added
     // by the input-gradient product of the block's first convolution instead of a kernel of its own
     const void* sc_dz = nullptr;
@@ -56,7 +57,7 @@ struct TensorInfo {
     bool sc_down = false;
     void* act = nullptr;
     void* dz = nullptr;
-    size_t elems() const { return (size_t)n * h * w * c; }
+    size_t elems() const { return (size_t)n * h * w * pitch; }   // as stored
 };
 
 struct NodeInfo {
@@ -68,13 +69,19 @@ struct NodeInfo {
     bool res_down = false;
     size_t w_off = 0, b_off = 0;   // element offsets into the parameter arena
     size_t w_elems = 0;      // weights in the public blob
-    size_t w_arena = 0;      // weights in the arena (rows padded to `kp` for im2col convolutions)
+    size_t w_arena = 0;      // weights in the arena, `out` rows of `ldw`
+    int ldw = 0;             // row of W in the arena: whole groups of 8 channels per tap / pixel (`kp` for im2col convolutions)
+    int cpad = 0;            // channels stored per tap / pixel of such a row
     int kp = 0;              // > 0: first-layer convolution executed over the shared im2col buffer
     int im2col_idx = -1;     // which shared buffer (pack_ctx::im2col)
+    bool in_copy = false;    // the input is read through a padded copy, its rows flat (LINEAR) or per pixel
+    int copy_idx = -1;       // which one (pack_ctx::im2col)
+    int res_copy_idx = -1;   // a shortcut from the input: its padded copy, -1 = none needed
     int fan_in = 0;
     size_t blob_off = 0;     // float offset of W in the member's public blob
     bool has_wt = false;     // convolution with an input gradient: a transposed copy of W is kept per step
     size_t wt_off = 0;       // element offset of that copy in pack_ctx::wt
+    size_t wt_elems = 0;
 };
 
 struct ModelInfo {
@@ -153,7 +160,6 @@ struct pack_ctx {
     bool keep_grads = false;          // fused packs: store the gradients as well (pack_read_grads)
     size_t head_desc_off = 0;         // problem table of the classifier-head launch
     int n_heads = 0;
-    std::vector<long long> im2col_xoff;   // byte offset of each loader's source in the step's input
     std::vector<Launch> plan;
     size_t device_bytes = 0;
     // per-launch timing (off unless pack_profile_start was called)
@@ -174,7 +180,8 @@ struct pack_ctx {
 namespace {
 
 // The tensors of a member's public blob and where they lie in the arenas.  linear: rows as they are.  conv: blob
-// [Cout][Cin][3][3], arena [Cout][3][3][Cin] (rows padded to `kp` for im2col convolutions; padding stays zero).
+// [Cout][Cin][3][3], arena [Cout][3][3][Cin].  The channels of a pixel or tap are padded to whole groups of 8 in the
+// arena (rows to `kp` for im2col convolutions); the padding stays zero.
 std::vector<BlobSeg> blob_segments(const ModelInfo& m) {
     std::vector<BlobSeg> segs;
     int tensor = 0;
@@ -184,9 +191,10 @@ std::vector<BlobSeg> blob_segments(const ModelInfo& m) {
         w.blob_off = (long long)nd.blob_off;
         w.arena_off = (long long)(nd.w_off - m.arena_begin);
         w.inner = nd.fan_in;
-        w.ldw = nd.kp ? nd.kp : nd.fan_in;
+        w.ldw = nd.ldw;
         w.conv = nd.kind == NODE_CONV;
-        w.cin = w.cpad = w.conv ? nd.fan_in / 9 : nd.fan_in;
+        w.cin = m.tensors[nd.in_t].is_input && !w.conv ? nd.fan_in : m.tensors[nd.in_t].c;   // (a LINEAR on the input sees flat rows)
+        w.cpad = nd.cpad;
         w.tensor = tensor;
         w.bound = std::sqrt(6.0f / (float)nd.fan_in);
         BlobSeg b{};
@@ -210,7 +218,8 @@ pack_status parse_model(const pack_input_spec& in, const pack_model_spec& spec, 
     m.batch = spec.batch;
     m.layers.assign(spec.layers, spec.layers + spec.n_layers);
     TensorInfo t0;
-    t0.n = spec.batch; t0.h = in.in_h; t0.w = in.in_w; t0.c = in.in_c; t0.is_input = true;
+    t0.n = spec.batch; t0.h = in.in_h; t0.w = in.in_w; t0.c = t0.pitch = in.in_c; t0.is_input = true;
+    const int V = in.dtype == PACK_BF16 ? 8 : 4;
     m.tensors.push_back(t0);
     int cur = 0;
     std::vector<int> res_stack;
@@ -241,12 +250,24 @@ pack_status parse_model(const pack_input_spec& in, const pack_model_spec& spec, 
                     o.w = (src.w - 1) / L.stride + 1;
                 }
                 o.c = L.out;
+                o.pitch = (int)align_up((size_t)L.out, 8);
                 nd.w_elems = (size_t)L.out * nd.fan_in;
-                nd.w_arena = nd.w_elems;
                 if (L.op == PACK_CONV3X3 && src.is_input && nd.fan_in <= 32) {
                     nd.kp = 32;   // few input channels: run over the shared im2col buffer
-                    nd.w_arena = (size_t)L.out * nd.kp;
+                    nd.cpad = src.c;
+                    nd.ldw = nd.kp;
+                } else if (L.op == PACK_CONV3X3) {
+                    nd.in_copy = src.is_input && src.c % 8 != 0;
+                    nd.cpad = (int)align_up((size_t)src.c, 8);
+                    nd.ldw = 9 * nd.cpad;
+                } else if (src.is_input) {
+                    nd.in_copy = nd.fan_in % V != 0;
+                    nd.cpad = nd.ldw = (int)align_up((size_t)nd.fan_in, 8);
+                } else {
+                    nd.cpad = src.pitch;
+                    nd.ldw = src.h * src.w * src.pitch;
                 }
+                nd.w_arena = (size_t)L.out * nd.ldw;
                 nd.blob_off = blob_off;
                 blob_off += nd.w_elems + L.out;
                 if (next_op == PACK_RELU || next_op == PACK_SIGMOID || next_op == PACK_TANH || next_op == PACK_LEAKY_RELU) {
@@ -282,7 +303,7 @@ pack_status parse_model(const pack_input_spec& in, const pack_model_spec& spec, 
                 nd.kind = NODE_GAP;
                 nd.in_t = cur;
                 TensorInfo o;
-                o.n = src.n; o.h = o.w = 1; o.c = src.c;
+                o.n = src.n; o.h = o.w = 1; o.c = src.c; o.pitch = src.pitch;
                 m.tensors.push_back(o);
                 nd.out_t = (int)m.tensors.size() - 1;
                 m.nodes.push_back(nd);
@@ -307,6 +328,7 @@ pack_status parse_model(const pack_input_spec& in, const pack_model_spec& spec, 
     if (m.nodes.empty() || m.nodes.back().kind != NODE_LINEAR || m.nodes.back().act)
         return fail(PACK_ESHAPE, who + "the layer list must end in a LINEAR layer producing the logits");
     m.tensors[cur].f32 = true;
+    m.tensors[cur].pitch = m.tensors[cur].c;   // logits as the caller reads them
     // The gradient wrt the logits keeps its rows padded to whole 16-byte vectors; the padding is
     // zeroed once at creation and never written, so the classifier's backward products read it
     // with aligned vector loads whatever the number of classes.
@@ -490,7 +512,7 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
         return is_input ? std::make_pair(1, x_off) : std::make_pair(0, (long long)(uintptr_t)ptr);
     };
     for (const GemmProb& g : probs) {
-        L.flops += 2.0 * g.R * g.Q * g.Kd;
+        L.flops += 2.0 * g.R * g.Q * (g.kd_real ? g.kd_real : g.Kd);
         const double out = (double)g.R * g.Q;
         double a = 0, b = 0, c = 0;
         switch (mode) {
@@ -517,6 +539,8 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
     for (const auto& kv : shared_b) L.bytes += kv.second * esz;
     p->plan.push_back(L);
 }
+
+void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vector<GemmProb>& probs, bool general);
 
 void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<GemmProb>& all_probs_in) {
     // PACK_GENERAL_TAIL: every forward / input-gradient tile takes the general form of the tail, for the test that
@@ -548,7 +572,7 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
                 default:
                     ea = (double)g.Kd * g.lda;
                     eb = (double)g.Kd / (g.Ho * g.Wo) * g.H * g.W * g.Cin + (g.W + 1) * g.Cin;
-                    if (g.Wo < 4) vec = false;
+                    if (g.Wo < 4 && !(g.flags & F_GATHER)) vec = false;
                     break;
             }
             if (ea * esz >= 2.0e9 || eb * esz >= 2.0e9) vec = false;
@@ -569,7 +593,8 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
         // PACK_NO_HALO_DW keeps them on the staged-tile form, for the test that compares the two bit for bit.
         std::vector<GemmProb> halo[3], rest;
         for (const GemmProb& g : probs) {
-            const int cfg = conv_dw_halo_cfg(p->bf16, g);
+            // (padded channels stay on the staged tiles, whose tail keeps the padding of the weights zero)
+            const int cfg = (g.pad_c || g.R != g.Cout) ? -1 : conv_dw_halo_cfg(p->bf16, g);
             if (cfg >= 0) halo[cfg - GEMM_CFG_HALO_S1].push_back(g);
             else rest.push_back(g);
         }
@@ -592,6 +617,20 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
             if (!rows[c].empty()) emit_gemm_launch(p, db, mode, GEMM_CFG_ROWS64 + c, rows[c]);
         probs.swap(rest);
     }
+    if (probs.empty()) return;
+    if (mode == CONV_FWD || mode == CONV_DX || mode == CONV_DW) {
+        // convolutions whose chunks straddle taps, images or rows: the same tiles with the general gather (GEMM_CFG_GATHER0)
+        std::vector<GemmProb> gen, rest;
+        for (const GemmProb& g : probs) ((g.flags & F_GATHER) ? gen : rest).push_back(g);
+        add_tiled_launches(p, db, mode, gen, true);
+        probs.swap(rest);
+        if (probs.empty()) return;
+    }
+    add_tiled_launches(p, db, mode, probs, false);
+}
+
+// problems with aligned operands onto the staged-tile kernels
+void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vector<GemmProb>& probs, bool general) {
     if (probs.empty()) return;
     // The tile shape only partitions the output; the summation order of an element does not
     // depend on it, so a member's bits do not depend on who else is in the launch.  Each problem
@@ -633,7 +672,8 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
             const int eff = (work[want[i]] < 0.15 * total) ? main_cfg : want[i];
             if (eff != c) continue;
             const int chunks = (std::min(probs[i].Kd, probs[i].ksplit) + chunk_k - 1) / chunk_k;
-            if (c == 0 && lean_ok && chunks <= 8) lean.push_back(probs[i]);
+            if (general) group.push_back(probs[i]);
+            else if (c == 0 && lean_ok && chunks <= 8) lean.push_back(probs[i]);
             else if (c == 1 && !is_dw && chunks <= lean64_chunks) lean.push_back(probs[i]);
             else group.push_back(probs[i]);
         }
@@ -642,7 +682,7 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
             lean.clear();
         }
         if (!lean.empty()) emit_gemm_launch(p, db, mode, is_dw ? GEMM_CFG_LEAN : GEMM_CFG_LEAN64, lean);
-        if (!group.empty()) emit_gemm_launch(p, db, mode, c, group);
+        if (!group.empty()) emit_gemm_launch(p, db, mode, general ? GEMM_CFG_GATHER0 + c : c, group);
     }
 }
 
@@ -664,9 +704,26 @@ void add_mapped_launch(pack_ctx* p, DescBuilder& db, int kind, const std::vector
 
 inline int elem_vec(bool bf16) { return bf16 ? 8 : 4; }
 
-// the gather kernels index with 32-bit element offsets
-inline bool small_tensors(const TensorInfo& a, const TensorInfo& b) {
-    return a.elems() < (size_t)1 << 30 && b.elems() < (size_t)1 << 30;
+// the aligned kernels address an operand inside a 2 GB window (some room left for a convolution's margin of a row and
+// a pixel), and divide by the channels of a tap and the pixels of a map with 32-bit multipliers
+inline bool small_tensors(const TensorInfo& a, const TensorInfo& b, bool bf16) {
+    auto ok = [&](const TensorInfo& t) {
+        const double px = (double)t.h * t.w, c = (double)align_up((size_t)t.c, 8);
+        return t.n * px * c * (bf16 ? 2 : 4) < 1.8e9 && (t.w + 1) * c * (bf16 ? 2 : 4) < 1e8 && px < 60000 && c < 16384;
+    };
+    return ok(a) && ok(b);
+}
+
+// row of a LINEAR layer's input as the products see it: the features, padding between the channels of pixels included
+inline int inner_dim(const ModelInfo& m, const NodeInfo& nd) {
+    const TensorInfo& t = m.tensors[nd.in_t];
+    return t.is_input || t.h * t.w == 1 ? nd.fan_in : nd.ldw;
+}
+// and the distance of those rows
+inline int row_pitch(const pack_ctx* p, const ModelInfo& m, const NodeInfo& nd) {
+    const TensorInfo& t = m.tensors[nd.in_t];
+    if (nd.in_copy) return p->im2col[nd.copy_idx].Kp;
+    return t.is_input ? nd.fan_in : t.h * t.w * t.pitch;
 }
 
 // Builds the whole launch sequence.  Workspace offsets are relative; `ws_need` returns the size.
@@ -688,12 +745,11 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
     };
 
     // ---------------- shared-input loader ----------------
-    for (size_t i = 0; i < p->im2col.size(); ++i) {
-        Launch L;
-        L.kind = L_IM2COL;
-        L.mode = (int)i;
-        L.n = 1;
-        p->plan.push_back(L);
+    {
+        std::vector<int> blocks;
+        for (const Im2colProb& ip : p->im2col)
+            blocks.push_back((int)(((long long)ip.B * ip.Ho * ip.Wo * (ip.Kp / V) + 255) / 256));
+        add_mapped_launch(p, db, L_IM2COL, p->im2col, blocks);
     }
 
     // ---------------- forward ----------------
@@ -708,9 +764,9 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
             const TensorInfo& to = m.tensors[nd.out_t];
             if (nd.kind == NODE_GAP) {
                 GapProb g{};
-                g.in = ti.act; g.out = to.act; g.n = ti.n; g.hw = ti.h * ti.w; g.c = ti.c;
+                g.in = ti.act; g.out = to.act; g.n = ti.n; g.hw = ti.h * ti.w; g.c = ti.pitch;
                 gaps.push_back(g);
-                gap_blocks.push_back((ti.n * ti.c + 255) / 256);
+                gap_blocks.push_back((ti.n * ti.pitch + 255) / 256);
                 continue;
             }
             if (m.fused_head && s + 1 == m.nodes.size()) continue;   // part of the head kernel
@@ -721,12 +777,30 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
             g.B = weight_ptr(nd);
             g.C = to.act;
             g.bias = p->master + nd.b_off;
-            g.flags = (nd.act == ACT_RELU ? F_RELU : 0) | (to.f32 ? F_OUT_F32 : 0) | (ti.is_input ? F_A_INPUT : 0);
+            g.flags = (nd.act == ACT_RELU ? F_RELU : 0) | (to.f32 ? F_OUT_F32 : F_PAD_OUT) | (ti.is_input ? F_A_INPUT : 0);
             g.act = nd.act;
+            g.kd_real = nd.fan_in;
+            if (nd.kind != NODE_LINEAR && nd.res_src >= 0) {
+                const TensorInfo& rs = m.tensors[nd.res_src];
+                g.aux = rs.is_input ? nullptr : rs.act;
+                g.resC = rs.pitch;
+                if (nd.res_copy_idx >= 0) {
+                    g.aux = p->im2col[nd.res_copy_idx].out;
+                    g.resC = p->im2col[nd.res_copy_idx].Kp;
+                } else if (rs.is_input) {
+                    g.flags |= F_AUX_INPUT;
+                }
+                g.flags |= nd.res_down ? F_RES_DOWN : F_RES_ID;
+                g.resH = rs.h; g.resW = rs.w;
+            }
+            if (nd.in_copy) {
+                g.A = p->im2col[nd.copy_idx].out;
+                g.flags &= ~F_A_INPUT;
+            }
             if (nd.kind == NODE_LINEAR) {
-                g.R = ti.n; g.Q = nd.out; g.Kd = nd.fan_in;
-                g.lda = nd.fan_in; g.ldb = nd.fan_in; g.ldc = nd.out;
-                if (g.Kd % V == 0) g.flags |= F_VEC_A | F_VEC_B;
+                g.R = ti.n; g.Q = nd.out; g.Kd = inner_dim(m, nd);
+                g.lda = row_pitch(p, m, nd); g.ldb = nd.ldw; g.ldc = to.pitch;
+                g.flags |= F_VEC_A | F_VEC_B;
                 g.ksplit = g.Kd;
                 lin.push_back(g);
             } else if (nd.kp) {
@@ -735,32 +809,20 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 g.flags &= ~F_A_INPUT;
                 g.H = ti.h; g.W = ti.w; g.Cin = ti.c; g.Ho = to.h; g.Wo = to.w; g.Cout = to.c; g.stride = nd.stride;
                 g.R = to.n * to.h * to.w; g.Q = to.c; g.Kd = nd.kp;
+                g.kd_real = 0;
                 set_row_space(g, to.w, to.h * to.w);
-                g.lda = nd.kp; g.ldb = nd.kp; g.ldc = to.c;
+                g.lda = nd.kp; g.ldb = nd.kp; g.ldc = to.pitch;
                 g.flags |= F_VEC_A | F_VEC_B;
-                if (nd.res_src >= 0) {
-                    const TensorInfo& rs = m.tensors[nd.res_src];
-                    g.aux = rs.is_input ? nullptr : rs.act;
-                    if (rs.is_input) g.flags |= F_AUX_INPUT;
-                    g.flags |= nd.res_down ? F_RES_DOWN : F_RES_ID;
-                    g.resH = rs.h; g.resW = rs.w; g.resC = rs.c;
-                }
                 g.ksplit = g.Kd;
                 lin.push_back(g);
             } else {
-                g.H = ti.h; g.W = ti.w; g.Cin = ti.c; g.Ho = to.h; g.Wo = to.w; g.Cout = to.c; g.stride = nd.stride;
-                g.R = to.n * to.h * to.w; g.Q = to.c; g.Kd = 9 * ti.c;
+                g.H = ti.h; g.W = ti.w; g.Cin = nd.cpad; g.Ho = to.h; g.Wo = to.w; g.Cout = to.pitch; g.stride = nd.stride;
+                g.R = to.n * to.h * to.w; g.Q = to.c; g.Kd = nd.ldw;
                 set_row_space(g, to.w, to.h * to.w);
-                g.lda = ti.c; g.ldb = 9 * ti.c; g.ldc = to.c;
-                // vector path of the gathered operand: a chunk must stay inside one tap
-                if (ti.c % BKc == 0 && small_tensors(ti, to)) g.flags |= F_VEC_A | F_VEC_B;
-                if (nd.res_src >= 0) {
-                    const TensorInfo& rs = m.tensors[nd.res_src];
-                    g.aux = rs.is_input ? nullptr : rs.act;
-                    if (rs.is_input) g.flags |= F_AUX_INPUT;
-                    g.flags |= nd.res_down ? F_RES_DOWN : F_RES_ID;
-                    g.resH = rs.h; g.resW = rs.w; g.resC = rs.c;
-                }
+                g.lda = nd.cpad; g.ldb = nd.ldw; g.ldc = to.pitch;
+                // a chunk that stays inside one tap needs no per-thread tap
+                if (small_tensors(ti, to, bf)) g.flags |= F_VEC_A | F_VEC_B | (nd.cpad % BKc ? F_GATHER : 0);
+                g.mg_span = div_multiplier(nd.cpad);
                 g.ksplit = g.Kd;
                 conv.push_back(g);
             }
@@ -785,7 +847,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 h.h = ti.act; h.W = weight_ptr(nd); h.bias = p->master + nd.b_off;
                 h.logits = (float*)lg.act; h.dlogits = lg.dz; h.dh = ti.needs_grad ? ti.dz : nullptr;
                 h.pred = m.pred; h.loss = m.loss; h.partial = m.head_partial;
-                h.rows = m.batch; h.C = m.C; h.Kd = nd.fan_in; h.ldd = lg.ld_dz;
+                h.rows = m.batch; h.C = m.C; h.Kd = nd.ldw; h.ldd = lg.ld_dz;
                 h.label_off = p->own_input ? (int)(&m - p->models.data()) * p->in.B : 0;
                 h.mask_act = ti.act_out;
                 h.nblk = (m.batch + HEAD_ROWS - 1) / HEAD_ROWS;
@@ -833,6 +895,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 t.src = weight_ptr(nd);
                 t.dst = (char*)p->wt + nd.wt_off * esz;
                 t.Cin = m.tensors[nd.in_t].c; t.Cout = nd.out;
+                t.ld_src = nd.cpad; t.ld_dst = m.tensors[nd.out_t].pitch;
                 t.tiles_ci = (t.Cin + 63) / 64; t.tiles_co = (t.Cout + 63) / 64;
                 tps.push_back(t);
                 tp_blocks.push_back(9 * t.tiles_ci * t.tiles_co);
@@ -857,7 +920,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
             if (nd.kind == NODE_GAP) {
                 if (!ti.needs_grad) continue;
                 GapProb g{};
-                g.in = ti.act; g.dz_out = to.dz; g.dz_in = ti.dz; g.n = ti.n; g.hw = ti.h * ti.w; g.c = ti.c;
+                g.in = ti.act; g.dz_out = to.dz; g.dz_in = ti.dz; g.n = ti.n; g.hw = ti.h * ti.w; g.c = ti.pitch;
                 g.mask = ti.act_out; g.accum = ti.grad_written;
                 ti.grad_written = true;
                 gaps.push_back(g);
@@ -873,27 +936,33 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 g.A = to.dz;
                 g.B = ti.is_input ? nullptr : ti.act;
                 g.flags = ti.is_input ? F_B_INPUT : 0;
-                const int q_dim = nd.kp ? nd.kp : nd.fan_in;   // columns of the weight matrix in the arena
+                const int q_dim = nd.kind == NODE_LINEAR ? inner_dim(m, nd) : nd.ldw;   // columns of the weight matrix in the arena
                 g.R = nd.out; g.Q = q_dim; g.Kd = rows;
-                g.lda = to.ld_dz ? to.ld_dz : nd.out; g.ldc = q_dim;
-                if (g.lda % V == 0) g.flags |= F_VEC_A;
+                g.lda = to.ld_dz ? to.ld_dz : to.pitch; g.ldc = nd.ldw;
+                g.flags |= F_VEC_A | F_VEC_B;
                 float* dst = p->grad + nd.w_off;
                 const bool dense = (nd.kind == NODE_LINEAR) || nd.kp;
+                if (nd.in_copy) {
+                    g.B = p->im2col[nd.copy_idx].out;
+                    g.flags &= ~F_B_INPUT;
+                }
+                if (!nd.kp && q_dim > nd.fan_in) { g.pad_c = nd.cpad; g.pad_real = ti.c; }   // padding between the channels of a pixel or tap
                 if (dense) {
-                    g.ldb = q_dim;
+                    g.ldb = nd.kp ? nd.kp : row_pitch(p, m, nd);
                     if (nd.kp) {
                         g.B = p->im2col[nd.im2col_idx].out;
                         g.flags &= ~F_B_INPUT;
                     }
-                    if (q_dim % V == 0) g.flags |= F_VEC_B;
                 } else {
-                    g.H = ti.h; g.W = ti.w; g.Cin = ti.c; g.Ho = to.h; g.Wo = to.w; g.Cout = to.c; g.stride = nd.stride;
-                    g.ldb = ti.c;
-                    // vector path of the gathered input: chunks of output pixels must stay inside
-                    // one image and rows must decode by shifts
+                    g.H = ti.h; g.W = ti.w; g.Cin = nd.cpad; g.Ho = to.h; g.Wo = to.w; g.Cout = to.pitch; g.stride = nd.stride;
+                    g.ldb = nd.cpad;
+                    // chunks of output pixels that stay inside one image, with rows that decode by shifts, need no
+                    // division per chunk
                     const bool pow2 = (to.w & (to.w - 1)) == 0;
-                    if (ti.c % V == 0 && pow2 && (to.h * to.w) % BKc == 0 && small_tensors(ti, to)) g.flags |= F_VEC_B;
-                    else g.flags &= ~F_VEC_A;
+                    if (!small_tensors(ti, to, bf)) g.flags &= ~(F_VEC_A | F_VEC_B);
+                    else if (!pow2 || to.w < 4 || (to.h * to.w) % BKc) g.flags |= F_GATHER;
+                    g.mg_hw = div_multiplier(to.h * to.w);
+                    g.mg_w = div_multiplier(to.w);
                 }
                 // long reductions (many pixels) are split over workgroups; the split length
                 // depends on the layer shape only, partial results are summed in split order
@@ -961,19 +1030,21 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 g.mask_act = ti.act_out;
                 ti.grad_written = true;
                 if (nd.kind == NODE_LINEAR) {
-                    g.R = ti.n; g.Q = nd.fan_in; g.Kd = nd.out;
-                    g.lda = to.ld_dz ? to.ld_dz : nd.out; g.ldb = nd.fan_in; g.ldc = nd.fan_in;
-                    if (g.lda % V == 0) g.flags |= F_VEC_A;
-                    if (nd.fan_in % V == 0) g.flags |= F_VEC_B;
+                    g.R = ti.n; g.Q = inner_dim(m, nd); g.Kd = nd.out;
+                    g.lda = to.ld_dz ? to.ld_dz : to.pitch; g.ldb = nd.ldw; g.ldc = nd.ldw;
+                    g.flags |= F_VEC_A | F_VEC_B | F_PAD_OUT;
                     g.ksplit = g.Kd;
                     lin_dx.push_back(g);
                 } else {
-                    g.H = ti.h; g.W = ti.w; g.Cin = ti.c; g.Ho = to.h; g.Wo = to.w; g.Cout = to.c; g.stride = nd.stride;
-                    g.R = ti.n * ti.h * ti.w; g.Q = ti.c; g.Kd = 9 * to.c;
+                    g.H = ti.h; g.W = ti.w; g.Cin = ti.pitch; g.Ho = to.h; g.Wo = to.w; g.Cout = to.pitch; g.stride = nd.stride;
+                    g.R = ti.n * ti.h * ti.w; g.Q = ti.c; g.Kd = 9 * to.pitch;
+                    g.kd_real = 9 * to.c;
                     set_row_space(g, ti.w, ti.h * ti.w);
                     g.B = (const char*)p->wt + nd.wt_off * esz;   // transposed copy [Cin][9][Cout]
-                    g.lda = to.c; g.ldb = 9 * to.c; g.ldc = ti.c;
-                    if (to.c % BKc == 0 && ti.c % V == 0 && small_tensors(ti, to)) g.flags |= F_VEC_A | F_VEC_B;
+                    g.lda = to.pitch; g.ldb = 9 * to.pitch; g.ldc = ti.pitch;
+                    g.flags |= F_PAD_OUT;
+                    if (small_tensors(ti, to, bf)) g.flags |= F_VEC_A | F_VEC_B | (to.pitch % BKc ? F_GATHER : 0);
+                    g.mg_span = div_multiplier(to.pitch);
                     g.ksplit = g.Kd;
                     const bool with_sc = ti.sc_dz != nullptr;
                     if (with_sc) {
@@ -995,7 +1066,8 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                                 c.cls_w = px ? (ti.w + 1) / 2 : ti.w / 2;
                                 c.R = ti.n * c.cls_h * c.cls_w;
                                 set_row_space(c, c.cls_w, c.cls_h * c.cls_w);
-                                c.Kd = (py ? 1 : 2) * (px ? 1 : 2) * to.c;
+                                c.Kd = (py ? 1 : 2) * (px ? 1 : 2) * to.pitch;
+                                c.kd_real = (py ? 1 : 2) * (px ? 1 : 2) * to.c;
                                 c.ksplit = c.Kd;
                                 if (py && px) c.flags |= sc_flag;   // pixels with even coordinates: the subsampling shortcut's
                                 if (c.R > 0) conv_dx.push_back(c);
@@ -1018,12 +1090,12 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 const bool fuse = readers == 1 && first >= 0 && first < (int)s && m.nodes[first].kind == NODE_CONV && !m.nodes[first].kp && !rs.grad_written &&
                                   !rs.is_input && !(nd.res_down && m.nodes[first].stride != 2) && !std::getenv("PACK_NO_FUSED_SHORTCUT");
                 if (fuse) {
-                    rs.sc_dz = to.dz; rs.sc_h = to.h; rs.sc_w = to.w; rs.sc_c = to.c; rs.sc_down = nd.res_down;
+                    rs.sc_dz = to.dz; rs.sc_h = to.h; rs.sc_w = to.w; rs.sc_c = to.pitch; rs.sc_down = nd.res_down;
                     continue;
                 }
                 ShortcutProb sp{};
                 sp.dz_out = to.dz; sp.src = rs.act; sp.dz_src = rs.dz;
-                sp.n = rs.n; sp.H = rs.h; sp.W = rs.w; sp.C = rs.c; sp.Ho = to.h; sp.Wo = to.w; sp.Co = to.c;
+                sp.n = rs.n; sp.H = rs.h; sp.W = rs.w; sp.C = rs.pitch; sp.Ho = to.h; sp.Wo = to.w; sp.Co = to.pitch;
                 sp.down = nd.res_down; sp.mask = rs.act_out; sp.accum = rs.grad_written;
                 rs.grad_written = true;
                 scs.push_back(sp);
@@ -1114,6 +1186,14 @@ const BlobSeg* member_segs(const pack_ctx* p, int k) { return (const BlobSeg*)(p
 pack_status upload_weights(pack_ctx* p, int k, const float* blob) {
     const ModelInfo& m = p->models[k];
     void* const shadow = p->bf16 ? (void*)((char*)p->shadow + m.arena_begin * 2) : nullptr;
+    // a member that has diverged may have left something else than zero in the padding of its rows
+    bool padded = false;
+    for (const NodeInfo& nd : m.nodes) padded = padded || (nd.kind != NODE_GAP && nd.ldw != nd.fan_in);
+    if (padded) {
+        const long long seg = (long long)(m.arena_end - m.arena_begin);
+        HIP_TRY(launch_fill_zero(p->master + m.arena_begin, seg * 4, p->stream), PACK_EDEVICE);
+        if (shadow) HIP_TRY(launch_fill_zero(shadow, seg * 2, p->stream), PACK_EDEVICE);
+    }
     HIP_TRY(import_blob(p->device, p->stream, p->master + m.arena_begin, shadow, member_segs(p, k), m.n_segs, m.n_params, blob), PACK_EDEVICE);
     return PACK_OK;
 }
@@ -1174,6 +1254,7 @@ pack_status build_device(pack_ctx* p) {
         TRY_ALLOC(p->opt_params, (size_t)K * sizeof(OptStatic));
     }
     if (need_v) TRY_ALLOC(p->opt_v, p->arena_elems * 4);
+    size_t wt_bytes = 0;
     {
         size_t wt_elems = 0;
         for (ModelInfo& m : p->models)
@@ -1181,35 +1262,43 @@ pack_status build_device(pack_ctx* p) {
                 if (nd.kind != NODE_CONV || nd.kp || !m.tensors[nd.in_t].needs_grad) continue;
                 nd.has_wt = true;
                 nd.wt_off = wt_elems;
-                wt_elems = align_up(wt_elems + nd.w_elems, 64);
+                nd.wt_elems = (size_t)m.tensors[nd.in_t].c * 9 * m.tensors[nd.out_t].pitch;
+                wt_elems = align_up(wt_elems + nd.wt_elems, 64);
             }
         if (wt_elems) TRY_ALLOC(p->wt, wt_elems * esz);
+        wt_bytes = wt_elems * esz;
     }
 
     // one slab for activations, their gradients, predictions, losses and the label-error flag
     size_t slab = 0;
     auto reserve = [&](size_t bytes) { const size_t o = slab; slab += align_up(std::max<size_t>(bytes, 16), 256); return o; };
     std::vector<std::pair<void**, size_t>> fix;
-    // shared im2col buffers: one per stride used by a first-layer convolution over few channels
-    p->im2col_xoff.clear();
+    // Shared-input loaders: im2col buffers (one per stride used by a first-layer convolution over few channels) and
+    // padded copies of an input whose rows or pixels are no whole 16-byte vectors.  Members that share the input share
+    // the loaders too.
+    auto loader = [&](const ModelInfo& m, int taps, int stride, int H, int W, int C, int Kp) {
+        const long long x_off = p->own_input ? (long long)(&m - p->models.data()) * input->B * input->in_h * input->in_w * input->in_c * (long long)esz : 0;
+        for (size_t i = 0; i < p->im2col.size(); ++i) {
+            const Im2colProb& o = p->im2col[i];
+            if (o.x_off == x_off && o.taps == taps && o.stride == stride && o.C == C && (!p->own_input || o.B == m.batch)) return (int)i;
+        }
+        Im2colProb ip{};
+        ip.B = p->own_input ? m.batch : input->B;
+        ip.H = H; ip.W = W; ip.C = C;
+        ip.stride = stride; ip.Kp = Kp; ip.taps = taps; ip.x_off = x_off;
+        ip.Ho = (H - 1) / stride + 1; ip.Wo = (W - 1) / stride + 1;
+        p->im2col.push_back(ip);
+        return (int)p->im2col.size() - 1;
+    };
     for (ModelInfo& m : p->models) {
         if (m.vacant) continue;
-        NodeInfo& nd = m.nodes[0];
-        if (!nd.kp) continue;
-        nd.im2col_idx = -1;
-        if (!p->own_input)   // one shared input: members with the same first-layer stride share one loader
-            for (size_t i = 0; i < p->im2col.size(); ++i)
-                if (p->im2col[i].stride == nd.stride) nd.im2col_idx = (int)i;
-        if (nd.im2col_idx < 0) {
-            Im2colProb ip{};
-            ip.B = p->own_input ? m.batch : input->B;
-            ip.H = input->in_h; ip.W = input->in_w; ip.C = input->in_c;
-            ip.stride = nd.stride; ip.Kp = nd.kp;
-            ip.Ho = (ip.H - 1) / nd.stride + 1; ip.Wo = (ip.W - 1) / nd.stride + 1;
-            p->im2col.push_back(ip);
-            p->im2col_xoff.push_back(p->own_input ? (long long)(&m - p->models.data()) * input->B * input->in_h *
-                                                        input->in_w * input->in_c * (long long)esz : 0);
-            nd.im2col_idx = (int)p->im2col.size() - 1;
+        for (NodeInfo& nd : m.nodes) {
+            const bool reads_input = m.tensors[nd.in_t].is_input;
+            if (reads_input && nd.kp) nd.im2col_idx = loader(m, 9, nd.stride, input->in_h, input->in_w, input->in_c, nd.kp);
+            if (reads_input && nd.in_copy)
+                nd.copy_idx = nd.kind == NODE_LINEAR ? loader(m, 1, 1, 1, 1, nd.fan_in, nd.ldw) : loader(m, 1, 1, input->in_h, input->in_w, input->in_c, nd.cpad);
+            if (nd.res_src >= 0 && m.tensors[nd.res_src].is_input && input->in_c % 8 != 0)
+                nd.res_copy_idx = loader(m, 1, 1, input->in_h, input->in_w, input->in_c, (int)align_up((size_t)input->in_c, 8));
         }
     }
     for (Im2colProb& ip : p->im2col)
@@ -1217,10 +1306,8 @@ pack_status build_device(pack_ctx* p) {
     for (ModelInfo& m : p->models) {
         if (m.vacant) continue;
         {   // few classes: logits, loss and the input gradient of the last layer in one kernel
-            const NodeInfo& last = m.nodes.back();
-            const TensorInfo& hin = m.tensors[last.in_t];
-            m.fused_head = !std::getenv("PACK_NO_FUSED_HEAD") && m.C <= HEAD_MAX_C && !hin.is_input &&
-                           last.fan_in % (p->bf16 ? 8 : 4) == 0;
+            const TensorInfo& hin = m.tensors[m.nodes.back().in_t];
+            m.fused_head = !std::getenv("PACK_NO_FUSED_HEAD") && m.C <= HEAD_MAX_C && !hin.is_input;
             if (m.fused_head) {
                 const int nblk = (m.batch + HEAD_ROWS - 1) / HEAD_ROWS;
                 fix.push_back({(void**)&m.head_partial, reserve((size_t)nblk * 4)});
@@ -1268,6 +1355,7 @@ pack_status build_device(pack_ctx* p) {
     if (e == hipSuccess) e = hipMemsetAsync(p->grad, 0, p->arena_elems * 4, p->stream);
     if (e == hipSuccess) e = hipMemsetAsync(p->master, 0, p->arena_elems * 4, p->stream);
     if (e == hipSuccess && p->shadow) e = hipMemsetAsync(p->shadow, 0, p->arena_elems * 2, p->stream);
+    if (e == hipSuccess && wt_bytes) e = hipMemsetAsync(p->wt, 0, wt_bytes, p->stream);   // (the padding of its rows is never written)
     if (e == hipSuccess && p->opt_m) e = hipMemsetAsync(p->opt_m, 0, p->arena_elems * 4, p->stream);
     if (e == hipSuccess && p->opt_v) e = hipMemsetAsync(p->opt_v, 0, p->arena_elems * 4, p->stream);
     std::vector<long long> ends(K);
@@ -1471,7 +1559,7 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
         const bool halo = L.mode == CONV_DW && is_halo_cfg(L.tile_cfg);
         const bool rows = (L.mode == CONV_FWD || L.mode == CONV_DX) && is_rows_cfg(L.tile_cfg);
         const int ci_t = halo ? GEMM_TILE_N[L.tile_cfg] / 9 : 0;      // input channels per tile
-        const bool staged = !halo && !rows && L.tile_cfg != GEMM_CFG_SCALAR;
+        const bool staged = !halo && !rows && L.tile_cfg != GEMM_CFG_SCALAR;   // (the general gather included)
         if (!halo && !rows && !staged) { ++skipped; continue; }      // the element-by-element kernels load by the definition itself
         ++walked;
         const GemmProb* probs = (const GemmProb*)(p->desc_host.data() + L.desc_off);
@@ -1633,7 +1721,7 @@ size_t pack_estimate_bytes(const pack_input_spec* input, const pack_model_spec* 
         if (nd.kind == NODE_GAP) continue;
         arena = align_up(arena + nd.w_arena, 64);
         arena = align_up(arena + (size_t)nd.out, 64);
-        if (nd.kind == NODE_CONV && !nd.kp && m.tensors[nd.in_t].needs_grad) wt = align_up(wt + nd.w_elems, 64);
+        if (nd.kind == NODE_CONV && !nd.kp && m.tensors[nd.in_t].needs_grad) wt = align_up(wt + (size_t)m.tensors[nd.in_t].c * 9 * m.tensors[nd.out_t].pitch, 64);
     }
     for (const TensorInfo& t : m.tensors) {
         if (t.is_input) continue;
@@ -1689,7 +1777,7 @@ static pack_status step_with_workspace(pack_t* p, const void* x_dev, const int32
             case L_GAP_FWD: e = launch_gap(bf, false, (const GapProb*)d, (const int2*)mp, L.n, p->stream); break;
             case L_GAP_BWD: e = launch_gap(bf, true, (const GapProb*)d, (const int2*)mp, L.n, p->stream); break;
             case L_SHORTCUT: e = launch_shortcut_bwd(bf, (const ShortcutProb*)d, (const int2*)mp, L.n, p->stream); break;
-            case L_IM2COL: e = launch_im2col(bf, p->im2col[L.mode], (const char*)x_dev + p->im2col_xoff[L.mode], p->stream); break;
+            case L_IM2COL: e = launch_im2col(bf, (const Im2colProb*)d, (const int2*)mp, L.n, x_dev, p->stream); break;
             case L_WTRANS: e = launch_wtranspose(bf, (const TransposeProb*)d, (const int2*)mp, L.n, p->stream); break;
             case L_SGD:
                 if (!p->any_opt) {

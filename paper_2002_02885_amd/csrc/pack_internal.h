@@ -46,8 +46,12 @@ enum GemmFlags : int {
     F_SC_DOWN = 32768, // likewise for the subsampling shortcut: pixel (2i, 2j) receives sc[b, i, j, col]
     F_WS = 65536,      // split weight gradient: C and dbias hold BYTE OFFSETS into the step's workspace (the
                        // buffer of partial sums the launch receives as an argument), not addresses
-    F_GENERAL_TAIL = 131072   // forward / input gradient: every tile takes the general form of the tail (set by a test
+    F_GENERAL_TAIL = 131072,  // forward / input gradient: every tile takes the general form of the tail (set by a test
                               // that compares it with the form whole tiles of the plain cases take)
+    F_GATHER = 262144, // convolution whose chunks of the reduction may straddle taps, images or rows of any width:
+                       // operands come through the general gather (GEMM_CFG_GATHER0 ..)
+    F_PAD_OUT = 524288 // output rows are stored in whole groups of 8 columns (ldc a multiple of 8, at least Q rounded
+                       // up): the columns from Q on hold zeros and are written as such
 };
 
 // activation kinds (paper Table 3); the value is also what GemmProb::act / mask_act hold
@@ -90,7 +94,15 @@ struct GemmProb {
     int member;                            // F_UPDATE: index into the step's learning-rate table
     const void* sc;                        // F_SC_ID / F_SC_DOWN: gradient wrt the block output [n, scH, scW, scC]
     int scH, scW, scC;
+    // Channels are stored in groups of 8 (Cin, Cout, resC, scC above are those stored counts, the padding zero).
+    int pad_c, pad_real;                   // weight gradients: columns q with q % pad_c >= pad_real are padding and stay zero (pad_c = 0: none)
+    int kd_real;                           // the reduction without padding (0: Kd), for the count of operations
+    unsigned mg_span, mg_hw, mg_w;         // F_GATHER: multipliers for divisions by the channels of a tap, Ho * Wo and Wo
 };
+
+// Exact quotients by multiply-high: n / d == umulhi(n, m) for n * d < 2^32, where m = floor(2^32 / d) + 1 (Granlund
+// and Montgomery); 0 stands for d = 1.
+inline unsigned div_multiplier(int d) { return d <= 1 ? 0u : (unsigned)(0x100000000ull / (unsigned)d + 1ull); }
 
 struct TileRef {      // one workgroup's job; prob < 0 marks a filler slot
     int prob;
@@ -151,9 +163,11 @@ struct ShortcutProb { // backward of the residual shortcut into the source tenso
     int accum;
 };
 
-struct Im2colProb {   // shared-input loader: x [B,H,W,C] -> xcol [B*Ho*Wo, Kp], k = tap*C + c, zero beyond 9*C
+struct Im2colProb {   // shared-input loader: x [B,H,W,C] -> out [B*Ho*Wo, Kp], k = tap*C + c, zero beyond taps * C
     void* out;
     int B, H, W, C, Ho, Wo, stride, Kp;
+    int taps;             // 9: the nine shifted views (im2col); 1: the rows as they are, padded to whole 16-byte vectors
+    long long x_off;      // bytes from the step's input pointer to the first element read
 };
 
 // One tensor of a member's public blob and where its elements lie in a parameter arena.  Element i of the tensor is
@@ -173,6 +187,7 @@ struct TransposeProb {   // convolution weights [Cout][9][Cin] -> [Cin][9][Cout]
     const void* src;
     void* dst;
     int Cin, Cout, tiles_ci, tiles_co;   // 64 x 64 tiles per tap
+    int ld_src, ld_dst;                  // stored channels: src [Cout][9][ld_src], dst [Cin][9][ld_dst]
 };
 
 
@@ -211,7 +226,7 @@ struct OptStatic { int kind; float mu, beta1, beta2, eps; };
 struct OptTable { float lr[256]; float c1[256]; float c2[256]; };   // c1, c2: Adam's 1/(1-beta1^t), 1/(1-beta2^t)
 hipError_t launch_opt(float* master, const float* grad, void* shadow_bf16, float* m, float* v, long long n,
                       const long long* seg_end_dev, const OptStatic* params_dev, int K, const OptTable& tab, hipStream_t st);
-hipError_t launch_im2col(bool bf16, const Im2colProb& p, const void* x_dev, hipStream_t st);
+hipError_t launch_im2col(bool bf16, const Im2colProb* probs_dev, const int2* map_dev, int n_blocks, const void* x_dev, hipStream_t st);
 hipError_t launch_wtranspose(bool bf16, const TransposeProb* probs_dev, const int2* map_dev, int n_blocks, hipStream_t st);
 // member state <-> blob (pack_state.hip): `arena` points at the member's first element, `shadow` at its first bf16
 // copy (or null), e0 .. e0 + n are blob elements, in / out are mapped host memory
@@ -235,8 +250,8 @@ hipError_t launch_gather_rows(const void* data, const int32_t* labels_all, const
 // 6, 7: the halo form of the convolution weight gradient (stride 1, stride 2): a tile is 64 output channels
 // x 64 input channels x all nine taps, i.e. 64 x 576 of the [Cout][9 * Cin] gradient
 // 8: the same with 32 input channels per tile (layers whose input channels are a multiple of 32 only; stride 1)
-constexpr int GEMM_TILE_M[11] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256};
-constexpr int GEMM_TILE_N[11] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32};
+constexpr int GEMM_TILE_M[14] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64};
+constexpr int GEMM_TILE_N[14] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64};
 constexpr int GEMM_CFG_SCALAR = 3;
 constexpr int GEMM_CFG_LEAN = 4;     // weight gradients, 128 x 128, short reductions
 constexpr int GEMM_CFG_LEAN64 = 5;   // forward / input gradients, 128 x 64, short reductions
@@ -247,6 +262,8 @@ inline bool is_halo_cfg(int cfg) { return cfg >= GEMM_CFG_HALO_S1 && cfg <= GEMM
 constexpr int GEMM_CFG_ROWS64 = 9;   // stride-1 convolution forward / input gradient, halo form, 256 pixels x 64 columns
 constexpr int GEMM_CFG_ROWS32 = 10;  // likewise, 256 pixels x 32 columns
 inline bool is_rows_cfg(int cfg) { return cfg == GEMM_CFG_ROWS64 || cfg == GEMM_CFG_ROWS32; }
+constexpr int GEMM_CFG_GATHER0 = 11; // 11..13: configurations 0..2 with the general gather (convolutions of any channel count and map)
+inline bool is_gather_cfg(int cfg) { return cfg >= GEMM_CFG_GATHER0 && cfg < GEMM_CFG_GATHER0 + 3; }
 constexpr int ELEMWISE_PER_BLOCK = 2048;   // elements one block of the elementwise kernels covers
 constexpr int SGD_PER_BLOCK = 2048;        // parameters one block of the update kernel covers (measured best of 1024..8192)
 

@@ -273,6 +273,9 @@ struct LdsBytes {
 // once, before the first read of `stage`: a caller that fills `stage` there (barrier, writes, barrier) has the
 // first batch's round trip run under that instead of after it.
 struct NoHook { __device__ __forceinline__ void operator()() const {} };
+// columns of an output row that are stored: all of Q, rounded up to whole groups of eight where the layout is (the rest zeros)
+__device__ __forceinline__ int stored_cols(const GemmProb& p) { return (p.flags & F_PAD_OUT) ? (p.Q + 7) & ~7 : p.Q; }
+
 template <int MODE, typename T, int BM, int BN, int MAXB = 4, class Hook = NoHook>
 __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, const int col0, float (*stage)[BN + 8],
                                             const float (&bias_v)[8], const bool vec_out, Hook staged = Hook()) {
@@ -319,7 +322,8 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
         static_assert(256 % GROUPS == 0 && NIT % BATCH == 0, "tile shape");
         const int lc = (threadIdx.x % GROUPS) * 8, lr0 = threadIdx.x / GROUPS;
         const int col = col0 + lc;
-        const bool full = col + 8 <= p.Q;
+        const int nreal = p.Q - col;                                  // columns of the thread's eight that exist
+        const bool full = col + 8 <= stored_cols(p);
         typedef typename std::conditional<sizeof(T) == 2, u32x4_t, f32x4_t>::type ev_t;   // 8 bf16 or 4 floats
         constexpr int EV = (sizeof(T) == 2) ? 1 : 2;   // vectors per 8 elements
         const bool col_ok = col < p.Q;   // (a thread beyond the last column still walks the loop: `staged` may hold barriers)
@@ -328,7 +332,7 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
         // of one stride, or the row's pixel for the parity classes of a stride-2 input gradient) and the flags are
         // looked at once per tile instead of once per row.  The arithmetic per element is that of the general form
         // below, operation for operation.
-        bool plain = !(p.flags & (F_RES_DOWN | F_SC_DOWN | F_GENERAL_TAIL)) && !out_f32 && row0 + BM <= p.R && col0 + BN <= p.Q;
+        bool plain = !(p.flags & (F_RES_DOWN | F_SC_DOWN | F_GENERAL_TAIL)) && !out_f32 && row0 + BM <= p.R && (col0 + BN <= p.Q || (p.flags & F_PAD_OUT));
         if constexpr (IS_FWD) plain = plain && ((p.flags & F_RELU) || !(p.act > ACT_RELU));
         else plain = plain && (!(p.flags & F_MASK) || p.mask_act == ACT_RELU);
         if (plain) {
@@ -348,6 +352,7 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
                 if (accum) op = (const T*)p.C;
                 if (add_sc) op = (const T*)p.sc;   // never together with F_ACCUM
             }
+            if (!col_ok) ap = op = nullptr;        // (beyond the last column: walks the loop for its barriers, touches nothing)
             T* const out = (T*)p.C;
 #pragma unroll 1
             for (int n0 = 0; n0 < NIT; n0 += BATCH) {
@@ -429,6 +434,12 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
 #pragma unroll
                             for (int e = 0; e < 8; ++e) v[e] += old[e];
                         }
+                    }
+                    if (!col_ok) continue;
+                    if (nreal < 8) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (e >= nreal) v[e] = 0.f;
                     }
                     T* const o = out + offn[n];
                     if constexpr (sizeof(T) == 2) {
@@ -553,6 +564,11 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
                         for (int e = 0; e < 8; ++e)
                             if (accum) v[e] += old[e];
                     }
+                    if (nreal < 8) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (e >= nreal) v[e] = 0.f;
+                    }
                     if (out_f32) {
                         *reinterpret_cast<f32x4_t*>(cf + off[n]) = f32x4_t{v[0], v[1], v[2], v[3]};
                         *reinterpret_cast<f32x4_t*>(cf + off[n] + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
@@ -582,7 +598,7 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
     }
 }
 
-template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false>
+template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false>
 __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, T* __restrict__ As_, T* __restrict__ Bs_, float lrk) {
     constexpr int V = ET<T>::V, BK = ET<T>::BK * BKM;
     typedef TileGeom<T, BM, BK> GA;
@@ -616,8 +632,8 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     float bias_grad = 0.f;
 
     u32x4_t ra[ST][GA::NREG], rb[ST][GB::NREG];
-    Fetcher<MODE, T, true, BM, BK, VEC> fa;
-    Fetcher<MODE, T, false, BN, BK, VEC> fb;
+    Fetcher<MODE, T, true, BM, BK, VEC, GEN> fa;
+    Fetcher<MODE, T, false, BN, BK, VEC, GEN> fb;
     fa.init(p, row0);
     fb.init(p, col0);
     // the epilogue's vector form, decided now so that the forward bias of the thread's eight
@@ -626,7 +642,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     float bias_v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if constexpr (MODE == LIN_FWD || MODE == CONV_FWD) {
         const int bcol = col0 + (int)(threadIdx.x % (BN / 8)) * 8;
-        if (vec_out && bcol + 8 <= p.Q) {
+        if (vec_out && bcol + 8 <= stored_cols(p)) {
             const f32x4_t b0 = *reinterpret_cast<const f32x4_t*>(p.bias + bcol);
             const f32x4_t b1 = *reinterpret_cast<const f32x4_t*>(p.bias + bcol + 4);
             bias_v[0] = b0.x; bias_v[1] = b0.y; bias_v[2] = b0.z; bias_v[3] = b0.w;
@@ -640,6 +656,15 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     constexpr int DW_G = BN / 4, DW_NIT = BM * DW_G / 256, DW_RSTEP = 256 / DW_G;
     const int dw_lc = (threadIdx.x % DW_G) * 4, dw_lr0 = threadIdx.x / DW_G;
     const bool dw_full = vec_out && (col0 + dw_lc + 4 <= p.Q);
+    // columns of the thread's four that are padding between real channels: they stay zero whatever the operands hold
+    unsigned dw_pad = 0;
+    if constexpr (IS_DW) {
+        if (p.pad_c) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((col0 + dw_lc + e) % p.pad_c >= p.pad_real) dw_pad |= 1u << e;
+        }
+    }
     const bool upd = IS_DW && (p.flags & F_UPDATE);
     const bool keep_g = !upd || (p.flags & F_KEEP_G);
     f32x4_t dw_w[IS_DW ? DW_NIT : 1];
@@ -888,7 +913,12 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
                         const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;   // lr in [half * BM/2, (half + 1) * BM/2)
                         if (row >= p.R) continue;
                         const size_t off = (size_t)row * p.ldc + col;
-                        const f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr - half * (BM / 2)][dw_lc]);
+                        f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr - half * (BM / 2)][dw_lc]);
+                        if (dw_pad) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if ((dw_pad >> e) & 1u) g[e] = 0.f;
+                        }
                         if (!dw_full) {
                             for (int e = 0; e < 4 && col + e < p.Q; ++e) {
                                 if (upd) update_one(p, off + e, g[e], lrk);
@@ -945,7 +975,12 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
                     const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;
                     if (row >= p.R) continue;
                     const size_t off = (size_t)row * p.ldc + col;
-                    const f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr][dw_lc]);
+                    f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr][dw_lc]);
+                    if (dw_pad) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if ((dw_pad >> e) & 1u) g[e] = 0.f;
+                    }
                     if (!dw_full) {   // ragged right edge: element by element
                         for (int e = 0; e < 4 && col + e < p.Q; ++e) {
                             if (upd) update_one(p, off + e, g[e], lrk);
@@ -1069,7 +1104,7 @@ __global__ __launch_bounds__(256, 2) void conv_rows_halo_kernel(const GemmProb* 
     float bias_v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if constexpr (MODE == CONV_FWD) {
         const int bcol = col0 + (tid % (BN / 8)) * 8;
-        if (vec_out && bcol + 8 <= p.Q) {
+        if (vec_out && bcol + 8 <= stored_cols(p)) {
             const f32x4_t b0v = *reinterpret_cast<const f32x4_t*>(p.bias + bcol);
             const f32x4_t b1v = *reinterpret_cast<const f32x4_t*>(p.bias + bcol + 4);
             bias_v[0] = b0v.x; bias_v[1] = b0v.y; bias_v[2] = b0v.z; bias_v[3] = b0v.w;
@@ -1189,7 +1224,7 @@ using LrArg = typename std::conditional<MODE == LIN_DW || MODE == CONV_DW, LrTab
 // sorts problems into launches by that); VEC = false: the element-by-element gather for any shape.
 // They are separate kernels because the gather needs many more registers, which would halve the
 // occupancy of the aligned path if both lived in one kernel.
-template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false>
+template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false>
 __global__ __launch_bounds__(256) void gemm_kernel(const GemmProb* __restrict__ probs,
                                                    const TileRef* __restrict__ tiles,
                                                    const void* __restrict__ x, char* __restrict__ ws, LrArg<MODE> lr) {
@@ -1216,7 +1251,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmProb* __restrict__ 
     T* const Bs = lds + NBUF * BM * TileGeom<T, BM, BK>::LDS_LD;
     float lrk = 0.f;
     if constexpr (MODE == LIN_DW || MODE == CONV_DW) lrk = lr.lr[p.member];
-    gemm_body<MODE, T, BM, BN, BKM, VEC, LEAN>(p, tr, As, Bs, lrk);
+    gemm_body<MODE, T, BM, BN, BKM, VEC, LEAN, GEN>(p, tr, As, Bs, lrk);
 }
 
 template <int MODE, typename T>
@@ -1234,6 +1269,15 @@ static void launch_gemm_tile(int tile_cfg, const GemmProb* probs, const TileRef*
         case GEMM_CFG_LEAN64:
             if constexpr (!(MODE == LIN_DW || MODE == CONV_DW))
                 hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            break;
+        case GEMM_CFG_GATHER0:
+            if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            break;
+        case GEMM_CFG_GATHER0 + 1:
+            if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            break;
+        case GEMM_CFG_GATHER0 + 2:
+            if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
         default: hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, false>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
     }
@@ -1997,40 +2041,50 @@ hipError_t launch_opt(float* master, const float* grad, void* shadow, float* m, 
 // are then plain aligned matrix products over that one buffer, instead of each member gathering
 // 3-channel pixels element by element.
 // ------------------------------------------------------------------------------------------------
+// With one tap the same kernel copies rows whose length is no multiple of 16 bytes into padded rows, so that the
+// products over them take aligned loads.  All loaders of a step (strides, or members with data of their own) are one
+// launch: an entry of the map is 256 vectors of one loader.
 template <typename T>
-__global__ __launch_bounds__(256) void im2col_kernel(Im2colProb p, const T* __restrict__ x) {
+__global__ __launch_bounds__(256) void im2col_kernel(const Im2colProb* __restrict__ probs, const int2* __restrict__ map, const char* __restrict__ x_dev) {
     constexpr int V = ET<T>::V;
+    const int2 m = map[blockIdx.x];
+    const Im2colProb p = probs[m.x];
+    const T* const x = (const T*)(x_dev + p.x_off);
     const int groups = p.Kp / V;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long idx = (long long)m.y * 256 + threadIdx.x;
     const long long rows = (long long)p.B * p.Ho * p.Wo;
     if (idx >= rows * groups) return;
     const int g = (int)(idx % groups);
     const long long r = idx / groups;
-    const int hw = p.Ho * p.Wo;
-    const int b = (int)(r / hw), rem = (int)(r - (long long)b * hw);
-    const int i = rem / p.Wo, j = rem - i * p.Wo;
     T vals[V];
+    if (p.taps == 1) {
+        const T* const row = x + r * p.C;
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-        const int k = g * V + e;
-        const int tap = k / p.C, c = k - tap * p.C;
-        const int y = p.stride * i + tap / 3 - 1, xx = p.stride * j + tap % 3 - 1;
-        T v = (T)0;
-        if (tap < 9 && (unsigned)y < (unsigned)p.H && (unsigned)xx < (unsigned)p.W)
-            v = x[((size_t)(b * p.H + y) * p.W + xx) * p.C + c];
-        vals[e] = v;
+        for (int e = 0; e < V; ++e) vals[e] = (g * V + e < p.C) ? row[g * V + e] : (T)0;
+    } else {
+        const int hw = p.Ho * p.Wo;
+        const int b = (int)(r / hw), rem = (int)(r - (long long)b * hw);
+        const int i = rem / p.Wo, j = rem - i * p.Wo;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const int k = g * V + e;
+            const int tap = k / p.C, c = k - tap * p.C;
+            const int y = p.stride * i + tap / 3 - 1, xx = p.stride * j + tap % 3 - 1;
+            T v = (T)0;
+            if (tap < 9 && (unsigned)y < (unsigned)p.H && (unsigned)xx < (unsigned)p.W)
+                v = x[((size_t)(b * p.H + y) * p.W + xx) * p.C + c];
+            vals[e] = v;
+        }
     }
     u32x4_t o;
     __builtin_memcpy(&o, vals, 16);
     *reinterpret_cast<u32x4_t*>((T*)p.out + (size_t)r * p.Kp + g * V) = o;
 }
 
-hipError_t launch_im2col(bool bf16, const Im2colProb& p, const void* x_dev, hipStream_t st) {
-    const long long items = (long long)p.B * p.Ho * p.Wo * (p.Kp / (bf16 ? 8 : 4));
-    const int blocks = (int)((items + 255) / 256);
-    if (blocks <= 0) return hipSuccess;
-    if (bf16) hipLaunchKernelGGL(im2col_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, p, (const bf16_t*)x_dev);
-    else hipLaunchKernelGGL(im2col_kernel<float>, dim3(blocks), dim3(256), 0, st, p, (const float*)x_dev);
+hipError_t launch_im2col(bool bf16, const Im2colProb* probs_dev, const int2* map_dev, int n_blocks, const void* x_dev, hipStream_t st) {
+    if (n_blocks <= 0) return hipSuccess;
+    if (bf16) hipLaunchKernelGGL(im2col_kernel<bf16_t>, dim3(n_blocks), dim3(256), 0, st, probs_dev, map_dev, (const char*)x_dev);
+    else hipLaunchKernelGGL(im2col_kernel<float>, dim3(n_blocks), dim3(256), 0, st, probs_dev, map_dev, (const char*)x_dev);
     return hipGetLastError();
 }
 
@@ -2053,13 +2107,13 @@ __global__ __launch_bounds__(256) void wtranspose_kernel(const TransposeProb* __
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int co = co0 + ty + 4 * i, ci = ci0 + tx;
-        if (co < p.Cout && ci < p.Cin) tile[ty + 4 * i][tx] = src[((size_t)co * 9 + tap) * p.Cin + ci];
+        if (co < p.Cout && ci < p.Cin) tile[ty + 4 * i][tx] = src[((size_t)co * 9 + tap) * p.ld_src + ci];
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int ci = ci0 + ty + 4 * i, co = co0 + tx;
-        if (co < p.Cout && ci < p.Cin) dst[((size_t)ci * 9 + tap) * p.Cout + co] = tile[tx][ty + 4 * i];
+        if (co < p.Cout && ci < p.Cin) dst[((size_t)ci * 9 + tap) * p.ld_dst + co] = tile[tx][ty + 4 * i];
     }
 }
 

@@ -1,0 +1,70 @@
+"""Shapes that fill neither a 16-byte vector nor a chunk nor a tile, on the padded layouts and the general gather of the
+convolutions: the device against the CPU oracle, with the tolerances of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from paper_2002_02885_amd import binding
+from tests import test_gpu_parity as tp
+from tests.test_plan_check_host import odd_layers
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape,classes", [((6, 5, 3), 3), ((9, 4, 9), 19), ((3, 3, 16), 5), ((1, 1, 13), 17)])
+def test_members_of_odd_shapes_f32(shape, classes):
+    w = wl.custom(f"odd{shape}", 21, wl.F32, 5, shape, odd_layers(shape[2], classes), batch=[5, 3, 2, 5, 4], n_classes=classes, steps=2)
+    tp._check_f32(w, production_form=True)
+
+
+@pytest.mark.parametrize("make", [
+    lambda: wl.custom("odd_bf16", 22, wl.BF16, 70, (7, 9, 3), odd_layers(3, 19)[1:], batch=[70, 64, 66, 70], n_classes=19, steps=2),
+    lambda: wl.custom("odd_mlp_bf16", 23, wl.BF16, 67, (1, 1, 203), [wl.mlp([130, 51], 21), wl.mlp([33], 21), [("linear", 21)]], batch=[67, 65, 64], n_classes=21, steps=2),
+    lambda: wl.custom("odd_cnn_bf16", 24, wl.BF16, 66, (14, 14, 1), [wl.small_cnn((24, 48, 96), 10)] * 2, batch=[66, 64], steps=2),
+])
+def test_members_of_odd_shapes_bf16(make):
+    tp._check_bf16(make(), production_form=True)
+
+
+def test_odd_resnets_f32_several_tiles_and_splits():
+    tp._check_f32(wl.config5(K=2, B=6, size=19, widths=(20, 40, 72, 72), n_classes=37, steps=2, dtype=wl.F32))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_members_on_unaligned_blocks_of_their_own_equal_members_alone(dtype):
+    """Blocks of 3 rows of 13 features begin where they like; the padded copy gives each member the bits it has alone."""
+    layers, B = wl.mlp([21], 5), 3
+    rng = np.random.default_rng(3)
+    x, y = rng.standard_normal((3 * B, 13)).astype(np.float32), rng.integers(0, 5, 3 * B).astype(np.int32)
+    lr = np.full(3, 0.05, np.float32)
+    dev = lambda a: (torch.from_numpy(a).to(torch.bfloat16) if dtype == "bf16" and a.dtype == np.float32 else torch.from_numpy(a)).cuda()
+    pk = binding.Pack(B, (1, 1, 13), dtype, [layers] * 3, seed=1)
+    pk.set_input_mode(True)
+    solo = [binding.Pack(B, (1, 1, 13), dtype, [layers], seed=1) for _ in range(3)]
+    for k in range(3):
+        solo[k].write_weights(0, pk.read_weights(k))
+    xd, yd = dev(x), dev(y)
+    parts = [(dev(x[k * B:(k + 1) * B].copy()), dev(y[k * B:(k + 1) * B].copy())) for k in range(3)]
+    for _ in range(2):
+        pk.step(xd.data_ptr(), yd.data_ptr(), lr)
+        for k in range(3):
+            solo[k].step(parts[k][0].data_ptr(), parts[k][1].data_ptr(), lr[:1])
+    for k in range(3):
+        assert np.array_equal(pk.read_weights(k), solo[k].read_weights(0))
+
+
+def test_weights_loaded_after_a_member_diverged_train_as_if_it_never_had():
+    """An infinite rate turns everything it touches into NaN, padding between channels included; loading weights cures it."""
+    layers, shape, B = [("conv3x3", 9, 1), ("relu",), ("conv3x3", 11, 2), ("relu",), ("linear", 5), ("relu",), ("linear", 3)], (6, 6, 5), 4
+    x, y = torch.rand((B,) + shape, device="cuda"), torch.randint(0, 3, (B,), device="cuda", dtype=torch.int32)
+    blob = binding.Pack(B, shape, "f32", [layers], seed=5).read_weights(0)
+    got = []
+    for first in (0.01, np.inf):
+        pk = binding.Pack(B, shape, "f32", [layers], seed=5)
+        pk.step(x.data_ptr(), y.data_ptr(), np.array([first], np.float32))
+        pk.write_weights(0, blob)
+        for _ in range(2):
+            pk.step(x.data_ptr(), y.data_ptr(), np.array([0.01], np.float32))
+        got.append(pk.read_weights(0))
+    assert np.all(np.isfinite(got[0])) and np.array_equal(got[0], got[1])

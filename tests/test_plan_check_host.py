@@ -41,6 +41,25 @@ def test_reduced_and_odd_shapes(make):
     assert walked >= 1 and loads > 0
 
 
+def odd_layers(c, classes):
+    """Members whose channel counts fill neither a vector nor a tile: layers on the input, on padded pixels and on padded
+    features, shortcuts from the input, maps that are no power of two."""
+    tail = [("linear", 7), ("tanh",), ("linear", classes)]
+    return [[("linear", classes)],
+            [("conv3x3", 5, 2), ("relu",), ("conv3x3", 9, 1), ("sigmoid",)] + tail,
+            [("res_begin",), ("conv3x3", c, 1), ("res_end",), ("conv3x3", 12, 2), ("relu",), ("gap",), ("linear", classes)],
+            [("res_begin",), ("conv3x3", c + 3, 2), ("res_end",)] + tail,
+            [("conv3x3", 20, 1), ("relu",), ("res_begin",), ("conv3x3", 36, 2), ("relu",), ("conv3x3", 36, 1), ("res_end",), ("conv3x3", 33, 2), ("tanh",)] + tail]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(6, 5, 3), (5, 7, 6), (1, 1, 13), (9, 4, 9), (3, 3, 16), (2, 2, 5), (8, 8, 12)])
+def test_no_shape_is_left_to_the_element_by_element_kernels(shape, dtype):
+    for own in (False, True):
+        walked, skipped, loads = binding.plan_check(5, shape, dtype, odd_layers(shape[2], 3), [5, 3, 2, 5, 4], per_member_input=own)
+        assert walked > 0 and skipped == 0 and loads > 0
+
+
 def test_members_on_their_own_batches_and_argument_errors():
     w = wl.config5(K=2, B=4, size=16, widths=(64, 64), n_classes=10, steps=1)
     _check(w, per_member_input=True)
@@ -119,7 +138,8 @@ def test_the_walk_of_the_stride_1_forward_and_input_gradient_form_notices_plante
 
 def test_the_walk_of_the_staged_tile_fetchers_notices_planted_mistakes(tmp_path):
     """Same for the fetchers of the aligned staged-tile kernels, which the walk runs on the CPU as they are: the
-    gathered pixels one column to the right, rows beyond the problem loaded instead of cut off."""
+    gathered pixels one column to the right, rows beyond the problem loaded instead of cut off, a straddled tap off by
+    an element, the step to the next image left out."""
     import os
     import shutil
     import subprocess
@@ -143,7 +163,13 @@ def test_the_walk_of_the_staged_tile_fetchers_notices_planted_mistakes(tmp_path)
     for c in cases:
         r = subprocess.run([clean, *c], capture_output=True, text=True)
         assert r.returncode == 0 and r.stdout.startswith("OK"), (c, r.stdout)
-    for plant in (7, 8):
+    # the general gather: 24 and 40 channels (chunks straddle taps), 7 x 7 and 3 x 3 maps (chunks straddle images)
+    general = [("1", "1", "3", "7", "7", "24", "48"), ("0", "2", "2", "9", "7", "40", "24"), ("1", "1", "9", "3", "3", "24", "40", "dw"), ("0", "2", "5", "9", "7", "8", "24", "dw")]
+    for c in general:
+        r = subprocess.run([clean, *c], capture_output=True, text=True)
+        assert r.returncode == 0 and r.stdout.startswith("OK"), (c, r.stdout)
+    cases += general
+    for plant in (7, 8, 9, 10):
         exe = build(plant)
         results = [subprocess.run([exe, *c], capture_output=True, text=True) for c in cases]
         assert any(r.returncode == 1 and "FAIL" in r.stdout for r in results), plant

@@ -766,7 +766,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 GapProb g{};
                 g.in = ti.act; g.out = to.act; g.n = ti.n; g.hw = ti.h * ti.w; g.c = ti.pitch;
                 gaps.push_back(g);
-                gap_blocks.push_back((ti.n * ti.pitch + 255) / 256);
+                gap_blocks.push_back(ti.n * ((ti.pitch / V + GAP_VECS - 1) / GAP_VECS));
                 continue;
             }
             if (m.fused_head && s + 1 == m.nodes.size()) continue;   // part of the head kernel

@@ -143,6 +143,7 @@ struct HeadProb {     // classifier head of one member in one kernel: logits, so
 constexpr int HEAD_ROWS = 4;       // rows one block of the head kernel handles
 constexpr int HEAD_MAX_C = 16;     // classes the head kernel keeps in registers
 
+constexpr int GAP_VECS = 8;        // 16-byte vectors of channels one block of the pooling kernel handles
 struct GapProb {      // global average pool: in [n, hw, c] -> out [n, c]
     const void* in;
     void* out;

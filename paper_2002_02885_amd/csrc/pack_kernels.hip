@@ -1731,61 +1731,6 @@ hipError_t launch_head(bool bf16, int max_c, const HeadProb* probs, const int2* 
 }
 
 // ------------------------------------------------------------------------------------------------
-// global average pool
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void gap_fwd_kernel(const GapProb* __restrict__ probs, const int2* __restrict__ map) {
-    const int2 m = map[blockIdx.x];
-    const GapProb p = probs[m.x];
-    const int e = m.y * 256 + threadIdx.x;   // output element (n, c)
-    if (e >= p.n * p.c) return;
-    const int n = e / p.c, c = e - n * p.c;
-    const T* in = (const T*)p.in + (size_t)n * p.hw * p.c + c;
-    // pixels are added in order; eight loads are issued before their adds so that they overlap
-    float s = 0.f;
-    for (int i0 = 0; i0 < p.hw; i0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (i0 + j < p.hw) ? ET<T>::to_f(in[(size_t)(i0 + j) * p.c]) : 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s += v[j];
-    }
-    ((T*)p.out)[e] = ET<T>::from_f(s / (float)p.hw);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void gap_bwd_kernel(const GapProb* __restrict__ probs, const int2* __restrict__ map) {
-    const int2 m = map[blockIdx.x];
-    const GapProb p = probs[m.x];
-    const long long total = (long long)p.n * p.hw * p.c;
-    const float inv = 1.f / (float)p.hw;
-#pragma unroll
-    for (int i = 0; i < ELEMWISE_PER_BLOCK / 256; ++i) {
-        const long long e = (long long)m.y * ELEMWISE_PER_BLOCK + i * 256 + threadIdx.x;
-        if (e >= total) break;
-        const int c = (int)(e % p.c);
-        const int n = (int)(e / ((long long)p.hw * p.c));
-        float g = ET<T>::to_f(((const T*)p.dz_out)[(size_t)n * p.c + c]) * inv;
-        if (p.mask == ACT_RELU) { if (!(ET<T>::to_f(((const T*)p.in)[e]) > 0.f)) g = 0.f; }
-        else if (p.mask) g *= act_deriv(p.mask, ET<T>::to_f(((const T*)p.in)[e]));
-        if (p.accum) g += ET<T>::to_f(((const T*)p.dz_in)[e]);
-        ((T*)p.dz_in)[e] = ET<T>::from_f(g);
-    }
-}
-
-hipError_t launch_gap(bool bf16, bool backward, const GapProb* probs, const int2* map, int n, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (!backward) {
-        if (bf16) hipLaunchKernelGGL(gap_fwd_kernel<bf16_t>, dim3(n), dim3(256), 0, st, probs, map);
-        else hipLaunchKernelGGL(gap_fwd_kernel<float>, dim3(n), dim3(256), 0, st, probs, map);
-    } else {
-        if (bf16) hipLaunchKernelGGL(gap_bwd_kernel<bf16_t>, dim3(n), dim3(256), 0, st, probs, map);
-        else hipLaunchKernelGGL(gap_bwd_kernel<float>, dim3(n), dim3(256), 0, st, probs, map);
-    }
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
 // backward of the residual shortcut
 // ------------------------------------------------------------------------------------------------
 template <typename T>
@@ -2030,61 +1975,6 @@ hipError_t launch_opt(float* master, const float* grad, void* shadow, float* m, 
     const int blocks = (int)((n + SGD_PER_BLOCK - 1) / SGD_PER_BLOCK);
     if (shadow) hipLaunchKernelGGL(opt_kernel<true>, dim3(blocks), dim3(256), 0, st, master, grad, (bf16_t*)shadow, m, v, n, seg_end, params, K, tab);
     else hipLaunchKernelGGL(opt_kernel<false>, dim3(blocks), dim3(256), 0, st, master, grad, (bf16_t*)nullptr, m, v, n, seg_end, params, K, tab);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
-// Shared-input loader for packs whose first layer is a convolution over few channels (paper
-// Section 3.4: the members read ONE input).  The nine shifted views of the batch are written
-// once per step as a dense matrix xcol[(b,i,j), tap*C + c] (zero for taps outside the image and
-// for the padding columns up to Kp); every member's first convolution and its weight gradient
-// are then plain aligned matrix products over that one buffer, instead of each member gathering
-// 3-channel pixels element by element.
-// ------------------------------------------------------------------------------------------------
-// With one tap the same kernel copies rows whose length is no multiple of 16 bytes into padded rows, so that the
-// products over them take aligned loads.  All loaders of a step (strides, or members with data of their own) are one
-// launch: an entry of the map is 256 vectors of one loader.
-template <typename T>
-__global__ __launch_bounds__(256) void im2col_kernel(const Im2colProb* __restrict__ probs, const int2* __restrict__ map, const char* __restrict__ x_dev) {
-    constexpr int V = ET<T>::V;
-    const int2 m = map[blockIdx.x];
-    const Im2colProb p = probs[m.x];
-    const T* const x = (const T*)(x_dev + p.x_off);
-    const int groups = p.Kp / V;
-    const long long idx = (long long)m.y * 256 + threadIdx.x;
-    const long long rows = (long long)p.B * p.Ho * p.Wo;
-    if (idx >= rows * groups) return;
-    const int g = (int)(idx % groups);
-    const long long r = idx / groups;
-    T vals[V];
-    if (p.taps == 1) {
-        const T* const row = x + r * p.C;
-#pragma unroll
-        for (int e = 0; e < V; ++e) vals[e] = (g * V + e < p.C) ? row[g * V + e] : (T)0;
-    } else {
-        const int hw = p.Ho * p.Wo;
-        const int b = (int)(r / hw), rem = (int)(r - (long long)b * hw);
-        const int i = rem / p.Wo, j = rem - i * p.Wo;
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            const int k = g * V + e;
-            const int tap = k / p.C, c = k - tap * p.C;
-            const int y = p.stride * i + tap / 3 - 1, xx = p.stride * j + tap % 3 - 1;
-            T v = (T)0;
-            if (tap < 9 && (unsigned)y < (unsigned)p.H && (unsigned)xx < (unsigned)p.W)
-                v = x[((size_t)(b * p.H + y) * p.W + xx) * p.C + c];
-            vals[e] = v;
-        }
-    }
-    u32x4_t o;
-    __builtin_memcpy(&o, vals, 16);
-    *reinterpret_cast<u32x4_t*>((T*)p.out + (size_t)r * p.Kp + g * V) = o;
-}
-
-hipError_t launch_im2col(bool bf16, const Im2colProb* probs_dev, const int2* map_dev, int n_blocks, const void* x_dev, hipStream_t st) {
-    if (n_blocks <= 0) return hipSuccess;
-    if (bf16) hipLaunchKernelGGL(im2col_kernel<bf16_t>, dim3(n_blocks), dim3(256), 0, st, probs_dev, map_dev, (const char*)x_dev);
-    else hipLaunchKernelGGL(im2col_kernel<float>, dim3(n_blocks), dim3(256), 0, st, probs_dev, map_dev, (const char*)x_dev);
     return hipGetLastError();
 }
 

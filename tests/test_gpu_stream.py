@@ -1,0 +1,18 @@
+"""Pooling and input-loader kernels at the sizes where their splits have remainders, against the float64 oracle."""
+import pytest
+
+import workloads as wl
+from tests import test_gpu_parity as tp
+
+pytestmark = pytest.mark.gpu
+
+
+# (side, channels): fewer pixels than slices, one more than a round of four slices, channel vectors that fill no block,
+# an image smaller than a block of the backward kernel, odd channel counts (stored padded)
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("side,channels,in_c", [(1, 8, 1), (3, 72, 2), (6, 33, 3), (12, 40, 5), (19, 24, 4)])
+def test_pool_and_loader_remainders(dtype, side, channels, in_c):
+    models = [[("conv3x3", channels, 1), (act,), ("gap",), ("linear", 7)] for act in ("relu", "tanh")]
+    models.append([("conv3x3", channels + 9, 2), ("relu",), ("gap",), ("linear", 7)])
+    w = wl.custom(f"pool_{side}_{channels}", 60 + side, dtype, 70, (side, side, in_c), models, batch=[70, 65, 67], n_classes=7, steps=1)
+    tp._check_f32(w) if dtype == wl.F32 else tp._check_bf16(w)

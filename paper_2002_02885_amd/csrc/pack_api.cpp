@@ -97,7 +97,7 @@ struct ModelInfo {
     size_t segs_off = 0;             // byte offset of the member's BlobSeg table in the descriptor buffer
     int n_segs = 0;
     bool fused_head = false;         // classifier head (last linear layer, loss, its input gradient) runs in one kernel
-    float* head_partial = nullptr;   // per-block loss sums of that kernel
+    float* loss_partial = nullptr;   // per-block loss sums of that kernel, or of the loss kernel
 };
 
 enum LaunchKind { L_GEMM, L_REDUCE, L_CE, L_GAP_FWD, L_GAP_BWD, L_SHORTCUT, L_SGD, L_IM2COL, L_WTRANS, L_HEAD };
@@ -160,6 +160,8 @@ struct pack_ctx {
     bool keep_grads = false;          // fused packs: store the gradients as well (pack_read_grads)
     size_t head_desc_off = 0;         // problem table of the classifier-head launch
     int n_heads = 0;
+    size_t ce_desc_off = 0;           // problem table of the loss launch
+    int n_ce = 0;
     std::vector<Launch> plan;
     size_t device_bytes = 0;
     // per-launch timing (off unless pack_profile_start was called)
@@ -835,6 +837,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
     // ---------------- loss ----------------
     {
         std::vector<CeProb> ce;
+        std::vector<int> ce_blocks;
         std::vector<HeadProb> heads;
         std::vector<int> head_blocks;
         for (ModelInfo& m : p->models) {
@@ -846,7 +849,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 HeadProb h{};
                 h.h = ti.act; h.W = weight_ptr(nd); h.bias = p->master + nd.b_off;
                 h.logits = (float*)lg.act; h.dlogits = lg.dz; h.dh = ti.needs_grad ? ti.dz : nullptr;
-                h.pred = m.pred; h.loss = m.loss; h.partial = m.head_partial;
+                h.pred = m.pred; h.loss = m.loss; h.partial = m.loss_partial;
                 h.rows = m.batch; h.C = m.C; h.Kd = nd.ldw; h.ldd = lg.ld_dz;
                 h.label_off = p->own_input ? (int)(&m - p->models.data()) * p->in.B : 0;
                 h.mask_act = ti.act_out;
@@ -859,15 +862,14 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
             c.logits = (const float*)lg.act; c.dlogits = lg.dz; c.pred = m.pred; c.loss = m.loss;
             c.rows = m.batch; c.C = m.C; c.ld = m.C; c.ldd = lg.ld_dz;
             c.label_off = p->own_input ? (int)(&m - p->models.data()) * p->in.B : 0;
+            c.partial = m.loss_partial;
+            c.nblk = (m.batch + ce_rows_per_block(m.C) - 1) / ce_rows_per_block(m.C);
             ce.push_back(c);
+            ce_blocks.push_back(c.nblk);
         }
-        if (!ce.empty()) {
-            Launch L;
-            L.kind = L_CE;
-            L.desc_off = db.add(ce.data(), ce.size() * sizeof(CeProb));
-            L.n = (int)ce.size();
-            p->plan.push_back(L);
-        }
+        add_mapped_launch(p, db, L_CE, ce, ce_blocks);
+        p->n_ce = (int)ce.size();
+        if (!ce.empty()) p->ce_desc_off = p->plan.back().desc_off;
         add_mapped_launch(p, db, L_HEAD, heads, head_blocks);
         p->n_heads = (int)heads.size();
         if (!heads.empty()) {
@@ -1308,10 +1310,8 @@ pack_status build_device(pack_ctx* p) {
         {   // few classes: logits, loss and the input gradient of the last layer in one kernel
             const TensorInfo& hin = m.tensors[m.nodes.back().in_t];
             m.fused_head = !std::getenv("PACK_NO_FUSED_HEAD") && m.C <= HEAD_MAX_C && !hin.is_input;
-            if (m.fused_head) {
-                const int nblk = (m.batch + HEAD_ROWS - 1) / HEAD_ROWS;
-                fix.push_back({(void**)&m.head_partial, reserve((size_t)nblk * 4)});
-            }
+            const int per_block = m.fused_head ? HEAD_ROWS : ce_rows_per_block(m.C);
+            fix.push_back({(void**)&m.loss_partial, reserve((size_t)((m.batch + per_block - 1) / per_block) * 4)});
         }
         for (TensorInfo& t : m.tensors) {
             if (t.is_input) continue;
@@ -1772,7 +1772,7 @@ static pack_status step_with_workspace(pack_t* p, const void* x_dev, const int32
                 e = launch_gemm(L.mode, bf, L.tile_cfg, (const GemmProb*)d, (const TileRef*)mp, L.n, x_dev, ws, lr, p->stream);
                 break;
             case L_REDUCE: e = launch_reduce((const ReduceProb*)d, (const int2*)mp, L.n, ws, lr, p->stream); break;
-            case L_CE: e = launch_ce(bf, (const CeProb*)d, L.n, labels_dev, p->err_flag, p->stream); break;
+            case L_CE: e = launch_ce(bf, (const CeProb*)d, (const int2*)mp, L.n, labels_dev, p->err_flag, p->stream); break;
             case L_HEAD: e = launch_head(bf, L.mode, (const HeadProb*)d, (const int2*)mp, L.n, labels_dev, p->err_flag, p->stream); break;
             case L_GAP_FWD: e = launch_gap(bf, false, (const GapProb*)d, (const int2*)mp, L.n, p->stream); break;
             case L_GAP_BWD: e = launch_gap(bf, true, (const GapProb*)d, (const int2*)mp, L.n, p->stream); break;
@@ -2054,7 +2054,8 @@ pack_status pack_measure_ceiling(int32_t what, void* stream, double* value_out) 
 
 pack_status pack_read_loss(pack_t* p, float* host_dst) {
     if (!p || !host_dst) return fail(PACK_EINVAL, "null argument");
-    // members with a fused classifier head leave per-block sums; add them up now, in block order
+    // the loss and classifier-head kernels leave per-block sums; add them up now, in block order
+    if (p->n_ce) HIP_TRY(launch_ce_loss((const CeProb*)(p->desc + p->ce_desc_off), p->n_ce, p->stream), PACK_EDEVICE);
     if (p->n_heads) HIP_TRY(launch_head_loss((const HeadProb*)(p->desc + p->head_desc_off), p->n_heads, p->stream), PACK_EDEVICE);
     HIP_TRY(hipStreamSynchronize(p->stream), PACK_EDEVICE);
     HIP_TRY(hipMemcpy(host_dst, p->loss_all, (size_t)p->K * 4, hipMemcpyDeviceToHost), PACK_EDEVICE);

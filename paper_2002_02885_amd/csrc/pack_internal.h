@@ -124,9 +124,18 @@ struct CeProb {       // softmax cross-entropy of one member
     void* dlogits;         // [rows, ldd] pack dtype
     int* pred;             // [rows]
     float* loss;           // scalar
+    float* partial;        // [nblk] per-block loss sums
     int rows, C, ld, ldd;
     int label_off;         // first label of the member in the step's label vector
+    int nblk;
 };
+constexpr int CE_WAVES = 4;        // wavefronts per block of the loss kernel
+__host__ __device__ inline int ce_lanes_per_row(int C) {   // a power of two, at least min(C, 64)
+    int lanes = 1;
+    while (lanes < 64 && lanes < C) lanes <<= 1;
+    return lanes;
+}
+inline int ce_rows_per_block(int C) { return CE_WAVES * (64 / ce_lanes_per_row(C)); }
 
 struct HeadProb {     // classifier head of one member in one kernel: logits, softmax cross-entropy, dlogits, input gradient
     const void* h;         // [rows, Kd] pack dtype: the activations the last linear layer reads
@@ -213,7 +222,8 @@ hipError_t launch_reduce(const ReduceProb* probs_dev, const int2* map_dev, int n
 // its address on the current device.  For the entry point that may not allocate.
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)128 << 20;
 hipError_t static_scratch(char** ptr);
-hipError_t launch_ce(bool bf16, const CeProb* probs_dev, int K, const int32_t* labels, int* err_flag, hipStream_t st);
+hipError_t launch_ce(bool bf16, const CeProb* probs_dev, const int2* map_dev, int n_blocks, const int32_t* labels, int* err_flag, hipStream_t st);
+hipError_t launch_ce_loss(const CeProb* probs_dev, int n_members, hipStream_t st);
 // max_c: the largest class count among the launch's members (<= HEAD_MAX_C)
 hipError_t launch_head(bool bf16, int max_c, const HeadProb* probs_dev, const int2* map_dev, int n_blocks, const int32_t* labels,
                        int* err_flag, hipStream_t st);

@@ -16,3 +16,12 @@ def test_pool_and_loader_remainders(dtype, side, channels, in_c):
     models.append([("conv3x3", channels + 9, 2), ("relu",), ("gap",), ("linear", 7)])
     w = wl.custom(f"pool_{side}_{channels}", 60 + side, dtype, 70, (side, side, in_c), models, batch=[70, 65, 67], n_classes=7, steps=1)
     tp._check_f32(w) if dtype == wl.F32 else tp._check_bf16(w)
+
+
+# (classes, rows): more rows than a block takes and not a multiple of it, one row, classes at the edges of a group of lanes
+# and beyond what the lanes keep in registers
+@pytest.mark.parametrize("classes,rows", [(17, [70, 1, 7]), (32, [67, 8, 9]), (33, [5, 4, 64]), (64, [13]), (256, [66]), (257, [65, 3])])
+def test_loss_in_blocks_of_rows(classes, rows):
+    models = [[("linear", 24), ("tanh",), ("linear", classes)]] * len(rows)
+    w = wl.custom(f"loss_{classes}", 80 + classes, wl.F32, max(rows), (1, 1, 40), models, batch=rows, n_classes=classes, steps=2)
+    tp._check_f32(w)

@@ -1334,9 +1334,52 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restric
     ReduceProb p = probs[m.x];
     p.in = (const float*)(ws + (size_t)p.in);   // the partial sums lie in the workspace this launch was given
     const float lrk = p.upd_w ? lr.lr[p.member] : 0.f;
-    // A thread owns four elements.  Partials are added in split order; the loads of eight splits of
-    // all four elements (32 loads) are issued before their adds, so that the strided reads overlap
-    // instead of paying one round trip each.
+    // Partials are added in split order.  Whole vectors (weights; only a bias can have an odd length): a thread owns four
+    // consecutive elements and requests sixteen splits before it adds them, since a layer with few weights has few threads
+    // and many splits and takes as long as its rounds of reads.  (Against eight splits of 4-byte reads: 48 -> 42 us on four
+    // residual networks, 107 -> 97 on eight larger ones, 13.4 -> 10.6 on five CNNs of 28 x 28 pixels.)
+    if (((p.n | (int)p.stride) & 3) == 0) {
+        const int e = m.y * 1024 + threadIdx.x * 4;
+        if (e >= p.n) return;
+        constexpr int DEEP = 16;
+        const float* const in = p.in + e;
+        f32x4_t w{}, s = {0.f, 0.f, 0.f, 0.f};
+        if (p.upd_w) w = *reinterpret_cast<const f32x4_t*>(p.upd_w + e);   // its round trip runs under the partials'
+        int k = 0;
+        for (; k + DEEP <= p.S; k += DEEP) {
+            f32x4_t v[DEEP];
+#pragma unroll
+            for (int j = 0; j < DEEP; ++j) v[j] = *reinterpret_cast<const f32x4_t*>(in + (size_t)(k + j) * p.stride);
+#pragma unroll
+            for (int j = 0; j < DEEP; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] += v[j][i];
+        }
+        if (k < p.S) {
+            f32x4_t v[DEEP];
+#pragma unroll
+            for (int j = 0; j < DEEP; ++j)   // (the last split again where there is none: read, not added)
+                v[j] = *reinterpret_cast<const f32x4_t*>(in + (size_t)min(k + j, p.S - 1) * p.stride);
+#pragma unroll
+            for (int j = 0; j < DEEP; ++j)
+                if (k + j < p.S) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s[i] += v[j][i];
+                }
+        }
+        if (p.upd_w) {   // fused update: the summed gradient goes straight into the weights
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = sgd_apply(w[i], s[i], lrk);
+            *reinterpret_cast<f32x4_t*>(p.upd_w + e) = w;
+            if (p.upd_shadow) {
+                typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+                *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + e) = u32x2_t{pack2bf(w[0], w[1]), pack2bf(w[2], w[3])};
+            }
+        }
+        if (!p.upd_w || p.keep_g) *reinterpret_cast<f32x4_t*>(p.out + e) = s;
+        return;
+    }
+    // A thread owns four elements 256 apart; the loads of eight splits (32 loads) are issued before their adds.
     const int e0 = m.y * 1024 + threadIdx.x;
     float s[4] = {0.f, 0.f, 0.f, 0.f};
     for (int k0 = 0; k0 < p.S; k0 += 8) {

@@ -25,3 +25,12 @@ def test_loss_in_blocks_of_rows(classes, rows):
     models = [[("linear", 24), ("tanh",), ("linear", classes)]] * len(rows)
     w = wl.custom(f"loss_{classes}", 80 + classes, wl.F32, max(rows), (1, 1, 40), models, batch=rows, n_classes=classes, steps=2)
     tp._check_f32(w)
+
+
+# splits of the weight gradients' reductions: fewer than the sixteen that are requested together, some more, twice and some
+# more; 33 channels give a bias that is no whole vectors, 40 one that is
+@pytest.mark.parametrize("rows,side", [(5, 14), (20, 16), (70, 16)])
+def test_split_weight_gradients_are_added_up(rows, side):
+    models = [[("conv3x3", 8, 1), ("relu",), ("conv3x3", channels, 1), ("tanh",), ("gap",), ("linear", 7)] for channels in (33, 40)]
+    w = wl.custom(f"splits_{rows}", 90 + rows, wl.F32, rows, (side, side, 3), models, n_classes=7, steps=2)
+    tp._check_f32(w)

@@ -140,7 +140,8 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
  * Section 2.2: "as if trained alone"); for the halo kernels of the 3x3 convolutions the walk also follows
  * what is stored to LDS and read back as matrix-instruction operands.  A load of existing elements outside
  * its descriptor's window or its allocation, a load of missing elements that is not cut off by construction,
- * an operand slot holding the wrong element, a tile dealt twice or not at all is an error.
+ * an operand slot holding the wrong element, a tile dealt twice or not at all, a reduction of split weight
+ * gradients that adds elements no product stores is an error.
  * input_mode: pack_input_mode.  Outputs (host, may be null): launches walked, matrix-product launches on the
  * element-by-element kernels for unaligned shapes (skipped: they load by the definition itself), loads and
  * operand reads checked.

@@ -942,6 +942,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 g.R = nd.out; g.Q = q_dim; g.Kd = rows;
                 g.lda = to.ld_dz ? to.ld_dz : to.pitch; g.ldc = nd.ldw;
                 g.flags |= F_VEC_A | F_VEC_B;
+                if (q_dim < nd.ldw) g.flags |= F_PAD_OUT;   // a row of W is stored, and its split sums are added up, with its padding
                 float* dst = p->grad + nd.w_off;
                 const bool dense = (nd.kind == NODE_LINEAR) || nd.kp;
                 if (nd.in_copy) {
@@ -1649,6 +1650,32 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
                     for (int tn = 0; tn < g.Cin / ci_t; ++tn)
                         if (seen.find({i, tm, tn, ks}) == seen.end() && err.empty())
                             err = "launch " + std::to_string(li) + ": problem " + std::to_string(i) + " lacks a tile";
+        }
+    }
+    // every element a reduction of split weight gradients reads is one that the products it belongs to store
+    std::map<unsigned long long, const GemmProb*> partial_w, partial_b;
+    for (const Launch& L : p->plan) {
+        if (L.kind != L_GEMM || (L.mode != LIN_DW && L.mode != CONV_DW)) continue;
+        const GemmProb* probs = (const GemmProb*)(p->desc_host.data() + L.desc_off);
+        const TileRef* tiles = (const TileRef*)(p->desc_host.data() + L.map_off);
+        for (int t = 0; t < L.n; ++t)
+            if (tiles[t].prob >= 0 && (probs[tiles[t].prob].flags & F_WS)) {
+                const GemmProb& g = probs[tiles[t].prob];
+                partial_w[(unsigned long long)(uintptr_t)g.C] = partial_b[(unsigned long long)(uintptr_t)g.dbias] = &g;
+            }
+    }
+    for (const Launch& L : p->plan) {
+        if (L.kind != L_REDUCE || !err.empty()) continue;
+        const ReduceProb* reds = (const ReduceProb*)(p->desc_host.data() + L.desc_off);
+        const int2* map = (const int2*)(p->desc_host.data() + L.map_off);
+        for (int t = 0; t < L.n && err.empty(); ++t) {
+            const ReduceProb& r = reds[map[t].x];
+            const auto w = partial_w.find((unsigned long long)(uintptr_t)r.in), b = partial_b.find((unsigned long long)(uintptr_t)r.in);
+            const GemmProb* g = w != partial_w.end() ? w->second : b != partial_b.end() ? b->second : nullptr;
+            bool written = g && r.S == (g->Kd + g->ksplit - 1) / g->ksplit;
+            if (written && w != partial_w.end()) written = r.n == (long long)g->R * g->ldc && stored_cols(*g) == g->ldc && r.stride == g->split_stride;
+            else if (written) written = r.n == g->R && r.stride == g->R;
+            if (!written) err = "reduction " + std::to_string(map[t].x) + " of split weight gradients adds elements that no product stores";
         }
     }
     release(p);

@@ -104,6 +104,9 @@ struct GemmProb {
 // and Montgomery); 0 stands for d = 1.
 inline unsigned div_multiplier(int d) { return d <= 1 ? 0u : (unsigned)(0x100000000ull / (unsigned)d + 1ull); }
 
+// columns of an output row that are stored: all of Q, rounded up to whole groups of eight where the layout is (the rest zeros)
+__host__ __device__ inline int stored_cols(const GemmProb& p) { return (p.flags & F_PAD_OUT) ? (p.Q + 7) & ~7 : p.Q; }
+
 struct TileRef {      // one workgroup's job; prob < 0 marks a filler slot
     int prob;
     int tm, tn, ks;

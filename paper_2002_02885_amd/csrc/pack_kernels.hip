@@ -273,9 +273,6 @@ struct LdsBytes {
 // once, before the first read of `stage`: a caller that fills `stage` there (barrier, writes, barrier) has the
 // first batch's round trip run under that instead of after it.
 struct NoHook { __device__ __forceinline__ void operator()() const {} };
-// columns of an output row that are stored: all of Q, rounded up to whole groups of eight where the layout is (the rest zeros)
-__device__ __forceinline__ int stored_cols(const GemmProb& p) { return (p.flags & F_PAD_OUT) ? (p.Q + 7) & ~7 : p.Q; }
-
 template <int MODE, typename T, int BM, int BN, int MAXB = 4, class Hook = NoHook>
 __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, const int col0, float (*stage)[BN + 8],
                                             const float (&bias_v)[8], const bool vec_out, Hook staged = Hook()) {
@@ -655,10 +652,15 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     // come from L2, then queue behind weights that come from HBM.)
     constexpr int DW_G = BN / 4, DW_NIT = BM * DW_G / 256, DW_RSTEP = 256 / DW_G;
     const int dw_lc = (threadIdx.x % DW_G) * 4, dw_lr0 = threadIdx.x / DW_G;
-    const bool dw_full = vec_out && (col0 + dw_lc + 4 <= p.Q);
-    // columns of the thread's four that are padding between real channels: they stay zero whatever the operands hold
+    const int dw_cols = stored_cols(p);
+    const bool dw_full = vec_out && (col0 + dw_lc + 4 <= dw_cols);
+    // columns of the thread's four that are padding, between real channels or at the end of a row: they are stored as
+    // zeros whatever the operands hold (a reduction of split products reads them like any other)
     unsigned dw_pad = 0;
     if constexpr (IS_DW) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (col0 + dw_lc + e >= p.Q) dw_pad |= 1u << e;
         if (p.pad_c) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -907,7 +909,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
             }
             lds_barrier();
             if (vec_out) {
-                if (col < p.Q) {
+                if (col < dw_cols) {
 #pragma unroll
                     for (int n = half * (DW_NIT / 2); n < (half + 1) * (DW_NIT / 2); ++n) {
                         const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;   // lr in [half * BM/2, (half + 1) * BM/2)
@@ -969,7 +971,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
         float* const gf = (float*)p.C + (size_t)tr.ks * p.split_stride;
         if (vec_out) {
             const int col = col0 + dw_lc;
-            if (col < p.Q) {
+            if (col < dw_cols) {
 #pragma unroll
                 for (int n = 0; n < DW_NIT; ++n) {
                     const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;

@@ -60,6 +60,18 @@ def test_no_shape_is_left_to_the_element_by_element_kernels(shape, dtype):
         assert walked > 0 and skipped == 0 and loads > 0
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,shape,layers", [
+    (2000, (1, 1, 30), wl.mlp([50, 20], 7)),                                             # rows of 30, 50 and 20 features stored as 32, 56 and 24
+    (2000, (1, 1, 36), wl.mlp([50], 19)),                                                # fp32: whole vectors, but no whole group of 8; no fused head
+    (9000, (1, 1, 30), wl.mlp([300], 7)),                                                # more than one tile of output
+    (1500, (4, 3, 3), [("conv3x3", 5, 1), ("relu",), ("conv3x3", 9, 2), ("relu",), ("linear", 11), ("tanh",), ("linear", 3)]),
+    (1500, (4, 3, 3), [("conv3x3", 12, 2), ("relu",), ("gap",), ("linear", 3)]),
+])
+def test_reductions_of_split_weight_gradients_read_stored_elements_only(B, shape, layers, dtype):
+    binding.plan_check(B, shape, dtype, [layers, layers], [B, B - 1])
+
+
 def test_members_on_their_own_batches_and_argument_errors():
     w = wl.config5(K=2, B=4, size=16, widths=(64, 64), n_classes=10, steps=1)
     _check(w, per_member_input=True)

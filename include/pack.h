@@ -283,7 +283,7 @@ pack_status pack_measure_ceiling(int32_t what, void* stream, double* value_out);
 
 /* load a member's weights (Section 2.2 `load`): host_src holds pack_num_params(p, k) floats in
  * the blob layout above.  For PACK_BF16 the bf16 operand copy is refreshed too.
- * Errors: PACK_EINVAL (k out of range, n_floats mismatch), PACK_EDEVICE. */
+ * Errors: PACK_EINVAL (k out of range, n_floats mismatch), PACK_ENOMEM (no host memory for the transfer), PACK_EDEVICE. */
 pack_status pack_write_weights(pack_t* p, int32_t k, const float* host_src, size_t n_floats);
 
 /* One synchronised training step of all K members (Section 2.2; shared input Section 3.4; batch
@@ -325,7 +325,8 @@ pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec);
  * array `slot` of member k in the blob layout of the weights (slot 0: momentum / Adagrad accumulator
  * or Adam's first moment; slot 1: Adam's second moment) and, if `steps` is not null, the number of
  * steps the optimiser has taken.  pack_write_opt_state restores both (the load of a checkpoint).
- * Errors: PACK_EINVAL (null, k out of range, n_floats mismatch, slot the member's optimiser does not have). */
+ * Errors: PACK_EINVAL (null, k out of range, n_floats mismatch, slot the member's optimiser does not have), PACK_ENOMEM
+ * and PACK_EDEVICE as for the weights. */
 pack_status pack_read_opt_state(pack_t* p, int32_t k, int32_t slot, float* host_dst, size_t n_floats, int64_t* steps);
 pack_status pack_write_opt_state(pack_t* p, int32_t k, int32_t slot, const float* host_src, size_t n_floats, int64_t steps);
 
@@ -336,7 +337,7 @@ pack_status pack_write_opt_state(pack_t* p, int32_t k, int32_t slot, const float
  * if pack_gather_batch met a sample index outside the dataset. */
 pack_status pack_read_loss(pack_t* p, float* host_dst);
 
-/* free's checkpoint (Section 2.2): the member's current fp32 weights in the blob layout. */
+/* free's checkpoint (Section 2.2): the member's current fp32 weights in the blob layout.  Errors as for pack_write_weights. */
 pack_status pack_read_weights(pack_t* p, int32_t k, float* host_dst, size_t n_floats);
 
 /* argmax over classes of the last step's logits of member k (lowest index on ties).

@@ -1186,19 +1186,19 @@ pack_status live_member(const pack_ctx* p, int32_t k);
 
 const BlobSeg* member_segs(const pack_ctx* p, int k) { return (const BlobSeg*)(p->desc + p->models[k].segs_off); }
 
+pack_status transfer_status(hipError_t e) {
+    if (e == hipSuccess) return PACK_OK;
+    return fail(e == hipErrorOutOfMemory ? PACK_ENOMEM : PACK_EDEVICE, std::string("checkpoint transfer: ") + hipGetErrorString(e));
+}
+
 pack_status upload_weights(pack_ctx* p, int k, const float* blob) {
     const ModelInfo& m = p->models[k];
     void* const shadow = p->bf16 ? (void*)((char*)p->shadow + m.arena_begin * 2) : nullptr;
     // a member that has diverged may have left something else than zero in the padding of its rows
     bool padded = false;
     for (const NodeInfo& nd : m.nodes) padded = padded || (nd.kind != NODE_GAP && nd.ldw != nd.fan_in);
-    if (padded) {
-        const long long seg = (long long)(m.arena_end - m.arena_begin);
-        HIP_TRY(launch_fill_zero(p->master + m.arena_begin, seg * 4, p->stream), PACK_EDEVICE);
-        if (shadow) HIP_TRY(launch_fill_zero(shadow, seg * 2, p->stream), PACK_EDEVICE);
-    }
-    HIP_TRY(import_blob(p->device, p->stream, p->master + m.arena_begin, shadow, member_segs(p, k), m.n_segs, m.n_params, blob), PACK_EDEVICE);
-    return PACK_OK;
+    return transfer_status(import_blob(p->device, p->stream, p->master + m.arena_begin, shadow, member_segs(p, k), m.n_segs, m.n_params, blob,
+                                       padded ? m.arena_end - m.arena_begin : 0, 0.f));
 }
 
 pack_status download(pack_ctx* p, int k, const float* dev_arena, float* host_dst, size_t n_floats) {
@@ -1207,8 +1207,7 @@ pack_status download(pack_ctx* p, int k, const float* dev_arena, float* host_dst
     if (st != PACK_OK) return st;
     const ModelInfo& m = p->models[k];
     if (n_floats != m.n_params) return fail(PACK_EINVAL, "n_floats does not match pack_num_params");
-    HIP_TRY(export_blob(p->device, p->stream, dev_arena + m.arena_begin, member_segs(p, k), m.n_segs, m.n_params, host_dst), PACK_EDEVICE);
-    return PACK_OK;
+    return transfer_status(export_blob(p->device, p->stream, dev_arena + m.arena_begin, member_segs(p, k), m.n_segs, m.n_params, host_dst));
 }
 
 // Lays the members of p->models out in the parameter arena, allocates every device buffer, builds the
@@ -2022,9 +2021,9 @@ pack_status pack_write_opt_state(pack_t* p, int32_t k, int32_t slot, const float
     const ModelInfo& m = p->models[k];
     if (n_floats != m.n_params) return fail(PACK_EINVAL, "n_floats does not match pack_num_params");
     // (positions outside the blob, alignment gaps and padded columns, keep the optimiser's starting value)
-    HIP_TRY(import_blob(p->device, p->stream, arena + m.arena_begin, nullptr, member_segs(p, k), m.n_segs, m.n_params, host_src), PACK_EDEVICE);
-    p->opt_t[k] = steps;
-    return PACK_OK;
+    st = transfer_status(import_blob(p->device, p->stream, arena + m.arena_begin, nullptr, member_segs(p, k), m.n_segs, m.n_params, host_src, 0, 0.f));
+    if (st == PACK_OK) p->opt_t[k] = steps;
+    return st;
 }
 
 pack_status pack_gather_batch(pack_t* p, const void* data_dev, const int32_t* labels_all_dev, int64_t n_samples,

@@ -248,9 +248,12 @@ hipError_t launch_export_blob(const float* arena, const BlobSeg* segs, int n_seg
 hipError_t launch_import_blob(float* arena, void* shadow, const BlobSeg* segs, int n_segs, long long e0, int n, const float* in, hipStream_t st);
 hipError_t launch_seed_blob(float* arena, void* shadow, const BlobSeg* segs, int n_segs, long long n, unsigned long long seed, unsigned long long member, hipStream_t st);
 hipError_t launch_fill_value(float* dst, long long n, float value, hipStream_t st);
-// whole blobs between pageable host memory and an arena (pack_transfer.cpp); both wait for the stream
+// whole blobs between pageable host memory and an arena (pack_transfer.cpp); both wait for the stream.  hipErrorOutOfMemory:
+// there is no memory for the transfer and nothing has been launched.  import_blob first sets the arena's `clear` elements (0:
+// none; a multiple of 4) to `value` and their bf16 copies to zero.
 hipError_t export_blob(int device, hipStream_t st, const float* arena, const BlobSeg* segs, int n_segs, size_t n, float* host);
-hipError_t import_blob(int device, hipStream_t st, float* arena, void* shadow, const BlobSeg* segs, int n_segs, size_t n, const float* host);
+hipError_t import_blob(int device, hipStream_t st, float* arena, void* shadow, const BlobSeg* segs, int n_segs, size_t n, const float* host,
+                       size_t clear, float value);
 hipError_t launch_fill_zero(void* dst, long long bytes, hipStream_t st);
 // x_out[r] = data[idx[r]], labels_out[r] = labels_all[idx[r]] for r < rows; rows of row_bytes bytes (a multiple of 2)
 hipError_t launch_ceiling_copy(const void* src, void* dst, long long bytes, hipStream_t st);

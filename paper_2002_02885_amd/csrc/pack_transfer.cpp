@@ -66,6 +66,7 @@ hipError_t acquire(int device, Ring** out) {
     if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&r->dev, r->host, 0);
     for (int i = 0; i < SLOTS && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&r->done[i], hipEventDisableTiming);
     if (e != hipSuccess) {
+        (void)hipGetLastError();   // (a later launch is not to report it)
         destroy(r);
         return e;
     }
@@ -87,9 +88,10 @@ void give_back(Ring* r) {
 }  // namespace
 
 // Moves n floats chunk by chunk.  `enqueue(slot, first, count)` launches the kernel that fills (to_host) or drains
-// (!to_host) the pinned slot.  Every kernel has ended when this returns, also on an error.
-template <typename Enqueue>
-static hipError_t move_blob(int device, hipStream_t st, float* host, size_t n, bool to_host, Enqueue&& enqueue) {
+// (!to_host) the pinned slot; `prepare()` is called once before, when everything that can be short of memory is there.
+// Every kernel has ended when this returns, also on an error.
+template <typename Prepare, typename Enqueue>
+static hipError_t move_blob(int device, hipStream_t st, float* host, size_t n, bool to_host, Prepare&& prepare, Enqueue&& enqueue) {
     if (n == 0) return hipStreamSynchronize(st);
     int current = -1;
     hipError_t e = hipGetDevice(&current);
@@ -100,9 +102,9 @@ static hipError_t move_blob(int device, hipStream_t st, float* host, size_t n, b
     const size_t per = CHUNK_BYTES / sizeof(float);
     const size_t chunks = (n + per - 1) / per;
     const int threads = (int)std::min<size_t>(MAX_THREADS, std::max<size_t>(1, chunks));
-    std::atomic<int> failed{0};
+    std::atomic<int> failed{(int)prepare()};
     auto work = [&](int t, bool helper) {
-        hipError_t we = helper || current != device ? hipSetDevice(device) : hipSuccess;
+        hipError_t we = failed.load() ? (hipError_t)failed.load() : helper || current != device ? hipSetDevice(device) : hipSuccess;
         auto count = [&](size_t c) { return std::min(per, n - c * per); };
         auto slot_of = [&](size_t i) { return 2 * t + (int)(i & 1); };
         auto slot_dev = [&](int s) { return (float*)(ring->dev + (size_t)s * CHUNK_BYTES); };
@@ -158,13 +160,19 @@ static hipError_t move_blob(int device, hipStream_t st, float* host, size_t n, b
 }
 
 hipError_t export_blob(int device, hipStream_t st, const float* arena, const BlobSeg* segs, int n_segs, size_t n, float* host) {
-    return move_blob(device, st, host, n, true, [&](float* slot, size_t first, int count) {
+    return move_blob(device, st, host, n, true, [] { return hipSuccess; }, [&](float* slot, size_t first, int count) {
         return launch_export_blob(arena, segs, n_segs, (long long)first, count, slot, st);
     });
 }
 
-hipError_t import_blob(int device, hipStream_t st, float* arena, void* shadow, const BlobSeg* segs, int n_segs, size_t n, const float* host) {
-    return move_blob(device, st, const_cast<float*>(host), n, false, [&](float* slot, size_t first, int count) {
+hipError_t import_blob(int device, hipStream_t st, float* arena, void* shadow, const BlobSeg* segs, int n_segs, size_t n, const float* host,
+                       size_t clear, float value) {
+    auto prepare = [&] {
+        hipError_t e = clear ? launch_fill_value(arena, (long long)clear, value, st) : hipSuccess;
+        if (e == hipSuccess && clear && shadow) e = launch_fill_zero(shadow, (long long)clear * 2, st);
+        return e;
+    };
+    return move_blob(device, st, const_cast<float*>(host), n, false, prepare, [&](float* slot, size_t first, int count) {
         return launch_import_blob(arena, shadow, segs, n_segs, (long long)first, count, slot, st);
     });
 }

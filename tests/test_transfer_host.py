@@ -1,0 +1,30 @@
+"""Checkpoints in and out (csrc/pack_transfer.cpp behind the C ABI) on a made-up GPU: host code only, compiled with
+tests/transfer_driver.cpp, which defines the HIP calls, late streams and failures included.  One scenario per process."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("no hipcc to compile the driver with")
+    csrc, exe = os.path.join(ROOT, "paper_2002_02885_amd", "csrc"), str(tmp_path_factory.mktemp("transfer") / "driver")
+    subprocess.run([hipcc, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-pthread", "-rdynamic", "-I", csrc,
+                    os.path.join(csrc, "pack_api.cpp"), os.path.join(csrc, "pack_transfer.cpp"),
+                    os.path.join(ROOT, "tests", "transfer_driver.cpp"), "-o", exe, "-ldl"], check=True, capture_output=True)
+    return exe
+
+
+def _run(driver, *args):
+    r = subprocess.run([driver, *args], capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and r.stdout == "OK\n", r.stdout + r.stderr
+
+
+def test_a_call_that_finds_no_pinned_memory_leaves_the_member_unchanged(driver):
+    _run(driver, "no_pinned")

@@ -1,0 +1,317 @@
+// Driver of the library's host code on a made-up GPU: tests/test_transfer_host.py compiles it together with
+// csrc/pack_api.cpp and csrc/pack_transfer.cpp (host code only) and runs one scenario per process.  Every HIP call the
+// two files make is defined here: a stream is a queue with a thread of its own that runs what was enqueued late and in
+// order, hipStreamPerThread names another stream in every host thread, device memory is host memory.  The few kernels
+// that matter (state in and out, seeding, clearing, the fused update) are plain loops, the others do nothing.
+#include "../include/pack.h"
+#include "pack_internal.h"
+
+#include <dlfcn.h>
+#include <pthread.h>
+#include <unistd.h>
+
+#include <atomic>
+#include <condition_variable>
+#include <cstdio>
+#include <cstring>
+#include <deque>
+#include <functional>
+#include <map>
+#include <memory>
+#include <mutex>
+#include <random>
+#include <string>
+#include <thread>
+#include <vector>
+
+using namespace packk;
+
+static std::atomic<int> g_fail_at{-1};          // the n-th fallible call from now fails (negative: none)
+static std::atomic<bool> g_no_pinned{false};    // pinned allocations fail
+static std::atomic<int> g_threads_left{-1};     // threads that may still be started (negative: any number)
+static std::atomic<int> g_pinned{0}, g_events{0};
+static std::atomic<long long> g_launches{0};
+static std::mutex g_mu;
+static std::vector<std::string> g_errors;
+static std::thread::id g_main;
+static std::map<const char*, size_t> g_host;    // live pinned allocations
+
+static void error(const std::string& s) {
+    std::lock_guard<std::mutex> l(g_mu);
+    if (g_errors.size() < 20) g_errors.push_back(s);
+}
+static thread_local hipError_t g_last = hipSuccess;   // what hipGetLastError reports, as a launch does after it
+static bool fails() { return g_fail_at.load() >= 0 && g_fail_at.fetch_sub(1) == 0; }
+
+extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* arg) {
+    typedef int (*fn)(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*);
+    static fn real = (fn)dlsym(RTLD_NEXT, "pthread_create");
+    if (g_threads_left.load() >= 0 && g_threads_left.fetch_sub(1) <= 0) { g_threads_left = 0; return EAGAIN; }
+    return real(t, a, f, arg);
+}
+
+struct Queue {
+    std::mutex mu;
+    std::condition_variable cv;
+    std::deque<std::function<void()>> q;
+    bool busy = false;
+    void run() {
+        std::mt19937 rng(7);
+        for (;;) {
+            std::function<void()> f;
+            {
+                std::unique_lock<std::mutex> l(mu);
+                busy = false;
+                cv.notify_all();
+                cv.wait(l, [&] { return !q.empty(); });
+                f = std::move(q.front());
+                q.pop_front();
+                busy = true;
+            }
+            usleep(rng() % 300);
+            f();
+        }
+    }
+    void push(std::function<void()> f) {
+        std::lock_guard<std::mutex> l(mu);
+        q.push_back(std::move(f));
+        cv.notify_all();
+    }
+    void drain() {
+        std::unique_lock<std::mutex> l(mu);
+        cv.wait(l, [&] { return q.empty() && !busy; });
+    }
+};
+static std::mutex g_streams_mu;
+static std::map<std::pair<hipStream_t, std::thread::id>, Queue*> g_streams;
+static Queue* queue_of(hipStream_t s) {
+    const auto key = std::make_pair(s, s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id());
+    std::lock_guard<std::mutex> l(g_streams_mu);
+    Queue*& q = g_streams[key];
+    if (!q) {
+        q = new Queue();
+        const int left = g_threads_left.exchange(-1);
+        std::thread([q] { q->run(); }).detach();
+        g_threads_left = left;
+    }
+    return q;
+}
+static hipError_t enqueue(hipStream_t st, std::function<void()> f) {
+    if (std::this_thread::get_id() != g_main) error("a kernel was launched from another thread than the caller's");
+    ++g_launches;
+    if (fails()) return hipErrorLaunchFailure;
+    if (g_last != hipSuccess) return hipGetLastError();
+    queue_of(st)->push(std::move(f));
+    return hipSuccess;
+}
+static void check_pinned(const void* p, size_t n) {
+    std::lock_guard<std::mutex> l(g_mu);
+    auto it = g_host.upper_bound((const char*)p);
+    if (it == g_host.begin() || (--it, (const char*)p + n > it->first + it->second)) g_errors.push_back("a kernel used pinned memory that is no longer there");
+}
+
+struct Event {
+    std::mutex mu;
+    std::condition_variable cv;
+    long long recorded = 0, reached = 0;
+};
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); std::memset(*p, 0xCD, n); return hipSuccess; }
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) { queue_of(st)->push([=] { std::memcpy(d, s, n); }); return hipSuccess; }
+hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) { queue_of(st)->push([=] { std::memset(d, v, n); }); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t st) { queue_of(st)->drain(); return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError(void) { const hipError_t e = g_last; g_last = hipSuccess; return e; }
+const char* hipGetErrorString(hipError_t) { return "made-up error"; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    if (g_no_pinned || fails()) return g_last = hipErrorOutOfMemory;
+    *p = malloc(n);
+    std::lock_guard<std::mutex> l(g_mu);
+    g_host[(const char*)*p] = n;
+    ++g_pinned;
+    return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipHostFree(void* p) {
+    std::lock_guard<std::mutex> l(g_mu);
+    g_host.erase((const char*)p);
+    --g_pinned;
+    std::memset(p, 0xEE, 64);   // (not given back to the system: a late reader is to be noticed, not to crash)
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t) new Event(); ++g_events; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventDestroy(hipEvent_t) { --g_events; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t ev, hipStream_t st) {
+    if (fails()) return hipErrorUnknown;
+    Event* e = (Event*)ev;
+    long long n;
+    {
+        std::lock_guard<std::mutex> l(e->mu);
+        n = ++e->recorded;
+    }
+    queue_of(st)->push([=] { std::lock_guard<std::mutex> l(e->mu); e->reached = n; e->cv.notify_all(); });
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t ev) {
+    if (fails()) return hipErrorUnknown;
+    Event* e = (Event*)ev;
+    std::unique_lock<std::mutex> l(e->mu);
+    const long long n = e->recorded;
+    e->cv.wait(l, [&] { return e->reached >= n; });
+    return hipSuccess;
+}
+}
+
+namespace packk {
+static long long place(const BlobSeg* segs, int n_segs, long long e) {
+    int k = n_segs - 1;
+    while (segs[k].blob_off > e) --k;
+    const BlobSeg& s = segs[k];
+    const long long i = e - s.blob_off, r = i / s.inner, j = i % s.inner;
+    const long long a = s.conv ? j % 9 : j / s.cin, b = s.conv ? j / 9 : j % s.cin;
+    return s.arena_off + r * s.ldw + a * s.cpad + b;
+}
+hipError_t launch_export_blob(const float* arena, const BlobSeg* segs, int n_segs, long long e0, int n, float* out, hipStream_t st) {
+    return enqueue(st, [=] { check_pinned(out, n * 4); for (int i = 0; i < n; ++i) out[i] = arena[place(segs, n_segs, e0 + i)]; });
+}
+hipError_t launch_import_blob(float* arena, void*, const BlobSeg* segs, int n_segs, long long e0, int n, const float* in, hipStream_t st) {
+    return enqueue(st, [=] { check_pinned(in, n * 4); for (int i = 0; i < n; ++i) arena[place(segs, n_segs, e0 + i)] = in[i]; });
+}
+hipError_t launch_seed_blob(float* arena, void*, const BlobSeg* segs, int n_segs, long long n, unsigned long long, unsigned long long, hipStream_t st) {
+    return enqueue(st, [=] { for (long long i = 0; i < n; ++i) arena[place(segs, n_segs, i)] = 0.5f; });
+}
+hipError_t launch_fill_value(float* d, long long n, float v, hipStream_t st) { return enqueue(st, [=] { for (long long i = 0; i < n; ++i) d[i] = v; }); }
+hipError_t launch_fill_zero(void* d, long long n, hipStream_t st) { return enqueue(st, [=] { std::memset(d, 0, n); }); }
+// the fused update adds 1 to every weight it owns, some milliseconds after it was enqueued
+hipError_t launch_gemm(int mode, bool, int, const GemmProb* probs, const TileRef* tiles, int n, const void*, char*, const LrTable&, hipStream_t st) {
+    if (mode != LIN_DW) return hipSuccess;
+    return enqueue(st, [=] {
+        usleep(5000);
+        std::map<int, bool> done;
+        for (int t = 0; t < n; ++t) {
+            if (tiles[t].prob < 0 || done[tiles[t].prob]) continue;
+            done[tiles[t].prob] = true;
+            const GemmProb& g = probs[tiles[t].prob];
+            for (int r = 0; r < g.R; ++r)
+                for (int q = 0; q < g.Q && g.upd_w; ++q) g.upd_w[(size_t)r * g.ldc + q] += 1.f;
+        }
+    });
+}
+int conv_dw_halo_cfg(bool, const GemmProb&) { return -1; }
+int conv_rows_halo_cfg(bool, int, const GemmProb&) { return -1; }
+#define NOTHING(name, ...) hipError_t name(__VA_ARGS__) { return hipSuccess; }
+NOTHING(launch_reduce, const ReduceProb*, const int2*, int, const char*, const LrTable&, hipStream_t)
+NOTHING(static_scratch, char**)
+NOTHING(launch_ce, bool, const CeProb*, const int2*, int, const int32_t*, int*, hipStream_t)
+NOTHING(launch_ce_loss, const CeProb*, int, hipStream_t)
+NOTHING(launch_head, bool, int, const HeadProb*, const int2*, int, const int32_t*, int*, hipStream_t)
+NOTHING(launch_head_loss, const HeadProb*, int, hipStream_t)
+NOTHING(launch_gap, bool, bool, const GapProb*, const int2*, int, hipStream_t)
+NOTHING(launch_shortcut_bwd, bool, const ShortcutProb*, const int2*, int, hipStream_t)
+NOTHING(launch_sgd, float*, const float*, void*, long long, const long long*, int, const LrTable&, hipStream_t)
+NOTHING(launch_opt, float*, const float*, void*, float*, float*, long long, const long long*, const OptStatic*, int, const OptTable&, hipStream_t)
+NOTHING(launch_im2col, bool, const Im2colProb*, const int2*, int, const void*, hipStream_t)
+NOTHING(launch_wtranspose, bool, const TransposeProb*, const int2*, int, hipStream_t)
+NOTHING(launch_ceiling_copy, const void*, void*, long long, hipStream_t)
+NOTHING(launch_ceiling_mfma, bool, float*, int, int, double*, hipStream_t)
+NOTHING(launch_gather_rows, const void*, const int32_t*, const long long*, long long, int, long long, void*, int32_t*, int*, hipStream_t)
+std::string conv_dw_halo_walk(bool, bool, const GemmProb&, const TileRef&, long long, long long, bool, long long*, long long*) { return ""; }
+std::string conv_rows_halo_walk(bool, bool, bool, const GemmProb&, const TileRef&, long long, long long*, long long*) { return ""; }
+std::string gemm_fetch_walk(bool, int, int, int, const GemmProb&, const TileRef&, unsigned long long*, unsigned long long*, unsigned long long*, unsigned long long*, long long*) { return ""; }
+}  // namespace packk
+
+// ---- scenarios -------------------------------------------------------------------------------------------
+static int g_bad = 0;
+#define EXPECT(cond) do { if (!(cond)) { ++g_bad; std::printf("FAIL line %d: %s (last error: %s)\n", __LINE__, #cond, pack_last_error()); } } while (0)
+
+// a member of `features` x `width` + a head: features 3001 and width 997 make 13 MB, more chunks than the ring has slots
+struct Member {
+    pack_t* p = nullptr;
+    int features, width;
+    size_t n = 0;
+    Member(void* stream, int f, int w) : features(f), width(w) {
+        const pack_layer layers[] = {{PACK_LINEAR, w, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 300, 0}};
+        const pack_model_spec m{layers, 3, 4};
+        const pack_input_spec in{4, 1, 1, f, PACK_F32};
+        EXPECT(pack_create(&in, &m, 1, 0, stream, &p) == PACK_OK);
+        n = pack_num_params(p, 0);
+    }
+    ~Member() { pack_destroy(p); }
+    bool bias(size_t i) const {
+        const size_t w1 = (size_t)features * width, w2 = w1 + width + (size_t)width * 300;
+        return (i >= w1 && i < w1 + width) || i >= w2;
+    }
+};
+static std::vector<float> blob(size_t n, int seed) {
+    std::mt19937 rng(seed);
+    std::vector<float> b(n);
+    for (float& v : b) v = (float)(rng() % 100000);
+    return b;
+}
+
+// weights written, a step, weights read, all on `stream`: each call sees what the one before it did
+static void order(void* stream, int features, int width) {
+    Member m(stream, features, width);
+    alignas(16) static float x[4 * 4096];
+    static int32_t y[4];
+    const float lr = 0.f;
+    for (int round = 0; round < 3; ++round) {
+        const std::vector<float> b = blob(m.n, round);
+        std::vector<float> given = b, got(m.n);
+        EXPECT(pack_write_weights(m.p, 0, given.data(), m.n) == PACK_OK);
+        std::fill(given.begin(), given.end(), -1.f);   // the caller's buffer is the caller's again
+        EXPECT(pack_step(m.p, x, y, &lr) == PACK_OK);
+        EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_OK);
+        size_t wrong = 0;
+        for (size_t i = 0; i < m.n; ++i) wrong += got[i] != b[i] + (m.bias(i) ? 0.f : 1.f);
+        EXPECT(wrong == 0);
+    }
+}
+
+// no pinned memory to be had: the calls report it and the member is what it was
+static void no_pinned() {
+    Member m(nullptr, 301, 97);
+    const pack_opt_spec adagrad{PACK_OPT_ADAGRAD, 0.f, 0.5f, 0.f, 0.f, 0.f};
+    EXPECT(pack_set_optimizer(m.p, 0, &adagrad) == PACK_OK);
+    EXPECT(hipStreamSynchronize(nullptr) == hipSuccess);
+    const long long before = g_launches;
+    const std::vector<float> b = blob(m.n, 1);
+    std::vector<float> got(m.n);
+    g_no_pinned = true;
+    EXPECT(pack_write_weights(m.p, 0, b.data(), m.n) == PACK_ENOMEM);
+    EXPECT(pack_write_opt_state(m.p, 0, 0, b.data(), m.n, 7) == PACK_ENOMEM);
+    EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_ENOMEM);
+    EXPECT(g_launches == before);
+    g_no_pinned = false;
+    int64_t steps = -1;
+    EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_OK);
+    for (float v : got) if (v != 0.5f) { EXPECT(!"the weights are unchanged"); break; }
+    EXPECT(pack_read_opt_state(m.p, 0, 0, got.data(), m.n, &steps) == PACK_OK && steps == 0);
+    for (float v : got) if (v != 0.5f) { EXPECT(!"the state is unchanged"); break; }
+}
+
+int main(int argc, char** argv) {
+    if (argc < 2) return 2;
+    alarm(100);
+    g_main = std::this_thread::get_id();
+    const std::string s = argv[1];
+    if (s == "order") {
+        for (int i = 0; i < 3; ++i) order(i == 0 ? nullptr : i == 1 ? (void*)hipStreamPerThread : (void*)0x1000, 3001, 997);
+        order((void*)hipStreamPerThread, 5, 3);
+    } else if (s == "no_pinned") {
+        no_pinned();
+    } else {
+        return 2;
+    }
+    for (const std::string& e : g_errors) std::printf("FAIL %s\n", e.c_str());
+    std::printf(g_bad || !g_errors.empty() ? "FAILED\n" : "OK\n");
+    std::fflush(stdout);
+    _exit(g_bad || !g_errors.empty() ? 1 : 0);   // (the streams' threads never end)
+}

@@ -949,7 +949,10 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.B = p->im2col[nd.copy_idx].out;
                     g.flags &= ~F_B_INPUT;
                 }
-                if (!nd.kp && q_dim > nd.fan_in) { g.pad_c = nd.cpad; g.pad_real = ti.c; }   // padding between the channels of a pixel or tap
+                // padding between the channels of a pixel or tap, or beyond the taps of an im2col row: its gradient is zero by
+                // construction, not by the operands (a diverged member's 0 * inf would stay in weights and optimiser state)
+                if (nd.kp) { g.pad_c = nd.kp; g.pad_real = nd.fan_in; }
+                else if (q_dim > nd.fan_in) { g.pad_c = nd.cpad; g.pad_real = ti.c; }
                 if (dense) {
                     g.ldb = nd.kp ? nd.kp : row_pitch(p, m, nd);
                     if (nd.kp) {
@@ -2020,8 +2023,10 @@ pack_status pack_write_opt_state(pack_t* p, int32_t k, int32_t slot, const float
     if (!host_src || steps < 0) return fail(PACK_EINVAL, "null argument or negative step count");
     const ModelInfo& m = p->models[k];
     if (n_floats != m.n_params) return fail(PACK_EINVAL, "n_floats does not match pack_num_params");
-    // (positions outside the blob, alignment gaps and padded columns, keep the optimiser's starting value)
-    st = transfer_status(import_blob(p->device, p->stream, arena + m.arena_begin, nullptr, member_segs(p, k), m.n_segs, m.n_params, host_src, 0, 0.f));
+    // positions outside the blob, alignment gaps and padded columns, hold the optimiser's starting value
+    const float start = p->opt[k].kind == PACK_OPT_ADAGRAD && slot == 0 ? p->opt[k].acc0 : 0.f;
+    st = transfer_status(import_blob(p->device, p->stream, arena + m.arena_begin, nullptr, member_segs(p, k), m.n_segs, m.n_params, host_src,
+                                     m.arena_end - m.arena_begin, start));
     if (st == PACK_OK) p->opt_t[k] = steps;
     return st;
 }

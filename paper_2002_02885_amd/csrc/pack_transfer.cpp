@@ -12,11 +12,11 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
-#include <system_error>
+#include <new>
 #include <thread>
-#include <vector>
 
 namespace packk {
 namespace {
@@ -85,11 +85,100 @@ void give_back(Ring* r) {
     destroy(r);
 }
 
+// One transfer, chunk by chunk through the ring's slots.  The calling thread launches every kernel and records every
+// event, in chunk order: a stream handle may name another stream in another thread (hipStreamPerThread), and work that
+// helpers launched on it would run beside the pack's steps.  Helper threads wait for events and copy between the ring and
+// the caller's buffer.  (Against threads that launch and copy their own chunks: 6.3 MB out 0.30 -> 0.28 ms and in
+// 0.29 -> 0.26, 16.8 MB 0.62 -> 0.59 and 0.69 -> 0.63.)
+struct Transfer {
+    Ring* ring;
+    char* host;
+    size_t bytes, chunks;
+    bool to_host;
+    std::mutex mu;
+    std::condition_variable work;         // a chunk to copy, or the end
+    size_t launched = 0;                  // chunks whose kernel is on the stream, its event behind it
+    size_t next = 0;                      // next chunk to copy
+    std::atomic<size_t> copied[SLOTS];    // 1 + the last chunk copied out of (into) the slot
+    std::atomic<hipError_t> failed;
+    std::thread helpers[MAX_THREADS];
+    int wanted;
+    std::atomic<int> started{0};
+
+    Transfer(Ring* r, float* h, size_t n, bool out, hipError_t e)
+        : ring(r), host((char*)h), bytes(n * sizeof(float)), chunks((bytes + CHUNK_BYTES - 1) / CHUNK_BYTES), to_host(out), failed(e),
+          wanted((int)std::min<size_t>(MAX_THREADS, chunks - 1)) {
+        for (auto& c : copied) c = 0;
+    }
+    // a chunk can be copied out once its kernel has been launched, and in once the kernel that reads the slot's previous
+    // chunk has been
+    bool can_copy() const { return next < chunks && next < (to_host ? launched : launched + SLOTS); }
+    bool over() const { return failed != hipSuccess || next == chunks; }
+    // chunk c's kernel may be launched: the slot's previous chunk is out, or this one is in
+    bool can_launch(size_t c) const {
+        const size_t last = copied[c % SLOTS].load(std::memory_order_acquire);
+        return to_host ? c < SLOTS || last == c - SLOTS + 1 : last == c + 1;
+    }
+
+    void fail(hipError_t e) {   // under the lock
+        if (failed.load() == hipSuccess) failed.store(e);
+        work.notify_all();
+    }
+    void copy_next(std::unique_lock<std::mutex>& lock) {
+        const size_t c = next++, s = c % SLOTS, at = c * CHUNK_BYTES, len = std::min(CHUNK_BYTES, bytes - at);
+        if (next == chunks) work.notify_all();
+        lock.unlock();
+        char* const slot = ring->host + s * CHUNK_BYTES;
+        const hipError_t e = to_host || c >= SLOTS ? hipEventSynchronize(ring->done[s]) : hipSuccess;
+        if (e == hipSuccess) {
+            std::memcpy(to_host ? host + at : slot, to_host ? slot : host + at, len);
+            copied[s].store(c + 1, std::memory_order_release);
+        }
+        lock.lock();
+        if (e != hipSuccess) fail(e);
+    }
+    void help() {
+        std::unique_lock<std::mutex> lock(mu);
+        while (!over()) {
+            if (can_copy()) copy_next(lock);
+            else work.wait(lock);
+        }
+    }
+    // Starts helper i, which first starts two more: a thread takes longer to start than a kernel, and the launching thread
+    // is not to spend its time on eight.
+    void start_helper(int i) {
+        if (i >= wanted) return;
+        try {
+            helpers[i] = std::thread([this, i] {
+                start_helper(2 * i + 2);
+                start_helper(2 * i + 3);
+                help();
+            });
+            ++started;
+        } catch (...) {
+            // no more threads to be had: the others, or the launching thread, do their share
+        }
+    }
+    void join() {
+        for (std::thread& h : helpers)   // (a helper is started by one with a smaller number)
+            if (h.joinable()) h.join();
+    }
+    // the launching thread, until chunk c may be launched; it copies meanwhile only where there are fewer helpers than
+    // would keep the link busy, and does not sleep: being woken takes as long as a chunk
+    void wait_for(size_t c) {
+        if (started < MAX_THREADS) {
+            std::unique_lock<std::mutex> lock(mu);
+            while (!over() && !can_launch(c) && can_copy()) copy_next(lock);
+        }
+        while (failed == hipSuccess && !can_launch(c)) std::this_thread::yield();
+    }
+};
+
 }  // namespace
 
-// Moves n floats chunk by chunk.  `enqueue(slot, first, count)` launches the kernel that fills (to_host) or drains
-// (!to_host) the pinned slot; `prepare()` is called once before, when everything that can be short of memory is there.
-// Every kernel has ended when this returns, also on an error.
+// Moves n floats.  `enqueue(slot, first, count)` launches the kernel that fills (to_host) or drains (!to_host) the pinned
+// slot; `prepare()` is called once before, when everything that can be short of memory is there.  Every kernel has ended
+// when this returns, also on an error.
 template <typename Prepare, typename Enqueue>
 static hipError_t move_blob(int device, hipStream_t st, float* host, size_t n, bool to_host, Prepare&& prepare, Enqueue&& enqueue) {
     if (n == 0) return hipStreamSynchronize(st);
@@ -99,64 +188,36 @@ static hipError_t move_blob(int device, hipStream_t st, float* host, size_t n, b
     Ring* ring = nullptr;
     e = acquire(device, &ring);
     if (e != hipSuccess) return e;
+    if (current != device) e = hipSetDevice(device);
+    if (e == hipSuccess) e = prepare();
+    Transfer t(ring, host, n, to_host, e);
     const size_t per = CHUNK_BYTES / sizeof(float);
-    const size_t chunks = (n + per - 1) / per;
-    const int threads = (int)std::min<size_t>(MAX_THREADS, std::max<size_t>(1, chunks));
-    std::atomic<int> failed{(int)prepare()};
-    auto work = [&](int t, bool helper) {
-        hipError_t we = failed.load() ? (hipError_t)failed.load() : helper || current != device ? hipSetDevice(device) : hipSuccess;
-        auto count = [&](size_t c) { return std::min(per, n - c * per); };
-        auto slot_of = [&](size_t i) { return 2 * t + (int)(i & 1); };
-        auto slot_dev = [&](int s) { return (float*)(ring->dev + (size_t)s * CHUNK_BYTES); };
-        auto slot_host = [&](int s) { return (float*)(ring->host + (size_t)s * CHUNK_BYTES); };
-        auto start = [&](size_t i) {
-            const size_t c = t + i * threads;
-            const int s = slot_of(i);
-            hipError_t q = enqueue(slot_dev(s), c * per, (int)count(c));
-            if (q == hipSuccess) q = hipEventRecord(ring->done[s], st);
-            return q;
-        };
-        const size_t mine = chunks > (size_t)t ? (chunks - t + threads - 1) / threads : 0;
-        size_t started = 0, ended = 0;
-        if (to_host) {
-            for (; we == hipSuccess && started < std::min<size_t>(2, mine); ++started) we = start(started);
-            for (; we == hipSuccess && ended < mine; ++ended) {
-                const size_t c = t + ended * threads;
-                const int s = slot_of(ended);
-                we = hipEventSynchronize(ring->done[s]);
-                if (we != hipSuccess) break;
-                std::memcpy(host + c * per, slot_host(s), count(c) * sizeof(float));
-                if (started < mine) we = start(started++);
-            }
-        } else {
-            for (; we == hipSuccess && started < mine; ++started) {
-                const size_t c = t + started * threads;
-                const int s = slot_of(started);
-                if (started >= 2) we = hipEventSynchronize(ring->done[s]);
-                if (we != hipSuccess) break;
-                std::memcpy(slot_host(s), host + c * per, count(c) * sizeof(float));
-                we = start(started);
-            }
+    for (size_t c = 0; c < t.chunks; ++c) {
+        // (into the arena there is something to copy at once, out of it when the first kernels have been launched)
+        if (c == (to_host ? std::min<size_t>(2, t.chunks - 1) : 0)) {
+            t.start_helper(0);
+            t.start_helper(1);
         }
-        if (we != hipSuccess) {
-            int none = 0;
-            failed.compare_exchange_strong(none, (int)we);
+        t.wait_for(c);
+        if (t.failed != hipSuccess) break;
+        const size_t s = c % SLOTS;
+        e = enqueue((float*)(ring->dev + s * CHUNK_BYTES), c * per, (int)std::min(per, n - c * per));
+        if (e == hipSuccess && (to_host || c + SLOTS < t.chunks)) e = hipEventRecord(ring->done[s], st);   // (where somebody waits for it)
+        std::unique_lock<std::mutex> lock(t.mu);
+        if (e != hipSuccess) {
+            t.fail(e);
+            break;
         }
-    };
-    std::vector<std::thread> pool;
-    int handed = 1;
-    try {
-        for (; handed < threads; ++handed) pool.emplace_back(work, handed, true);
-    } catch (const std::system_error&) {
-        // no more threads to be had: this one does their share
+        t.launched = c + 1;
+        lock.unlock();
+        t.work.notify_one();
     }
-    work(0, false);
-    for (int t = handed; t < threads; ++t) work(t, false);
-    for (std::thread& t : pool) t.join();
+    t.help();
+    t.join();
     e = hipStreamSynchronize(st);
     if (current != device) (void)hipSetDevice(current);
-    give_back(ring);
-    return failed.load() ? (hipError_t)failed.load() : e;
+    if (e == hipSuccess) give_back(ring);   // (a ring that a kernel may still be using is neither used again nor released)
+    return t.failed != hipSuccess ? t.failed.load() : e;
 }
 
 hipError_t export_blob(int device, hipStream_t st, const float* arena, const BlobSeg* segs, int n_segs, size_t n, float* host) {

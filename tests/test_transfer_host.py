@@ -28,3 +28,17 @@ def _run(driver, *args):
 
 def test_a_call_that_finds_no_pinned_memory_leaves_the_member_unchanged(driver):
     _run(driver, "no_pinned")
+
+
+def test_every_kernel_of_a_transfer_is_launched_by_the_calling_thread(driver):
+    """A handle may name another stream in another thread (hipStreamPerThread): weights written, a step and weights read
+    back see each other, and the caller's buffer is not read after the call."""
+    _run(driver, "order")
+
+
+def test_transfers_with_fewer_threads_than_wanted(driver):
+    _run(driver, "few_threads")
+
+
+def test_a_failure_anywhere_in_a_transfer_ends_it_and_the_next_one_works(driver):
+    _run(driver, "failures")

@@ -297,6 +297,39 @@ static void no_pinned() {
     for (float v : got) if (v != 0.5f) { EXPECT(!"the state is unchanged"); break; }
 }
 
+// fewer threads than wanted, down to none
+static void few_threads() {
+    for (int left : {0, 1, 3}) {
+        Member m(nullptr, 3001, 997);
+        const std::vector<float> b = blob(m.n, left);
+        std::vector<float> got(m.n);
+        EXPECT(hipStreamSynchronize(nullptr) == hipSuccess);
+        g_threads_left = left;
+        EXPECT(pack_write_weights(m.p, 0, b.data(), m.n) == PACK_OK);
+        g_threads_left = left;
+        EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_OK);
+        g_threads_left = -1;
+        EXPECT(got == b);
+    }
+}
+
+// the n-th launch, event or wait of a transfer fails: it says so and ends, and the next one works
+static void failures() {
+    Member m(nullptr, 3001, 997);
+    const std::vector<float> b = blob(m.n, 3);
+    std::vector<float> got(m.n);
+    EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_OK);
+    for (int n = 0; n < 47; n += n < 6 ? 1 : 9) {
+        g_fail_at = n;
+        EXPECT(pack_write_weights(m.p, 0, b.data(), m.n) == PACK_EDEVICE);
+        g_fail_at = n;
+        EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_EDEVICE);
+        g_fail_at = -1;
+        EXPECT(pack_write_weights(m.p, 0, b.data(), m.n) == PACK_OK);
+        EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_OK && got == b);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -307,6 +340,10 @@ int main(int argc, char** argv) {
         order((void*)hipStreamPerThread, 5, 3);
     } else if (s == "no_pinned") {
         no_pinned();
+    } else if (s == "few_threads") {
+        few_threads();
+    } else if (s == "failures") {
+        failures();
     } else {
         return 2;
     }

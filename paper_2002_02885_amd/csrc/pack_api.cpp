@@ -706,15 +706,18 @@ void add_mapped_launch(pack_ctx* p, DescBuilder& db, int kind, const std::vector
 
 inline int elem_vec(bool bf16) { return bf16 ? 8 : 4; }
 
-// the aligned kernels address an operand inside a 2 GB window (some room left for a convolution's margin of a row and
-// a pixel), and divide by the channels of a tap and the pixels of a map with 32-bit multipliers
-inline bool small_tensors(const TensorInfo& a, const TensorInfo& b, bool bf16) {
-    auto ok = [&](const TensorInfo& t) {
-        const double px = (double)t.h * t.w, c = (double)align_up((size_t)t.c, 8);
-        return t.n * px * c * (bf16 ? 2 : 4) < 1.8e9 && (t.w + 1) * c * (bf16 ? 2 : 4) < 1e8 && px < 60000 && c < 16384;
-    };
-    return ok(a) && ok(b);
+// Which kernels a convolution between tensors a and b may take.  The aligned ones index rows and outputs with 32-bit element
+// offsets (add_gemm_launch holds their operands to a 2 GB window as well).  Where a chunk straddles taps, images or rows they
+// need the general gather, and that its 32-bit multipliers divide exactly; whole chunks divide by nothing.
+inline int conv_flags(const TensorInfo& a, const TensorInfo& b, bool straddles, bool divides) {
+    auto small = [](const TensorInfo& t) { return (size_t)t.n * t.h * t.w * align_up((size_t)t.c, 8) < (size_t)1 << 30; };
+    if (!small(a) || !small(b) || (straddles && !divides)) return 0;
+    return F_VEC_A | F_VEC_B | (straddles ? F_GATHER : 0);
 }
+// a reduction index over the nine taps of `span` channels by the span, and a pixel of up to a chunk beyond an image of hw
+// pixels by hw: n * d < 2^32 (div_multiplier), with some room left
+inline bool span_divides(int span) { return span < 16384; }
+inline bool image_divides(int hw) { return hw < 60000; }
 
 // row of a LINEAR layer's input as the products see it: the features, padding between the channels of pixels included
 inline int inner_dim(const ModelInfo& m, const NodeInfo& nd) {
@@ -823,7 +826,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 set_row_space(g, to.w, to.h * to.w);
                 g.lda = nd.cpad; g.ldb = nd.ldw; g.ldc = to.pitch;
                 // a chunk that stays inside one tap needs no per-thread tap
-                if (small_tensors(ti, to, bf)) g.flags |= F_VEC_A | F_VEC_B | (nd.cpad % BKc ? F_GATHER : 0);
+                g.flags |= conv_flags(ti, to, nd.cpad % BKc != 0, span_divides(nd.cpad));
                 g.mg_span = div_multiplier(nd.cpad);
                 g.ksplit = g.Kd;
                 conv.push_back(g);
@@ -965,8 +968,8 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     // chunks of output pixels that stay inside one image, with rows that decode by shifts, need no
                     // division per chunk
                     const bool pow2 = (to.w & (to.w - 1)) == 0;
-                    if (!small_tensors(ti, to, bf)) g.flags &= ~(F_VEC_A | F_VEC_B);
-                    else if (!pow2 || to.w < 4 || (to.h * to.w) % BKc) g.flags |= F_GATHER;
+                    g.flags &= ~(F_VEC_A | F_VEC_B);
+                    g.flags |= conv_flags(ti, to, !pow2 || to.w < 4 || (to.h * to.w) % BKc != 0, image_divides(to.h * to.w));
                     g.mg_hw = div_multiplier(to.h * to.w);
                     g.mg_w = div_multiplier(to.w);
                 }
@@ -1049,7 +1052,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.B = (const char*)p->wt + nd.wt_off * esz;   // transposed copy [Cin][9][Cout]
                     g.lda = to.pitch; g.ldb = 9 * to.pitch; g.ldc = ti.pitch;
                     g.flags |= F_PAD_OUT;
-                    if (small_tensors(ti, to, bf)) g.flags |= F_VEC_A | F_VEC_B | (to.pitch % BKc ? F_GATHER : 0);
+                    g.flags |= conv_flags(ti, to, to.pitch % BKc != 0, span_divides(to.pitch));
                     g.mg_span = div_multiplier(to.pitch);
                     g.ksplit = g.Kd;
                     const bool with_sc = ti.sc_dz != nullptr;

@@ -68,3 +68,13 @@ def test_weights_loaded_after_a_member_diverged_train_as_if_it_never_had():
             pk.step(x.data_ptr(), y.data_ptr(), np.array([0.01], np.float32))
         got.append(pk.read_weights(0))
     assert np.all(np.isfinite(got[0])) and np.array_equal(got[0], got[1])
+
+
+# 251 x 250 pixels: the weight gradient over them goes element by element on padded channels; 256 x 256: whole chunks of
+# channels on the staged-tile and halo kernels
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("shape,widths", [((251, 250, 5), (9, 12)), ((256, 256, 8), (64, 32))])
+def test_maps_of_more_than_60000_pixels(shape, widths, dtype):
+    layers = [("conv3x3", widths[0], 1), ("relu",), ("conv3x3", widths[1], 1), ("tanh",), ("conv3x3", widths[1], 2), ("relu",), ("gap",), ("linear", 7)]
+    w = wl.custom(f"large_map_{shape[0]}", 25, dtype, 1, shape, [layers], n_classes=7, steps=1)
+    tp._check_f32(w, trials=1) if dtype == wl.F32 else tp._check_bf16(w, trials=1)

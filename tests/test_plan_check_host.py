@@ -72,6 +72,26 @@ def test_reductions_of_split_weight_gradients_read_stored_elements_only(B, shape
     binding.plan_check(B, shape, dtype, [layers, layers], [B, B - 1])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("side,channels,widths,by_element", [
+    (256, 3, (64, 64), 0), (256, 8, (64, 128), 0),          # maps of 65536 pixels, whole chunks of channels
+    (300, 8, (64, 64), 1), (300, 8, (24, 40), 1),           # of 90000, no power of two: only the weight gradients' launch, whose
+])                                                          # gather divides by the pixels of a map with 32-bit multipliers
+def test_large_maps_stay_on_the_aligned_kernels(side, channels, widths, by_element, dtype):
+    layers = [("conv3x3", widths[0], 1), ("relu",), ("conv3x3", widths[1], 1), ("relu",), ("gap",), ("linear", 10)]
+    walked, skipped, loads = binding.plan_check(1, (side, side, channels), dtype, [layers])
+    assert walked > 0 and skipped == by_element and loads > 0
+
+
+@pytest.mark.parametrize("channels,by_element", [(16384, 0), (16392, 1)])
+def test_channel_counts_the_general_gather_divides_by(channels, by_element):
+    """A forward pass over 16392 channels, which fill no whole chunks, is beyond the multipliers' range and goes element by
+    element; 16384 fill whole chunks, whose addresses need no division."""
+    layers = [("conv3x3", channels, 1), ("relu",), ("conv3x3", 8, 1), ("relu",), ("gap",), ("linear", 3)]
+    walked, skipped, loads = binding.plan_check(1, (1, 2, 8), "f32", [layers])
+    assert walked > 0 and skipped == by_element and loads > 0
+
+
 def test_members_on_their_own_batches_and_argument_errors():
     w = wl.config5(K=2, B=4, size=16, widths=(64, 64), n_classes=10, steps=1)
     _check(w, per_member_input=True)

@@ -303,7 +303,9 @@ pack_status pack_step(pack_t* p, const void* x_dev, const int32_t* labels_dev, c
  * the library runs on holds its own copy until the process ends).  The call allocates and frees nothing,
  * on the device or through any library; the first call on a device looks the array's address up.
  * A pack whose split weight gradients need more than the array holds (pack_workspace_bytes(p)) is rejected
- * with PACK_ENOMEM and nothing is launched; the five reference configurations need at most 113 MB.  Launch
+ * with PACK_ENOMEM and nothing is launched; the five reference configurations need at most 113 MB.  (Rows are
+ * padded to whole groups of 8 channels; a pack that only this padding takes beyond the array is accepted and
+ * keeps its sums in the workspace it has had since its creation.)  Launch
  * timing must be off (PACK_EINVAL otherwise: events are allocations).  All packs of a process share the
  * array of their GPU: a step overwrites what the previous one left there and needs nothing cleared, but
  * two steps that overlap in time on one GPU (different streams or threads) race on it; keep such steps on

@@ -149,6 +149,7 @@ struct pack_ctx {
     size_t slab_bytes = 0;
     char* workspace = nullptr;   // partial sums of split reductions
     size_t workspace_bytes = 0;
+    size_t workspace_unpadded = 0;   // what it would be without the padding of rows to groups of 8 channels
     char* desc = nullptr;        // problem descriptors and block maps
     size_t desc_bytes = 0;
     int* err_flag = nullptr;
@@ -910,7 +911,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
     std::vector<ReduceProb> dw_red;
     std::vector<int> dw_red_blocks;
     std::vector<GemmProb> lin_dw, conv_dw;
-    size_t ws_off = 0;
+    size_t ws_off = 0, ws_unpadded = 0;
     for (size_t s = max_nodes; s-- > 0;) {
         std::vector<GemmProb> lin_dx, conv_dx;
         std::vector<GapProb> gaps;
@@ -1006,6 +1007,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     dw_red.push_back(r);
                     dw_red_blocks.push_back((int)((nd.w_arena + 1023) / 1024));
                     ws_off += align_up((size_t)S * nd.w_arena * 4, 256);
+                    ws_unpadded += align_up((size_t)S * (nd.kp ? nd.w_arena : nd.w_elems) * 4, 256) + align_up((size_t)S * nd.out * 4, 256);
                     g.dbias = (float*)(uintptr_t)ws_off;
                     ReduceProb rb{};
                     rb.in = (const float*)(uintptr_t)ws_off; rb.out = p->grad + nd.b_off; rb.stride = nd.out; rb.n = nd.out; rb.S = S;
@@ -1117,6 +1119,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
         add_mapped_launch(p, db, L_GAP_BWD, gaps, gap_blocks);
     }
     ws_need = ws_off;
+    p->workspace_unpadded = ws_unpadded;
     // a grid drains best when its slowest tiles start first: unaligned problems (scalar gather),
     // then long reductions, then large outputs
     auto slow_first = [](const GemmProb& a, const GemmProb& b) {
@@ -1853,7 +1856,8 @@ size_t pack_workspace_bytes(const pack_t* p) { return p ? p->workspace_bytes : 0
 pack_status pack_step_static(pack_t* p, const void* x_dev, const int32_t* labels_dev, const float* lr_host) {
     if (!p || !x_dev || !labels_dev || !lr_host) return fail(PACK_EINVAL, "null argument");
     if (p->profiling) return fail(PACK_EINVAL, "pack_step_static does not time launches (events are allocations): call pack_profile_stop first");
-    if (p->workspace_bytes > STATIC_SCRATCH_BYTES)
+    // (the padding of rows is the library's own business: it makes no pack too large for this call)
+    if (p->workspace_unpadded > STATIC_SCRATCH_BYTES)
         return fail(PACK_ENOMEM, "the pack's split weight gradients need " + std::to_string(p->workspace_bytes) +
                                  " bytes of scratch, the library's static array holds " + std::to_string(STATIC_SCRATCH_BYTES));
     // the array's address on this device, looked up once per device (every GPU holds its own copy)
@@ -1863,6 +1867,7 @@ pack_status pack_step_static(pack_t* p, const void* x_dev, const int32_t* labels
     HIP_TRY(hipGetDevice(&dev), PACK_EDEVICE);
     if (dev < 0 || dev >= 64) return fail(PACK_EDEVICE, "device index outside [0, 64)");
     if (dev != p->device) return fail(PACK_EINVAL, "the pack was created on another device than the current one");
+    if (p->workspace_bytes > STATIC_SCRATCH_BYTES) return step_with_workspace(p, x_dev, labels_dev, lr_host, p->workspace);
     char* ws = nullptr;
     {
         std::lock_guard<std::mutex> lock(mu);

@@ -85,3 +85,21 @@ def test_static_scratch_step_rejects_what_does_not_fit_and_a_pack_that_is_being_
         assert e.value.status == binding.PACK_ENOMEM and "static" in str(e.value)
     finally:
         pk.destroy()
+
+
+def test_static_scratch_step_takes_a_pack_that_only_padded_rows_make_too_large():
+    """Two convolutions of 124 channels, 118 splits each: 131 MB of partial sums, 135 with the rows padded to 128 channels."""
+    layers = [op for _ in range(3) for op in (("conv3x3", 124, 1), ("relu",))] + [("gap",), ("linear", 10)]
+    w = wl.custom("padded_scratch", 12, wl.F32, 118, (32, 32, 3), [layers], lr=[0.01], steps=2)
+    ref, sta = _twins(w)
+    try:
+        assert 0 < sta.workspace_bytes() - binding.static_scratch_bytes() < 4 << 20
+        x, y = pu.device_inputs(w)
+        for _ in range(w.steps):
+            ref.step(x.data_ptr(), y.data_ptr(), w.lr)
+            sta.step_static(x.data_ptr(), y.data_ptr(), w.lr)
+        (wr, lr_, pr), (ws, ls, ps) = _state(ref, w), _state(sta, w)
+        assert np.array_equal(wr[0], ws[0]) and np.array_equal(lr_, ls) and np.array_equal(pr[0], ps[0]) and np.isfinite(ls[0])
+    finally:
+        ref.destroy()
+        sta.destroy()

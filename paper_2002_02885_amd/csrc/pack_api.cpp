@@ -1384,7 +1384,7 @@ pack_status build_device(pack_ctx* p) {
 }
 
 // seeded initial weights of member k: uniform in +-sqrt(6/fan_in), biases in +-1/sqrt(fan_in), drawn on the device
-// (enqueues only)
+// (enqueues only: the caller waits)
 pack_status seed_weights(pack_ctx* p, int k, uint64_t seed) {
     const ModelInfo& m = p->models[k];
     void* const shadow = p->bf16 ? (void*)((char*)p->shadow + m.arena_begin * 2) : nullptr;
@@ -1458,6 +1458,8 @@ pack_status rebuild(pack_ctx* p, int B, const std::vector<SlotPlan>& slots, uint
         s = seed_weights(q, k, seed);
         if (s != PACK_OK) { release(q); return s; }
     }
+    e = hipStreamSynchronize(p->stream);
+    if (e != hipSuccess) { release(q); return fail(PACK_EDEVICE, std::string("initial weights: ") + hipGetErrorString(e)); }
     std::swap(*p, *q);
     release(q);   // the previous buffers
     return PACK_OK;
@@ -1521,6 +1523,10 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
     for (int k = 0; k < K; ++k) {
         s = seed_weights(p, k, seed);
         if (s != PACK_OK) { release(p); return s; }
+    }
+    if (const hipError_t e = hipStreamSynchronize(p->stream); e != hipSuccess) {
+        release(p);
+        return fail(PACK_EDEVICE, std::string("initial weights: ") + hipGetErrorString(e));
     }
     *out = p;
     return PACK_OK;
@@ -2002,6 +2008,7 @@ pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec) 
     const long long seg = (long long)(m.arena_end - m.arena_begin);
     if (p->opt_m) HIP_TRY(launch_fill_value(p->opt_m + m.arena_begin, seg, o.kind == PACK_OPT_ADAGRAD ? o.acc0 : 0.f, p->stream), PACK_EDEVICE);
     if (p->opt_v) HIP_TRY(launch_fill_value(p->opt_v + m.arena_begin, seg, 0.f, p->stream), PACK_EDEVICE);
+    HIP_TRY(hipStreamSynchronize(p->stream), PACK_EDEVICE);
     return PACK_OK;
 }
 

@@ -42,3 +42,8 @@ def test_transfers_with_fewer_threads_than_wanted(driver):
 
 def test_a_failure_anywhere_in_a_transfer_ends_it_and_the_next_one_works(driver):
     _run(driver, "failures")
+
+
+def test_a_pack_is_ready_when_the_call_that_made_it_returns(driver):
+    """Creation, a joining member and a new optimiser as another thread sees them, and creation on a capturing stream."""
+    _run(driver, "ready")

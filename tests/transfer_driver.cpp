@@ -33,6 +33,7 @@ static std::atomic<int> g_pinned{0}, g_events{0};
 static std::atomic<long long> g_launches{0};
 static std::mutex g_mu;
 static std::vector<std::string> g_errors;
+static std::atomic<bool> g_capturing{false};    // the streams are being captured: waiting for one is an error
 static std::thread::id g_main;
 static std::map<const char*, size_t> g_host;    // live pinned allocations
 
@@ -96,6 +97,14 @@ static Queue* queue_of(hipStream_t s) {
     }
     return q;
 }
+static bool idle() {
+    std::lock_guard<std::mutex> l(g_streams_mu);
+    for (auto& q : g_streams) {
+        std::lock_guard<std::mutex> lq(q.second->mu);
+        if (!q.second->q.empty() || q.second->busy) return false;
+    }
+    return true;
+}
 static hipError_t enqueue(hipStream_t st, std::function<void()> f) {
     if (std::this_thread::get_id() != g_main) error("a kernel was launched from another thread than the caller's");
     ++g_launches;
@@ -123,7 +132,11 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::mem
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) { queue_of(st)->push([=] { std::memcpy(d, s, n); }); return hipSuccess; }
 hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) { queue_of(st)->push([=] { std::memset(d, v, n); }); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t st) { queue_of(st)->drain(); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t st) {
+    if (g_capturing) return hipErrorStreamCaptureUnsupported;
+    queue_of(st)->drain();
+    return hipSuccess;
+}
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError(void) { const hipError_t e = g_last; g_last = hipSuccess; return e; }
@@ -330,6 +343,36 @@ static void failures() {
     }
 }
 
+// what a call has set up is there when it returns, for a thread whose stream is another one too, and no pack is created on
+// a stream that only records
+static void ready() {
+    Member m((void*)hipStreamPerThread, 301, 97);
+    const pack_opt_spec adagrad{PACK_OPT_ADAGRAD, 0.f, 0.25f, 0.f, 0.f, 0.f};
+    const pack_layer layers[] = {{PACK_LINEAR, 3, 0}};
+    const pack_model_spec one{layers, 1, 4};
+    std::vector<float> got(m.n), state(m.n, 0.f), joined;
+    EXPECT(idle());
+    auto elsewhere = [&](auto f) {
+        std::thread([&] { g_main = std::this_thread::get_id(); f(); }).join();
+        g_main = std::this_thread::get_id();
+    };
+    elsewhere([&] { EXPECT(pack_read_weights(m.p, 0, got.data(), m.n) == PACK_OK); });
+    EXPECT(got == std::vector<float>(m.n, 0.5f));
+    EXPECT(pack_set_optimizer(m.p, 0, &adagrad) == PACK_OK && idle());
+    elsewhere([&] { EXPECT(pack_read_opt_state(m.p, 0, 0, state.data(), m.n, nullptr) == PACK_OK); });
+    EXPECT(state == std::vector<float>(m.n, 0.25f));
+    int32_t k = -1;
+    EXPECT(pack_load(m.p, &one, 1, &k) == PACK_OK && k == 1 && idle());
+    joined.resize(pack_num_params(m.p, 1));
+    elsewhere([&] { EXPECT(pack_read_weights(m.p, 1, joined.data(), joined.size()) == PACK_OK); });
+    EXPECT(joined == std::vector<float>(joined.size(), 0.5f));
+    const pack_input_spec in{4, 1, 1, 30, PACK_F32};
+    pack_t* p = nullptr;
+    g_capturing = true;
+    EXPECT(pack_create(&in, &one, 1, 0, (void*)0x2000, &p) == PACK_EDEVICE && !p);
+    g_capturing = false;
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -342,6 +385,8 @@ int main(int argc, char** argv) {
         no_pinned();
     } else if (s == "few_threads") {
         few_threads();
+    } else if (s == "ready") {
+        ready();
     } else if (s == "failures") {
         failures();
     } else {

@@ -1528,6 +1528,7 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
         release(p);
         return fail(PACK_EDEVICE, std::string("initial weights: ") + hipGetErrorString(e));
     }
+    transfer_open();
     *out = p;
     return PACK_OK;
 }
@@ -2164,6 +2165,7 @@ void pack_destroy(pack_t* p) {
     if (!p) return;
     (void)hipStreamSynchronize(p->stream);
     release(p);
+    transfer_close();
 }
 
 }  // extern "C"

@@ -254,6 +254,9 @@ hipError_t launch_fill_value(float* dst, long long n, float value, hipStream_t s
 hipError_t export_blob(int device, hipStream_t st, const float* arena, const BlobSeg* segs, int n_segs, size_t n, float* host);
 hipError_t import_blob(int device, hipStream_t st, float* arena, void* shadow, const BlobSeg* segs, int n_segs, size_t n, const float* host,
                        size_t clear, float value);
+// a pack has been created, is about to go: the pinned memory that is kept between transfers goes with the last one
+void transfer_open();
+void transfer_close();
 hipError_t launch_fill_zero(void* dst, long long bytes, hipStream_t st);
 // x_out[r] = data[idx[r]], labels_out[r] = labels_all[idx[r]] for r < rows; rows of row_bytes bytes (a multiple of 2)
 hipError_t launch_ceiling_copy(const void* src, void* dst, long long bytes, hipStream_t st);

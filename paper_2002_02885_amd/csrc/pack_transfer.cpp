@@ -17,6 +17,7 @@
 #include <mutex>
 #include <new>
 #include <thread>
+#include <utility>
 
 namespace packk {
 namespace {
@@ -31,10 +32,12 @@ struct Ring {
     hipEvent_t done[SLOTS] = {};
 };
 
-// One idle ring (8 MB) is kept for the next transfer, whichever pack asks for it; every further one is released
-// when its transfer ends.  (Pinning 8 MB and touching it for the first time takes 3 ms, as long as a transfer of 150 MB.)
+// One idle ring (8 MB) is kept for the next transfer, whichever pack asks for it, while there is a pack; every further one
+// is released when its transfer ends, and the last one with the last pack.  (A transfer that makes and releases its own
+// spends some 60 us on it; the first of a process, whose pages the system has yet to pin and clear, 3 ms.)
 std::mutex g_mu;
 Ring* g_idle = nullptr;
+int g_packs = 0;
 
 void destroy(Ring* r) {
     if (!r) return;
@@ -175,6 +178,19 @@ struct Transfer {
 };
 
 }  // namespace
+
+void transfer_open() {
+    std::lock_guard<std::mutex> lock(g_mu);
+    ++g_packs;
+}
+void transfer_close() {
+    Ring* last = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_mu);
+        if (--g_packs == 0) std::swap(last, g_idle);
+    }
+    destroy(last);
+}
 
 // Moves n floats.  `enqueue(slot, first, count)` launches the kernel that fills (to_host) or drains (!to_host) the pinned
 // slot; `prepare()` is called once before, when everything that can be short of memory is there.  Every kernel has ended

@@ -47,3 +47,7 @@ def test_a_failure_anywhere_in_a_transfer_ends_it_and_the_next_one_works(driver)
 def test_a_pack_is_ready_when_the_call_that_made_it_returns(driver):
     """Creation, a joining member and a new optimiser as another thread sees them, and creation on a capturing stream."""
     _run(driver, "ready")
+
+
+def test_pinned_memory_goes_with_the_last_pack(driver):
+    _run(driver, "released")

@@ -373,6 +373,24 @@ static void ready() {
     g_capturing = false;
 }
 
+// the pinned memory kept between transfers: one ring while there is a pack, nothing after the last one
+static void released() {
+    for (int round = 0; round < 2; ++round) {
+        Member a(nullptr, 301, 97);
+        std::vector<float> got(a.n);
+        {
+            Member b(nullptr, 301, 97);
+            EXPECT(pack_read_weights(b.p, 0, got.data(), b.n) == PACK_OK && g_pinned == 1);
+            EXPECT(pack_read_weights(a.p, 0, got.data(), a.n) == PACK_OK && g_pinned == 1);
+        }
+        EXPECT(g_pinned == 1);
+        EXPECT(pack_write_weights(a.p, 0, got.data(), a.n) == PACK_OK && g_pinned == 1);
+        pack_destroy(a.p);
+        a.p = nullptr;
+        EXPECT(g_pinned == 0 && g_events == 0);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -387,6 +405,8 @@ int main(int argc, char** argv) {
         few_threads();
     } else if (s == "ready") {
         ready();
+    } else if (s == "released") {
+        released();
     } else if (s == "failures") {
         failures();
     } else {

@@ -515,7 +515,9 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
         return is_input ? std::make_pair(1, x_off) : std::make_pair(0, (long long)(uintptr_t)ptr);
     };
     for (const GemmProb& g : probs) {
-        L.flops += 2.0 * g.R * g.Q * (g.kd_real ? g.kd_real : g.Kd);
+        // (multiply-adds of the layers as they are: neither reduction nor columns count the padding between channels)
+        const double cols = (g.pad_c && g.Q > g.pad_c) ? (double)g.Q / g.pad_c * g.pad_real : g.Q;
+        L.flops += 2.0 * g.R * cols * (g.kd_real ? g.kd_real : g.Kd);
         const double out = (double)g.R * g.Q;
         double a = 0, b = 0, c = 0;
         switch (mode) {
@@ -1044,6 +1046,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.R = ti.n; g.Q = inner_dim(m, nd); g.Kd = nd.out;
                     g.lda = to.ld_dz ? to.ld_dz : to.pitch; g.ldb = nd.ldw; g.ldc = nd.ldw;
                     g.flags |= F_VEC_A | F_VEC_B | F_PAD_OUT;
+                    if (g.Q > nd.fan_in) { g.pad_c = nd.cpad; g.pad_real = ti.c; }
                     g.ksplit = g.Kd;
                     lin_dx.push_back(g);
                 } else {

@@ -51,3 +51,7 @@ def test_a_pack_is_ready_when_the_call_that_made_it_returns(driver):
 
 def test_pinned_memory_goes_with_the_last_pack(driver):
     _run(driver, "released")
+
+
+def test_counted_operations_are_those_of_the_layers_without_padding(driver):
+    _run(driver, "work")

@@ -391,6 +391,33 @@ static void released() {
     }
 }
 
+// multiply-adds as the layers define them, whatever the rows are padded to: 5 -> 12 -> 9 channels, 3 x 3 x 9 -> 11 -> 20 features
+static void work() {
+    const pack_layer layers[] = {{PACK_CONV3X3, 12, 1}, {PACK_RELU, 0, 0}, {PACK_CONV3X3, 9, 2}, {PACK_RELU, 0, 0},
+                                 {PACK_LINEAR, 11, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 20, 0}};
+    for (int dtype : {PACK_F32, PACK_BF16}) {
+        const pack_model_spec m{layers, 7, 4};
+        const pack_input_spec in{4, 6, 6, 5, dtype};
+        pack_t* p = nullptr;
+        EXPECT(pack_create(&in, &m, 1, 0, nullptr, &p) == PACK_OK);
+        std::map<std::string, double> got;
+        for (int i = 0; i < pack_num_launches(p); ++i) {
+            char name[64];
+            double f = 0.0;
+            EXPECT(pack_launch_name(p, i, name, sizeof name) == PACK_OK && pack_launch_flops(p, i, &f) == PACK_OK);
+            got[std::string(name).substr(0, std::string(name).find('+'))] += f;
+        }
+        const double c1 = 2.0 * 4 * 36 * 45 * 12, c2 = 2.0 * 4 * 9 * 108 * 9, l1 = 2.0 * 4 * 81 * 11, l2 = 2.0 * 4 * 11 * 20;
+        EXPECT(got["gemm_conv_fwd"] == c1 + c2);
+        EXPECT(got["gemm_conv_dw"] == c1 + c2);
+        EXPECT(got["gemm_conv_dx"] == c2);   // (each product of the stride-2 layer once: parity classes)
+        EXPECT(got["gemm_lin_fwd"] == l1 + l2);
+        EXPECT(got["gemm_lin_dw"] == l1 + l2);
+        EXPECT(got["gemm_lin_dx"] == l1 + l2);
+        pack_destroy(p);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -407,6 +434,8 @@ int main(int argc, char** argv) {
         ready();
     } else if (s == "released") {
         released();
+    } else if (s == "work") {
+        work();
     } else if (s == "failures") {
         failures();
     } else {

@@ -28,7 +28,7 @@
  *     owns weights (fp32 master, bf16 operand copy), activations, gradients, loss/prediction
  *     buffers and the launch plan, and releases them in pack_destroy.
  *   - pack_step only enqueues work on the stream given at pack_create and does not wait for it.
- *     pack_read_* and pack_write_weights wait for that stream.
+ *     pack_read_* and pack_write_* wait for that stream.
  *   - Shared batch x: row-major [B, D] for flat inputs, NHWC [B, H, W, C] for images; element type
  *     float for PACK_F32 packs, bfloat16 (upper 16 bits of a float) for PACK_BF16 packs.
  *   - labels: int32 [B], one vector shared by all members (one dataset, Section 3.4), values in
@@ -125,7 +125,7 @@ typedef struct {
  * `models` and the layer arrays are host memory and are copied.  Weights are initialised from
  * `seed` (uniform in +-sqrt(6/fan_in), biases in +-1/sqrt(fan_in)); callers that need specific
  * weights use pack_write_weights.  `hip_stream` is a hipStream_t (0 = the null stream) on
- * which every later call enqueues its work.
+ * which every later call enqueues its work.  The pack is ready when the call returns.
  * The layer list must end in a PACK_LINEAR (without ReLU): its output [b_k, C_k] is the logits.
  * Errors: PACK_EINVAL, PACK_ESHAPE (unsupported op order, RES_BEGIN/RES_END mismatch, shortcut
  * shapes that neither agree nor halve, last layer not linear), PACK_ENOMEM, PACK_EDEVICE. */
@@ -143,7 +143,7 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
  * an operand slot holding the wrong element, a tile dealt twice or not at all, a reduction of split weight
  * gradients that adds elements no product stores is an error.
  * input_mode: pack_input_mode.  Outputs (host, may be null): launches walked, matrix-product launches on the
- * element-by-element kernels for unaligned shapes (skipped: they load by the definition itself), loads and
+ * element-by-element kernels for sizes the others do not address (skipped: they load by the definition itself), loads and
  * operand reads checked.
  * Errors: PACK_EINVAL (bad arguments, or a violation: pack_last_error names launch and tile), PACK_ESHAPE, PACK_ENOMEM. */
 pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec* models, int32_t K, int32_t input_mode,

@@ -206,7 +206,7 @@ PACK_DEV void rc_block_coords(int b, int& kq, int& rv) {
     kq = (rest / G::RPV) * KQ_LO + lo;
 }
 
-// the element-by-element gather of the kernels for unaligned shapes (device only)
+// the element-by-element gather of the kernels for sizes the aligned ones do not address (device only)
 template <int MODE, typename T, bool IS_A, int BR, int BK, bool VEC>
 PACK_DEV void fetch_tile(const GemmProb& p, int row0, int k0, int kend, u32x4_t (&regs)[TileGeom<T, BR, BK>::NREG]);
 

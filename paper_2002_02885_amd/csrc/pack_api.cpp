@@ -184,7 +184,7 @@ namespace {
 
 // The tensors of a member's public blob and where they lie in the arenas.  linear: rows as they are.  conv: blob
 // [Cout][Cin][3][3], arena [Cout][3][3][Cin].  The channels of a pixel or tap are padded to whole groups of 8 in the
-// arena (rows to `kp` for im2col convolutions); the padding stays zero.
+// arena (rows to `kp` for im2col convolutions); the padding stays zero, since the products store its gradient as zero.
 std::vector<BlobSeg> blob_segments(const ModelInfo& m) {
     std::vector<BlobSeg> segs;
     int tensor = 0;
@@ -553,14 +553,13 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
     std::vector<GemmProb> all_probs = all_probs_in;
     if (std::getenv("PACK_GENERAL_TAIL"))
         for (GemmProb& g : all_probs) g.flags |= F_GENERAL_TAIL;
-    // problems whose operands are not aligned for 16-byte loads go to the scalar-gather kernel
+    // problems the aligned kernels do not address go to the scalar-gather kernel
     std::vector<GemmProb> probs, scalar;
     for (const GemmProb& g : all_probs) {
         bool vec = (g.flags & F_VEC_A) && (g.flags & F_VEC_B);
         if (vec) {
             // The aligned kernels address an operand with 32-bit byte offsets inside a 2 GB window:
-            // larger operands (and weight-gradient convolutions over images narrower than the four
-            // pixels a load block covers) take the scalar kernel.
+            // larger operands take the scalar kernel.
             const double esz = p->bf16 ? 2.0 : 4.0;
             double ea = 0, eb = 0;
             switch (mode) {
@@ -577,7 +576,6 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
                 default:
                     ea = (double)g.Kd * g.lda;
                     eb = (double)g.Kd / (g.Ho * g.Wo) * g.H * g.W * g.Cin + (g.W + 1) * g.Cin;
-                    if (g.Wo < 4 && !(g.flags & F_GATHER)) vec = false;
                     break;
             }
             if (ea * esz >= 2.0e9 || eb * esz >= 2.0e9) vec = false;
@@ -1123,7 +1121,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
     }
     ws_need = ws_off;
     p->workspace_unpadded = ws_unpadded;
-    // a grid drains best when its slowest tiles start first: unaligned problems (scalar gather),
+    // a grid drains best when its slowest tiles start first: problems of the scalar gather,
     // then long reductions, then large outputs
     auto slow_first = [](const GemmProb& a, const GemmProb& b) {
         const bool va = (a.flags & F_VEC_A) && (a.flags & F_VEC_B), vb = (b.flags & F_VEC_A) && (b.flags & F_VEC_B);

@@ -55,7 +55,7 @@ __device__ __forceinline__ u32x4_t load_vec(const GemmProb& p, int r, int k, int
     return v;
 }
 
-// gathers V scalars into one 16-byte register group (slow path for unaligned shapes)
+// gathers V scalars into one 16-byte register group (slow path)
 template <int MODE, typename T, bool IS_A, bool KC>
 __device__ __forceinline__ u32x4_t fetch_scalars(const GemmProb& p, int r, int k, int kend) {
     constexpr int V = ET<T>::V;
@@ -1223,7 +1223,7 @@ template <int MODE>
 using LrArg = typename std::conditional<MODE == LIN_DW || MODE == CONV_DW, LrTable, NoLr>::type;
 
 // VEC = true: every problem of the launch has both operands aligned for 16-byte loads (the planner
-// sorts problems into launches by that); VEC = false: the element-by-element gather for any shape.
+// sorts problems into launches by that); VEC = false: the element-by-element gather for any size.
 // They are separate kernels because the gather needs many more registers, which would halve the
 // occupancy of the aligned path if both lived in one kernel.
 template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false>

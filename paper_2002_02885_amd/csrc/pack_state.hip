@@ -5,7 +5,7 @@
 // A checkpoint crosses PCIe once and is laid out on the way: the export kernel gathers arena elements in blob
 // order and writes them straight into pinned host memory, the import kernel reads pinned host memory and scatters
 // into the arena (and its bf16 operand copy).  What bounds both is the link: 4-byte gathers at 52 GB/s are 13 G
-// elements/s, a few hundred gathers per compute unit and microsecond, so the index arithmetic is free and no device
+// elements/s, some fifty gathers per compute unit and microsecond, so the index arithmetic is free and no device
 // staging copy is needed.  Measured, 16 MB: kernel stores to pinned memory 52.7 GB/s, the DMA engine 55.7 GB/s.
 #include "pack_internal.h"
 #include "pack_device.h"

@@ -23,7 +23,7 @@ namespace packk {
 namespace {
 
 constexpr size_t CHUNK_BYTES = (size_t)1 << 19;
-constexpr int MAX_THREADS = 8, SLOTS = 2 * MAX_THREADS;    // two chunks in flight per thread
+constexpr int MAX_THREADS = 8, SLOTS = 2 * MAX_THREADS;    // helpers; per helper a chunk being copied and one on the link
 
 struct Ring {
     int device = -1;

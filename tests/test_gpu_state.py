@@ -13,8 +13,10 @@ def _pack(models, in_shape, dtype="f32", seed=0):
     return binding.Pack(2, in_shape, dtype, models, seed=seed)
 
 
-# a linear layer alone has D * C + C parameters; a transfer moves chunks of 2^18 floats, two per thread and four threads
-@pytest.mark.parametrize("D,C", [(1, 1), (5, 3), (87381, 3), (131071, 2), (131072, 2), (524287, 2), (1048573, 2), (1300001, 2)])
+# a linear layer alone has D * C + C parameters; a transfer moves chunks of 2^17 floats through a ring of sixteen: around one
+# chunk, around one ring and beyond two of them, and sizes that end inside a chunk
+@pytest.mark.parametrize("D,C", [(131070, 1), (131071, 1), (131072, 1), (2097150, 1), (2097151, 1), (2097152, 1), (1400001, 3),
+                                 (1, 1), (5, 3), (87381, 3), (131071, 2), (131072, 2), (524287, 2), (1048573, 2), (1300001, 2)])
 def test_blob_round_trip_around_chunk_boundaries(D, C):
     pk = _pack([[("linear", C)]], (1, 1, D))
     blob = np.random.default_rng(D).standard_normal(D * C + C).astype(np.float32)

@@ -1581,6 +1581,13 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
         ++walked;
         const GemmProb* probs = (const GemmProb*)(p->desc_host.data() + L.desc_off);
         const TileRef* tiles = (const TileRef*)(p->desc_host.data() + L.map_off);
+        // the tails store whole vectors: weights in rows of whole groups of 8, everything but the logits too
+        for (int t = 0; t < L.n && err.empty(); ++t) {
+            if (tiles[t].prob < 0) continue;
+            const GemmProb& g = probs[tiles[t].prob];
+            const bool whole = g.ldc % 8 == 0 && stored_cols(g) % 8 == 0 && stored_cols(g) <= g.ldc;
+            if (!whole && (L.mode == LIN_DW || L.mode == CONV_DW || g.ldc % 8 == 0)) err = "launch " + std::to_string(li) + ": the rows of problem " + std::to_string(tiles[t].prob) + " are no whole vectors";
+        }
         if (staged) {
             // aligned staged-tile kernels: the fetchers themselves, run on the CPU, against the definition of the operands
             const int BMc = GEMM_TILE_M[L.tile_cfg], BNc = GEMM_TILE_N[L.tile_cfg];

@@ -224,12 +224,6 @@ struct StageCount {   // register stages of prefetch per tile shape (bounded by 
     static constexpr int value = (BKM > 1 || !VEC) ? 2 : ((BM * BN >= 128 * 128) ? 2 : ((BM * BN >= 128 * 64) ? 3 : 4));
 };
 
-__device__ __forceinline__ void update_one(const GemmProb& p, size_t off, float g, float lr) {
-    const float w = sgd_apply(p.upd_w[off], g, lr);
-    p.upd_w[off] = w;
-    if (p.upd_shadow) ((bf16_t*)p.upd_shadow)[off] = ET<bf16_t>::from_f(w);
-}
-
 // Gradient that reaches output row `row` of an input-gradient problem through the block's shortcut
 // (element offset into p.sc of column 0), or -1 if none does.  Identity: same pixel.  Subsampling
 // shortcut: only pixels with even coordinates, from the pixel at half the coordinates; a problem
@@ -320,7 +314,6 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
         const int lc = (threadIdx.x % GROUPS) * 8, lr0 = threadIdx.x / GROUPS;
         const int col = col0 + lc;
         const int nreal = p.Q - col;                                  // columns of the thread's eight that exist
-        const bool full = col + 8 <= stored_cols(p);
         typedef typename std::conditional<sizeof(T) == 2, u32x4_t, f32x4_t>::type ev_t;   // 8 bf16 or 4 floats
         constexpr int EV = (sizeof(T) == 2) ? 1 : 2;   // vectors per 8 elements
         const bool col_ok = col < p.Q;   // (a thread beyond the last column still walks the loop: `staged` may hold barriers)
@@ -465,7 +458,7 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
                     off[n] = out_row_base(p, live[n] ? row : row0) + col;
                     const T* ap = nullptr;
                     const T* op = nullptr;
-                    if (live[n] && full) {
+                    if (live[n]) {
                         if constexpr (IS_FWD) {
                             if (p.flags & F_RES_ID) {
                                 ap = (const T*)p.aux + off[n];
@@ -510,14 +503,6 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
                         const f32x4_t s1 = *reinterpret_cast<const f32x4_t*>(&stage[lr][lc + 4]);
                         v[0] = s0.x; v[1] = s0.y; v[2] = s0.z; v[3] = s0.w;
                         v[4] = s1.x; v[5] = s1.y; v[6] = s1.z; v[7] = s1.w;
-                    }
-                    if (!full) {   // ragged right edge: element by element
-                        for (int e = 0; e < 8 && col + e < p.Q; ++e) {
-                            const float r = finish(v[e], row, col + e, off[n] + e);
-                            if (out_f32) cf[off[n] + e] = r;
-                            else ((T*)p.C)[off[n] + e] = ET<T>::from_f(r);
-                        }
-                        continue;
                     }
                     float ax[8], old[8];
                     if constexpr (sizeof(T) == 2) {
@@ -652,8 +637,9 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     // come from L2, then queue behind weights that come from HBM.)
     constexpr int DW_G = BN / 4, DW_NIT = BM * DW_G / 256, DW_RSTEP = 256 / DW_G;
     const int dw_lc = (threadIdx.x % DW_G) * 4, dw_lr0 = threadIdx.x / DW_G;
+    // (rows of weights are stored in whole groups of 8: no thread's four are cut off)
     const int dw_cols = stored_cols(p);
-    const bool dw_full = vec_out && (col0 + dw_lc + 4 <= dw_cols);
+    const bool dw_live = col0 + dw_lc < dw_cols;
     // columns of the thread's four that are padding, between real channels or at the end of a row: they are stored as
     // zeros whatever the operands hold (a reduction of split products reads them like any other)
     unsigned dw_pad = 0;
@@ -882,7 +868,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     float(*stage)[SLD] = reinterpret_cast<float(*)[SLD]>(As_);
     // the weights of the tile: their round trip runs under the staging of the accumulators
     if constexpr (IS_DW) {
-        if (upd && dw_full) {
+        if (upd && dw_live) {
 #pragma unroll
             for (int n = 0; n < DW_NIT; ++n) {
                 const int row = row0 + dw_lr0 + n * DW_RSTEP;
@@ -908,47 +894,29 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
                             stage[a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)][wn * (BN / 2) + b * 32 + (lane & 31)] = acc[a][b][e];
             }
             lds_barrier();
-            if (vec_out) {
-                if (col < dw_cols) {
+            if (dw_live) {
 #pragma unroll
-                    for (int n = half * (DW_NIT / 2); n < (half + 1) * (DW_NIT / 2); ++n) {
-                        const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;   // lr in [half * BM/2, (half + 1) * BM/2)
-                        if (row >= p.R) continue;
-                        const size_t off = (size_t)row * p.ldc + col;
-                        f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr - half * (BM / 2)][dw_lc]);
-                        if (dw_pad) {
+                for (int n = half * (DW_NIT / 2); n < (half + 1) * (DW_NIT / 2); ++n) {
+                    const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;   // lr in [half * BM/2, (half + 1) * BM/2)
+                    if (row >= p.R) continue;
+                    const size_t off = (size_t)row * p.ldc + col;
+                    f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr - half * (BM / 2)][dw_lc]);
+                    if (dw_pad) {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if ((dw_pad >> e) & 1u) g[e] = 0.f;
-                        }
-                        if (!dw_full) {
-                            for (int e = 0; e < 4 && col + e < p.Q; ++e) {
-                                if (upd) update_one(p, off + e, g[e], lrk);
-                                if (keep_g) gf[off + e] = g[e];
-                            }
-                            continue;
-                        }
-                        if (upd) {
-                            f32x4_t w;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) w[e] = sgd_apply(dw_w[n][e], g[e], lrk);
-                            *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w;
-                            if (p.upd_shadow) {
-                                typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
-                                *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[0], w[1]), pack2bf(w[2], w[3])};
-                            }
-                        }
-                        if (keep_g) *reinterpret_cast<f32x4_t*>(gf + off) = g;
+                        for (int e = 0; e < 4; ++e)
+                            if ((dw_pad >> e) & 1u) g[e] = 0.f;
                     }
-                }
-            } else {
-                for (int idx = threadIdx.x; idx < (BM / 2) * BN; idx += 256) {
-                    const int lr = idx / BN, lc = idx % BN;
-                    const int row = row0 + half * (BM / 2) + lr, c2 = col0 + lc;
-                    if (row >= p.R || c2 >= p.Q) continue;
-                    const size_t off = (size_t)row * p.ldc + c2;
-                    if (upd) update_one(p, off, stage[lr][lc], lrk);
-                    if (keep_g) gf[off] = stage[lr][lc];
+                    if (upd) {
+                        f32x4_t w;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w[e] = sgd_apply(dw_w[n][e], g[e], lrk);
+                        *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w;
+                        if (p.upd_shadow) {
+                            typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+                            *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[0], w[1]), pack2bf(w[2], w[3])};
+                        }
+                    }
+                    if (keep_g) *reinterpret_cast<f32x4_t*>(gf + off) = g;
                 }
             }
         }
@@ -969,48 +937,30 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
 
     if constexpr (IS_DW) {
         float* const gf = (float*)p.C + (size_t)tr.ks * p.split_stride;
-        if (vec_out) {
-            const int col = col0 + dw_lc;
-            if (col < dw_cols) {
+        const int col = col0 + dw_lc;
+        if (dw_live) {
 #pragma unroll
-                for (int n = 0; n < DW_NIT; ++n) {
-                    const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;
-                    if (row >= p.R) continue;
-                    const size_t off = (size_t)row * p.ldc + col;
-                    f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr][dw_lc]);
-                    if (dw_pad) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if ((dw_pad >> e) & 1u) g[e] = 0.f;
-                    }
-                    if (!dw_full) {   // ragged right edge: element by element
-                        for (int e = 0; e < 4 && col + e < p.Q; ++e) {
-                            if (upd) update_one(p, off + e, g[e], lrk);
-                            if (keep_g) gf[off + e] = g[e];
-                        }
-                        continue;
-                    }
-                    if (upd) {
-                        f32x4_t w;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) w[e] = sgd_apply(dw_w[n][e], g[e], lrk);
-                        *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w;
-                        if (p.upd_shadow) {
-                            typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
-                            *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[0], w[1]), pack2bf(w[2], w[3])};
-                        }
-                    }
-                    if (keep_g) *reinterpret_cast<f32x4_t*>(gf + off) = g;
-                }
-            }
-        } else {
-            for (int idx = threadIdx.x; idx < BM * BN; idx += 256) {
-                const int lr = idx / BN, lc = idx % BN;
-                const int row = row0 + lr, col = col0 + lc;
-                if (row >= p.R || col >= p.Q) continue;
+            for (int n = 0; n < DW_NIT; ++n) {
+                const int lr = dw_lr0 + n * DW_RSTEP, row = row0 + lr;
+                if (row >= p.R) continue;
                 const size_t off = (size_t)row * p.ldc + col;
-                if (upd) update_one(p, off, stage[lr][lc], lrk);
-                if (keep_g) gf[off] = stage[lr][lc];
+                f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr][dw_lc]);
+                if (dw_pad) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if ((dw_pad >> e) & 1u) g[e] = 0.f;
+                }
+                if (upd) {
+                    f32x4_t w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = sgd_apply(dw_w[n][e], g[e], lrk);
+                    *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w;
+                    if (p.upd_shadow) {
+                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+                        *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[0], w[1]), pack2bf(w[2], w[3])};
+                    }
+                }
+                if (keep_g) *reinterpret_cast<f32x4_t*>(gf + off) = g;
             }
         }
         return;

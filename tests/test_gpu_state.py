@@ -1,4 +1,4 @@
-"""Member state in and out: the blob layout through the chunked transfer (sizes around its chunk and thread
+"""Member state in and out: the blob layout through the chunked transfer (sizes around its chunk and ring
 boundaries) and the seeded initial weights against their definition, value for value."""
 import numpy as np
 import pytest

@@ -1519,6 +1519,12 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
         release(p);
         return fail(PACK_EDEVICE, "no HIP device is current");
     }
+    // A stream that cannot be waited for (one that is being captured) is refused before anything is allocated or enqueued: a
+    // failure at the end would free buffers that the work enqueued in between still names.
+    if (const hipError_t e = hipStreamSynchronize(p->stream); e != hipSuccess) {
+        release(p);
+        return fail(PACK_EDEVICE, std::string("the pack's stream: ") + hipGetErrorString(e));
+    }
     pack_status s = build_device(p);
     if (s != PACK_OK) { release(p); return s; }
     for (int k = 0; k < K; ++k) {

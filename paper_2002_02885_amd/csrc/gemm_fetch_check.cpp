@@ -35,6 +35,7 @@ template <> struct ET<bf16_t> { static constexpr int V = 8, BK = 64; };
 }  // namespace packk
 
 #include "gemm_fetch.h"
+#include "gemm_slim_check.h"
 
 namespace packk {
 namespace {
@@ -190,13 +191,14 @@ std::string walk_mode(int mode, int bm, int bn, const GemmProb& p, const TileRef
 
 }  // namespace
 
-// One tile of a launch on the aligned staged-tile kernels (tile shape bm x bn).  On success a_lo .. b_hi hold
+// One tile of a launch on the aligned staged-tile kernels, or of the slim form (tile shape bm x bn).  On success a_lo .. b_hi hold
 // the range of addresses the tile's real loads of each operand touched (lo > hi: none), for the caller to hold
 // against its allocations.  Returns an empty string or what is wrong.
 std::string gemm_fetch_walk(bool bf16, int mode, int bm, int bn, const GemmProb& p, const TileRef& tr, unsigned long long* a_lo,
                             unsigned long long* a_hi, unsigned long long* b_lo, unsigned long long* b_hi, long long* loads) {
     Span sa, sb;
-    const std::string err = bf16 ? walk_mode<bf16_t>(mode, bm, bn, p, tr, sa, sb, loads) : walk_mode<float>(mode, bm, bn, p, tr, sa, sb, loads);
+    const std::string err = (p.flags & F_SLIM) ? slim_check::walk(bf16, mode, bm, p, tr, sa, sb, loads) :
+                            bf16 ? walk_mode<bf16_t>(mode, bm, bn, p, tr, sa, sb, loads) : walk_mode<float>(mode, bm, bn, p, tr, sa, sb, loads);
     *a_lo = sa.lo; *a_hi = sa.hi; *b_lo = sb.lo; *b_hi = sb.hi;
     return err;
 }

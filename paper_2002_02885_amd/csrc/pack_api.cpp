@@ -8,6 +8,7 @@
 // Members therefore never exchange data, which is what makes packing lossless (Section 3.1).
 #include "../../include/pack.h"
 #include "pack_internal.h"
+#include "gemm_slim.h"
 
 #include <algorithm>
 #include <cmath>
@@ -372,6 +373,10 @@ constexpr size_t XCD_RUN = 8;
 // 256-tile launches of config 2 lose 15 %).
 constexpr int LEAN64_MAX_CHUNKS = 18;
 constexpr size_t LEAN64_MIN_TILES = 1024;
+// The slim form's 64 x 64 tiles, one workgroup per compute unit at a time, pay once the launch has about as many of them as
+// there are compute units (1024 tiles of 32 x 32 are 256: 34 -> 25 us over 3072 indices, 9.0 -> 8.0 over 512; 256 are 64:
+// 8.0 -> 13).
+constexpr size_t SLIM64_MIN_TILES32 = 768;
 std::vector<TileRef> xcd_order(const std::vector<TileOrder>& logical) {
     const size_t n = align_up(std::max<size_t>(logical.size(), 1), 8 * XCD_RUN);
     std::vector<TileRef> out(n, TileRef{-1, 0, 0, 0});
@@ -585,7 +590,7 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
             probs.push_back(g);
         } else {
             GemmProb gs = g;
-            gs.flags &= ~(F_VEC_A | F_VEC_B);
+            gs.flags &= ~(F_VEC_A | F_VEC_B | F_SLIM);
             scalar.push_back(gs);
         }
     }
@@ -603,6 +608,19 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
         }
         for (int c = 0; c < 3; ++c)
             if (!halo[c].empty()) emit_gemm_launch(p, db, mode, GEMM_CFG_HALO_S1 + c, halo[c]);
+        probs.swap(rest);
+    }
+    if ((mode == LIN_FWD || mode == LIN_DX) && !std::getenv("PACK_MIN_TILES")) {
+        // (PACK_MIN_TILES asks for staged tiles)
+        // products with few outputs: the reduction shared by the waves of a workgroup (whether a problem does: slim_ok).
+        // The tile is the launch's choice, since the order of a sum does not depend on it: 32 x 32 spreads a launch over the
+        // compute units, 64 x 64 reads half as much per product, and is built for the only products that are bound by that.
+        std::vector<GemmProb> slim, rest;
+        for (const GemmProb& g : probs) ((g.flags & F_SLIM) ? slim : rest).push_back(g);
+        if (!slim.empty()) {
+            const bool big = p->bf16 && mode == LIN_FWD && count_tiles(slim, GEMM_CFG_SLIM32) >= SLIM64_MIN_TILES32;
+            emit_gemm_launch(p, db, mode, big ? GEMM_CFG_SLIM64 : GEMM_CFG_SLIM32, slim);
+        }
         probs.swap(rest);
     }
     if ((mode == CONV_FWD || mode == CONV_DX) && !std::getenv("PACK_NO_HALO_ROWS")) {
@@ -746,6 +764,14 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
     auto x_off = [&](const ModelInfo& m) -> long long {
         return p->own_input ? (long long)(&m - p->models.data()) * block_bytes : 0;
     };
+    // Products that take the slim form.  Single-precision members under Adam do not: the form adds up in another order, and
+    // Adam, which divides by the root of the second moment, lifts the last bits of a small gradient to the size of an update,
+    // so their results would part from those of the staged tiles (1 % of the weights' norm after 200 steps of three
+    // 2048-wide members; 1e-6 under the other optimisers).
+    auto slim_flag = [&](const ModelInfo& m, const GemmProb& g) {
+        const bool keeps_order = !bf && p->opt[&m - p->models.data()].kind == PACK_OPT_ADAM;
+        return !keeps_order && slim_ok(g) ? F_SLIM : 0;
+    };
     auto weight_ptr = [&](const NodeInfo& nd) -> const void* {
         return bf ? (const void*)((const char*)p->shadow + nd.w_off * 2) : (const void*)(p->master + nd.w_off);
     };
@@ -808,6 +834,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 g.lda = row_pitch(p, m, nd); g.ldb = nd.ldw; g.ldc = to.pitch;
                 g.flags |= F_VEC_A | F_VEC_B;
                 g.ksplit = g.Kd;
+                g.flags |= slim_flag(m, g);
                 lin.push_back(g);
             } else if (nd.kp) {
                 // first convolution over the shared im2col buffer: a dense product, rows = pixels
@@ -820,6 +847,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                 g.lda = nd.kp; g.ldb = nd.kp; g.ldc = to.pitch;
                 g.flags |= F_VEC_A | F_VEC_B;
                 g.ksplit = g.Kd;
+                g.flags |= slim_flag(m, g);
                 lin.push_back(g);
             } else {
                 g.H = ti.h; g.W = ti.w; g.Cin = nd.cpad; g.Ho = to.h; g.Wo = to.w; g.Cout = to.pitch; g.stride = nd.stride;
@@ -1046,6 +1074,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.flags |= F_VEC_A | F_VEC_B | F_PAD_OUT;
                     if (g.Q > nd.fan_in) { g.pad_c = nd.cpad; g.pad_real = ti.c; }
                     g.ksplit = g.Kd;
+                    g.flags |= slim_flag(m, g);
                     lin_dx.push_back(g);
                 } else {
                     g.H = ti.h; g.W = ti.w; g.Cin = ti.pitch; g.Ho = to.h; g.Wo = to.w; g.Cout = to.pitch; g.stride = nd.stride;
@@ -1381,6 +1410,46 @@ pack_status build_device(pack_ctx* p) {
         free_device(p);
         return fail(PACK_EDEVICE, std::string("initial upload: ") + hipGetErrorString(e));
     }
+    return PACK_OK;
+}
+
+// Plans the launches of a pack again whose members' products changed their form: the buffers stay, the tables are new.  The
+// stream is idle.  On failure the pack is what it was.
+pack_status replan(pack_ctx* p) {
+    const std::vector<Launch> plan = p->plan;
+    const size_t ce_off = p->ce_desc_off, head_off = p->head_desc_off;
+    std::vector<size_t> segs_off;
+    for (const ModelInfo& m : p->models) segs_off.push_back(m.segs_off);
+    const size_t bytes = p->device_bytes;
+    p->plan.clear();
+    DescBuilder db;
+    size_t need = 0;
+    build_plan(p, db, need);
+    for (ModelInfo& m : p->models) {
+        const std::vector<BlobSeg> segs = blob_segments(m);
+        m.segs_off = db.add(segs.data(), segs.size() * sizeof(BlobSeg));
+    }
+    char* desc = nullptr;
+    pack_status s = need == p->workspace_bytes ? dev_alloc((void**)&desc, db.bytes.size(), p) : fail(PACK_EINVAL, "internal: the workspace changed");
+    if (s == PACK_OK)
+        if (const hipError_t e = hipMemcpy(desc, db.bytes.data(), db.bytes.size(), hipMemcpyHostToDevice); e != hipSuccess)
+            s = fail(PACK_EDEVICE, std::string("launch tables: ") + hipGetErrorString(e));
+    if (s != PACK_OK) {
+        if (desc) (void)hipFree(desc);
+        p->plan = plan;
+        p->ce_desc_off = ce_off;
+        p->head_desc_off = head_off;
+        for (size_t k = 0; k < segs_off.size(); ++k) p->models[k].segs_off = segs_off[k];
+        p->device_bytes = bytes;
+        return s;
+    }
+    (void)hipFree(p->desc);
+    p->desc = desc;
+    p->device_bytes = bytes - align_up(p->desc_bytes, 256) + align_up(db.bytes.size(), 256);
+    p->desc_bytes = db.bytes.size();
+    for (auto& t : p->stamps) { (void)hipEventDestroy(t.t0); (void)hipEventDestroy(t.t1); }   // (launch numbers have changed)
+    p->stamps.clear();
+    p->profiling = false;
     return PACK_OK;
 }
 
@@ -2012,6 +2081,14 @@ pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec) 
             return st;
         }
     } else if (p->opt_params) {
+        if (!p->bf16 && (old_spec.kind == PACK_OPT_ADAM) != (o.kind == PACK_OPT_ADAM)) {   // the form of the member's dense products (slim_flag)
+            pack_status st = replan(p);
+            if (st != PACK_OK) {
+                p->opt[k] = old_spec;
+                p->opt_t[k] = old_t;
+                return st;
+            }
+        }
         std::vector<OptStatic> par(p->K);
         for (int i = 0; i < p->K; ++i)
             par[i] = OptStatic{p->opt[i].kind, p->opt[i].mu, p->opt[i].beta1, p->opt[i].beta2, p->opt[i].eps};

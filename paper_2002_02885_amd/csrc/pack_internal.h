@@ -50,6 +50,7 @@ enum GemmFlags : int {
                               // that compares it with the form whole tiles of the plain cases take)
     F_GATHER = 262144, // convolution whose chunks of the reduction may straddle taps, images or rows of any width:
                        // operands come through the general gather (GEMM_CFG_GATHER0 ..)
+    F_SLIM = 1048576,  // dense forward product or input gradient in the slim form (GEMM_CFG_SLIM32, GEMM_CFG_SLIM64)
     F_PAD_OUT = 524288 // output rows are stored in whole groups of 8 columns (ldc a multiple of 8, at least Q rounded
                        // up): the columns from Q on hold zeros and are written as such
 };
@@ -220,6 +221,8 @@ int conv_dw_halo_cfg(bool bf16, const GemmProb& p);
 // the halo configuration (GEMM_CFG_ROWS*) a stride-1 convolution forward (mode CONV_FWD) or input-gradient (CONV_DX)
 // problem can take, or -1
 int conv_rows_halo_cfg(bool bf16, int mode, const GemmProb& p);
+// slim form of dense forward products and input gradients (pack_slim.hip): every problem passes slim_ok
+hipError_t launch_slim(int mode, bool bf16, int tile_cfg, const GemmProb* probs_dev, const TileRef* tiles_dev, int n_tiles, const void* x_dev, hipStream_t st);
 hipError_t launch_reduce(const ReduceProb* probs_dev, const int2* map_dev, int n_blocks, const char* ws, const LrTable& lr, hipStream_t st);
 // The library's own scratch array (file-scope device memory, STATIC_SCRATCH_BYTES long, one copy per GPU):
 // its address on the current device.  For the entry point that may not allocate.
@@ -270,8 +273,8 @@ hipError_t launch_gather_rows(const void* data, const int32_t* labels_all, const
 // 6, 7: the halo form of the convolution weight gradient (stride 1, stride 2): a tile is 64 output channels
 // x 64 input channels x all nine taps, i.e. 64 x 576 of the [Cout][9 * Cin] gradient
 // 8: the same with 32 input channels per tile (layers whose input channels are a multiple of 32 only; stride 1)
-constexpr int GEMM_TILE_M[14] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64};
-constexpr int GEMM_TILE_N[14] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64};
+constexpr int GEMM_TILE_M[16] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64};
+constexpr int GEMM_TILE_N[16] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64};
 constexpr int GEMM_CFG_SCALAR = 3;
 constexpr int GEMM_CFG_LEAN = 4;     // weight gradients, 128 x 128, short reductions
 constexpr int GEMM_CFG_LEAN64 = 5;   // forward / input gradients, 128 x 64, short reductions
@@ -284,6 +287,9 @@ constexpr int GEMM_CFG_ROWS32 = 10;  // likewise, 256 pixels x 32 columns
 inline bool is_rows_cfg(int cfg) { return cfg == GEMM_CFG_ROWS64 || cfg == GEMM_CFG_ROWS32; }
 constexpr int GEMM_CFG_GATHER0 = 11; // 11..13: configurations 0..2 with the general gather (convolutions of any channel count and map)
 inline bool is_gather_cfg(int cfg) { return cfg >= GEMM_CFG_GATHER0 && cfg < GEMM_CFG_GATHER0 + 3; }
+constexpr int GEMM_CFG_SLIM32 = 14;  // dense products with few outputs, reduction dealt over the waves, 32 x 32 tiles
+constexpr int GEMM_CFG_SLIM64 = 15;  // likewise, 64 x 64 tiles (bfloat16 forward products)
+inline bool is_slim_cfg(int cfg) { return cfg == GEMM_CFG_SLIM32 || cfg == GEMM_CFG_SLIM64; }
 constexpr int ELEMWISE_PER_BLOCK = 2048;   // elements one block of the elementwise kernels covers
 constexpr int SGD_PER_BLOCK = 2048;        // parameters one block of the update kernel covers (measured best of 1024..8192)
 

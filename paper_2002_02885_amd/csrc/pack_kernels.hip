@@ -1267,6 +1267,7 @@ hipError_t launch_gemm(int mode, bool bf16, int tile_cfg, const GemmProb* probs,
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
+    if (is_slim_cfg(tile_cfg)) return launch_slim(mode, bf16, tile_cfg, probs, tiles, n, x, st);
     if (mode == CONV_DW && is_halo_cfg(tile_cfg)) return launch_conv_dw_halo(bf16, tile_cfg, probs, tiles, n, x, ws, lr, st);
     switch (mode) {
         case LIN_FWD: return launch_gemm_mode<LIN_FWD>(bf16, tile_cfg, probs, tiles, n, x, ws, lr, st);

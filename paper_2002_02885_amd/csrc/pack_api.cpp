@@ -158,8 +158,8 @@ struct pack_ctx {
     void* zeros = nullptr;       // 256 bytes of zeros inside the slab (never written)
     std::vector<Im2colProb> im2col;   // shared-input loaders, one per first-layer stride in use
     bool own_input = false;           // members read their own block of the step's input instead of one shared batch
-    bool fused = false;               // all members use plain SGD: the update is applied in the weight-gradient kernels
-    bool keep_grads = false;          // fused packs: store the gradients as well (pack_read_grads)
+    bool fused = false;               // the update is applied in the weight-gradient kernels
+    bool keep_grads = false;          // packs of plain SGD, fused: store the gradients as well (pack_read_grads)
     size_t head_desc_off = 0;         // problem table of the classifier-head launch
     int n_heads = 0;
     size_t ce_desc_off = 0;           // problem table of the loss launch
@@ -542,7 +542,8 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
         if (mode == LIN_DW || mode == CONV_DW) {
             const double splits = std::max(1, (g.Kd + g.ksplit - 1) / g.ksplit);
             if (!(g.flags & F_UPDATE) || (g.flags & F_KEEP_G)) L.bytes += out * 4.0 * splits;      // gradient (or partials) written
-            if (g.flags & F_UPDATE) L.bytes += out * (8.0 + (g.upd_shadow ? 2.0 : 0.0));            // W read + written, bf16 copy written
+            if (g.flags & F_UPDATE)                                                                 // W and its state read + written, bf16 copy written
+                L.bytes += out * (8.0 * (1 + (p->opt[g.member].kind != PACK_OPT_SGD) + (p->opt[g.member].kind == PACK_OPT_ADAM)) + (g.upd_shadow ? 2.0 : 0.0));
         }
     }
     for (const auto& kv : shared_a) L.bytes += kv.second * esz;
@@ -653,6 +654,18 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
 // problems with aligned operands onto the staged-tile kernels
 void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vector<GemmProb>& probs, bool general) {
     if (probs.empty()) return;
+    if (mode == LIN_DW && p->any_opt && p->fused) {
+        // Updates by an optimiser with state are bound by the streams of weights and state, and smaller tiles keep more of them in
+        // flight (gemm_body, OPT); reductions of more than eight chunks keep the pipelined tiles, as those of plain SGD do.
+        std::vector<GemmProb> opt, rest;
+        const int chunk = p->bf16 ? 64 : 32;
+        for (const GemmProb& g : probs) ((std::min(g.Kd, g.ksplit) + chunk - 1) / chunk <= 8 && g.Kd <= g.ksplit ? opt : rest).push_back(g);
+        if (!opt.empty()) {
+            emit_gemm_launch(p, db, mode, GEMM_CFG_LEAN_OPT, opt);
+            if (!rest.empty()) add_tiled_launches(p, db, mode, rest, general);
+            return;
+        }
+    }
     // The tile shape only partitions the output; the summation order of an element does not
     // depend on it, so a member's bits do not depend on who else is in the launch.  Each problem
     // prefers the shape that multiplies the fewest padding elements (a 64-channel layer wastes
@@ -679,7 +692,7 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
         if (work[c] > work[main_cfg]) main_cfg = c;
     // weight gradients whose reduction is at most a few chunks long take the lean form of the
     // 128 x 128 kernel (more tiles resident per compute unit)
-    const bool lean_ok = (mode == LIN_DW || mode == CONV_DW);
+    const bool lean_ok = (mode == LIN_DW && !(p->any_opt && p->fused)) || mode == CONV_DW;   // (with other optimisers: above)
     // forward products and input gradients on 128 x 64 tiles have a lean form too (one register stage,
     // one operand buffer, four workgroups per compute unit); PACK_LEAN64_CHUNKS sets the longest
     // reduction, in chunks, that takes it (0: never; a measuring aid)
@@ -936,6 +949,8 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
             }
         add_mapped_launch(p, db, L_WTRANS, tps, tp_blocks);
     }
+    // (packs with other optimisers than SGD always store their gradients: pack_read_grads asks nothing of them)
+    const bool keeps_g = p->keep_grads || p->any_opt;
     std::vector<ReduceProb> dw_red;
     std::vector<int> dw_red_blocks;
     std::vector<GemmProb> lin_dw, conv_dw;
@@ -1031,7 +1046,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.split_stride = (long long)nd.w_arena;
                     ReduceProb r{};
                     r.in = (const float*)(uintptr_t)ws_off; r.out = dst; r.stride = (long long)nd.w_arena; r.n = (int)nd.w_arena; r.S = S;
-                    if (p->fused) { r.upd_w = p->master + nd.w_off; r.upd_shadow = shadow_w; r.member = member; r.keep_g = p->keep_grads; }
+                    if (p->fused) { r.upd_w = p->master + nd.w_off; r.upd_shadow = shadow_w; r.member = member; r.keep_g = keeps_g; }
                     dw_red.push_back(r);
                     dw_red_blocks.push_back((int)((nd.w_arena + 1023) / 1024));
                     ws_off += align_up((size_t)S * nd.w_arena * 4, 256);
@@ -1039,7 +1054,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.dbias = (float*)(uintptr_t)ws_off;
                     ReduceProb rb{};
                     rb.in = (const float*)(uintptr_t)ws_off; rb.out = p->grad + nd.b_off; rb.stride = nd.out; rb.n = nd.out; rb.S = S;
-                    if (p->fused) { rb.upd_w = p->master + nd.b_off; rb.member = member; rb.keep_g = p->keep_grads; }
+                    if (p->fused) { rb.upd_w = p->master + nd.b_off; rb.member = member; rb.keep_g = keeps_g; }
                     dw_red.push_back(rb);
                     dw_red_blocks.push_back((nd.out + 1023) / 1024);
                     ws_off += align_up((size_t)S * nd.out * 4, 256);
@@ -1047,8 +1062,20 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
                     g.ksplit = std::max(g.Kd, 1);
                     g.C = dst;
                     g.dbias = p->grad + nd.b_off;
-                    if (p->fused) {
-                        g.flags |= F_UPDATE | (p->keep_grads ? F_KEEP_G : 0);
+                    if (p->fused && p->any_opt && !dense) {
+                        // (the convolutions' kernels apply SGD only: the reduction launch applies the optimiser to a gradient that
+                        // is in place already)
+                        for (int part = 0; part < 2; ++part) {
+                            ReduceProb r{};
+                            r.in = r.out = part ? p->grad + nd.b_off : dst;
+                            r.n = part ? nd.out : (int)nd.w_arena;
+                            r.S = 1; r.stride = r.n; r.stored = 1;
+                            r.upd_w = p->master + (part ? nd.b_off : nd.w_off); r.upd_shadow = part ? nullptr : shadow_w; r.member = member;
+                            dw_red.push_back(r);
+                            dw_red_blocks.push_back((r.n + 1023) / 1024);
+                        }
+                    } else if (p->fused) {
+                        g.flags |= F_UPDATE | (keeps_g ? F_KEEP_G : 0);
                         g.upd_w = p->master + nd.w_off; g.upd_shadow = shadow_w; g.upd_b = p->master + nd.b_off; g.member = member;
                     }
                 }
@@ -1289,7 +1316,7 @@ pack_status build_device(pack_ctx* p) {
         if (o.kind == PACK_OPT_ADAM) need_v = true;
     }
     p->any_opt = need_m;
-    p->fused = !need_m && !std::getenv("PACK_NO_FUSED_UPDATE");   // the variable is a measuring aid
+    p->fused = !std::getenv("PACK_NO_FUSED_UPDATE");   // a measuring aid, and the partner of the tests of the fused update
     if (need_m) {
         TRY_ALLOC(p->opt_m, p->arena_elems * 4);
         TRY_ALLOC(p->opt_params, (size_t)K * sizeof(OptStatic));
@@ -1878,6 +1905,21 @@ static pack_status step_with_workspace(pack_t* p, const void* x_dev, const int32
     if (((uintptr_t)x_dev & 15) || ((uintptr_t)labels_dev & 3)) return fail(PACK_EINVAL, "x_dev must be 16-byte aligned");
     LrTable lr;
     for (int k = 0; k < PACK_LR_N; ++k) lr.lr[k] = (k < p->K) ? lr_host[k] : 0.f;
+    lr.opt = nullptr;
+    OptArgs oa;
+    if (p->any_opt) {
+        for (int k = 0; k < 256; ++k) {
+            oa.tab.lr[k] = (k < p->K) ? lr_host[k] : 0.f;
+            oa.tab.c1[k] = oa.tab.c2[k] = 1.f;
+            if (k < p->K && p->opt[k].kind == PACK_OPT_ADAM) {
+                const double t = (double)(p->opt_t[k] + 1);
+                oa.tab.c1[k] = (float)(1.0 / (1.0 - std::pow((double)p->opt[k].beta1, t)));
+                oa.tab.c2[k] = (float)(1.0 / (1.0 - std::pow((double)p->opt[k].beta2, t)));
+            }
+        }
+        oa.params = p->opt_params; oa.master = p->master; oa.m = p->opt_m; oa.v = p->opt_v;
+        lr.opt = &oa;
+    }
     const bool bf = p->bf16;
     const bool timed_step = p->profiling && (p->profile_step++ % p->profile_every == 0);
     for (size_t li = 0; li < p->plan.size(); ++li) {
@@ -1908,20 +1950,8 @@ static pack_status step_with_workspace(pack_t* p, const void* x_dev, const int32
                 if (!p->any_opt) {
                     e = launch_sgd(p->master, p->grad, p->shadow, (long long)p->arena_elems, p->seg_end, p->K, lr, p->stream);
                 } else {
-                    OptTable tab;
-                    for (int k = 0; k < 256; ++k) {
-                        tab.lr[k] = (k < p->K) ? lr_host[k] : 0.f;
-                        tab.c1[k] = tab.c2[k] = 1.f;
-                        if (k < p->K && p->opt[k].kind == PACK_OPT_ADAM) {
-                            const double t = (double)(p->opt_t[k] + 1);
-                            tab.c1[k] = (float)(1.0 / (1.0 - std::pow((double)p->opt[k].beta1, t)));
-                            tab.c2[k] = (float)(1.0 / (1.0 - std::pow((double)p->opt[k].beta2, t)));
-                        }
-                    }
                     e = launch_opt(p->master, p->grad, p->shadow, p->opt_m, p->opt_v, (long long)p->arena_elems,
-                                   p->seg_end, p->opt_params, p->K, tab, p->stream);
-                    if (e == hipSuccess)
-                        for (int k = 0; k < p->K; ++k) ++p->opt_t[k];
+                                   p->seg_end, p->opt_params, p->K, oa.tab, p->stream);
                 }
                 break;
         }
@@ -1931,6 +1961,8 @@ static pack_status step_with_workspace(pack_t* p, const void* x_dev, const int32
             p->stamps.push_back(stamp);
         }
     }
+    if (p->any_opt)
+        for (int k = 0; k < p->K; ++k) ++p->opt_t[k];
     return PACK_OK;
 }
 
@@ -2006,7 +2038,7 @@ pack_status pack_launch_name(const pack_t* p, int32_t i, char* buf, size_t n) {
     const char* nm = (L.kind == L_GEMM) ? gemm_names[L.mode] : names[L.kind];
     if (L.kind == L_SGD && p->any_opt) nm = "optimizer_update";
     const bool with_update = p->fused && (L.kind == L_REDUCE || (L.kind == L_GEMM && (L.mode == LIN_DW || L.mode == CONV_DW)));
-    std::snprintf(buf, n, "%s%s", nm, with_update ? "+sgd" : "");
+    std::snprintf(buf, n, "%s%s", nm, !with_update ? "" : p->any_opt ? "+opt" : "+sgd");
     return PACK_OK;
 }
 
@@ -2031,7 +2063,7 @@ pack_status pack_launch_tile(const pack_t* p, int32_t i, int32_t* tile_rows, int
     const bool gemm = L.kind == L_GEMM;
     *tile_rows = gemm ? GEMM_TILE_M[L.tile_cfg] : 0;
     *tile_cols = gemm ? GEMM_TILE_N[L.tile_cfg] : 0;
-    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN64);
+    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_LEAN64);
     return PACK_OK;
 }
 
@@ -2212,7 +2244,7 @@ pack_status pack_read_weights(pack_t* p, int32_t k, float* host_dst, size_t n_fl
 }
 
 pack_status pack_read_grads(pack_t* p, int32_t k, float* host_dst, size_t n_floats) {
-    if (p && p->fused && !p->keep_grads)
+    if (p && p->fused && !p->any_opt && !p->keep_grads)
         return fail(PACK_EINVAL, "plain-SGD packs apply the update where the gradient is produced and do not store it: "
                                  "call pack_keep_grads(p, 1) first");
     return download(p, k, p ? p->grad : nullptr, host_dst, n_floats);

@@ -104,4 +104,53 @@ __device__ __forceinline__ void wait_loads() {
 // uses this one expression so that a member's bits do not depend on which path its pack takes
 __device__ __forceinline__ float sgd_apply(float w, float g, float lr) { return __builtin_fmaf(-lr, g, w); }
 
+
+// One member's optimiser in one launch, and the update of one parameter and its state.  Every path that applies it uses
+// this one function, with its multiply-adds spelled out, for the same reason:
+//   momentum  acc <- mu*acc + g;  W <- W - lr*acc
+//   adagrad   acc <- acc + g*g;   W <- W - lr*g/sqrt(acc)
+//   adam      m <- b1*m + (1-b1)*g;  v <- b2*v + (1-b2)*g*g;  W <- W - lr*(m*c1)/(sqrt(v*c2) + eps),
+//             c1 = 1/(1-b1^t), c2 = 1/(1-b2^t) for step number t (computed on the host in double)
+struct OptRef {
+    OptStatic o;
+    float lr, c1, c2;
+};
+__device__ __forceinline__ OptRef opt_ref(const OptTable& tab, const OptStatic* params, int member) {
+    return OptRef{params[member], tab.lr[member], tab.c1[member], tab.c2[member]};
+}
+__device__ __forceinline__ void opt_apply(const OptRef& r, f32x4_t& w, const f32x4_t& g, f32x4_t& a, f32x4_t& b) {
+    if (r.o.kind == OPT_SGD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = sgd_apply(w[e], g[e], r.lr);
+    } else if (r.o.kind == OPT_MOMENTUM) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = __builtin_fmaf(r.o.mu, a[e], g[e]);
+            w[e] = __builtin_fmaf(-r.lr, a[e], w[e]);
+        }
+    } else if (r.o.kind == OPT_ADAGRAD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = __builtin_fmaf(g[e], g[e], a[e]);
+            w[e] = __builtin_fmaf(-r.lr, g[e] / sqrtf(a[e]), w[e]);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = __builtin_fmaf(r.o.beta1, a[e], (1.f - r.o.beta1) * g[e]);
+            b[e] = __builtin_fmaf(r.o.beta2, b[e], (1.f - r.o.beta2) * (g[e] * g[e]));
+            w[e] = __builtin_fmaf(-r.lr, (a[e] * r.c1) / (sqrtf(b[e] * r.c2) + r.o.eps), w[e]);
+        }
+    }
+}
+// the same for the one parameter at `i` of an array whose state lies at ms[i] (and vs[i])
+__device__ __forceinline__ float opt_apply_one(const OptRef& r, float w, float g, float* ms, float* vs, size_t i) {
+    const bool has_m = r.o.kind != OPT_SGD, has_v = r.o.kind == OPT_ADAM;
+    f32x4_t w4 = {w, 0.f, 0.f, 0.f}, g4 = {g, 0.f, 0.f, 0.f}, a = {has_m ? ms[i] : 0.f, 1.f, 1.f, 1.f}, b = {has_v ? vs[i] : 0.f, 1.f, 1.f, 1.f};
+    opt_apply(r, w4, g4, a, b);
+    if (has_m) ms[i] = a[0];
+    if (has_v) vs[i] = b[0];
+    return w4[0];
+}
+
 }  // namespace packk

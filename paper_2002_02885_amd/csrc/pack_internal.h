@@ -21,7 +21,22 @@ enum GemmMode : int {
 #ifndef PACK_LR_N
 #define PACK_LR_N 256
 #endif
-struct LrTable { float lr[PACK_LR_N]; };
+struct OptArgs;
+// the step's learning rates, by value; opt (host side only): what the update kernels of members with other optimisers need, or null
+struct LrTable { float lr[PACK_LR_N]; const OptArgs* opt; };
+
+// optimisers, as pack.h numbers them; a member's, in device memory; per-step tables (c1, c2: Adam's 1/(1-beta1^t), 1/(1-beta2^t))
+enum OptKind : int { OPT_SGD = 0, OPT_MOMENTUM = 1, OPT_ADAGRAD = 2, OPT_ADAM = 3 };
+struct OptStatic { int kind; float mu, beta1, beta2, eps; };
+struct OptTable { float lr[256]; float c1[256]; float c2[256]; };
+// by value to the weight-gradient and reduction kernels of packs with such members: the state arrays have the arena's layout
+struct OptArgs {
+    OptTable tab;
+    const OptStatic* params;
+    const float* master;
+    float* m;
+    float* v;
+};
 
 enum GemmFlags : int {
     F_RELU = 1,        // forward: max(v, 0)
@@ -121,6 +136,7 @@ struct ReduceProb {   // out[e] = sum_{s < S} in[s * stride + e], fixed order
     float* upd_w;         // not null: apply w[e] <- w[e] - lr[member] * sum instead of (keep_g: as well as) storing it
     void* upd_shadow;     // bf16 copy of w to refresh, or null
     int member, keep_g;
+    int stored;           // `in` is an address after all: a gradient that lies where it belongs and only has to be applied (S = 1)
 };
 
 struct CeProb {       // softmax cross-entropy of one member
@@ -238,9 +254,6 @@ hipError_t launch_gap(bool bf16, bool backward, const GapProb* probs_dev, const 
 hipError_t launch_shortcut_bwd(bool bf16, const ShortcutProb* probs_dev, const int2* map_dev, int n_blocks, hipStream_t st);
 hipError_t launch_sgd(float* master, const float* grad, void* shadow_bf16, long long n,
                       const long long* seg_end_dev, int K, const LrTable& lr, hipStream_t st);
-// per-member optimiser description (device memory, one entry per member) and per-step table (by value)
-struct OptStatic { int kind; float mu, beta1, beta2, eps; };
-struct OptTable { float lr[256]; float c1[256]; float c2[256]; };   // c1, c2: Adam's 1/(1-beta1^t), 1/(1-beta2^t)
 hipError_t launch_opt(float* master, const float* grad, void* shadow_bf16, float* m, float* v, long long n,
                       const long long* seg_end_dev, const OptStatic* params_dev, int K, const OptTable& tab, hipStream_t st);
 hipError_t launch_im2col(bool bf16, const Im2colProb* probs_dev, const int2* map_dev, int n_blocks, const void* x_dev, hipStream_t st);
@@ -273,8 +286,8 @@ hipError_t launch_gather_rows(const void* data, const int32_t* labels_all, const
 // 6, 7: the halo form of the convolution weight gradient (stride 1, stride 2): a tile is 64 output channels
 // x 64 input channels x all nine taps, i.e. 64 x 576 of the [Cout][9 * Cin] gradient
 // 8: the same with 32 input channels per tile (layers whose input channels are a multiple of 32 only; stride 1)
-constexpr int GEMM_TILE_M[16] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64};
-constexpr int GEMM_TILE_N[16] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64};
+constexpr int GEMM_TILE_M[17] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64};
+constexpr int GEMM_TILE_N[17] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64};
 constexpr int GEMM_CFG_SCALAR = 3;
 constexpr int GEMM_CFG_LEAN = 4;     // weight gradients, 128 x 128, short reductions
 constexpr int GEMM_CFG_LEAN64 = 5;   // forward / input gradients, 128 x 64, short reductions
@@ -289,6 +302,7 @@ constexpr int GEMM_CFG_GATHER0 = 11; // 11..13: configurations 0..2 with the gen
 inline bool is_gather_cfg(int cfg) { return cfg >= GEMM_CFG_GATHER0 && cfg < GEMM_CFG_GATHER0 + 3; }
 constexpr int GEMM_CFG_SLIM32 = 14;  // dense products with few outputs, reduction dealt over the waves, 32 x 32 tiles
 constexpr int GEMM_CFG_SLIM64 = 15;  // likewise, 64 x 64 tiles (bfloat16 forward products)
+constexpr int GEMM_CFG_LEAN_OPT = 16;   // dense weight gradients with another optimiser than SGD, short reductions
 inline bool is_slim_cfg(int cfg) { return cfg == GEMM_CFG_SLIM32 || cfg == GEMM_CFG_SLIM64; }
 constexpr int ELEMWISE_PER_BLOCK = 2048;   // elements one block of the elementwise kernels covers
 constexpr int SGD_PER_BLOCK = 2048;        // parameters one block of the update kernel covers (measured best of 1024..8192)

@@ -244,10 +244,11 @@ __device__ __forceinline__ long long shortcut_row(const GemmProb& p, int row) {
 // LEAN (aligned operands, reductions only a few chunks long): one register stage and one LDS buffer
 // instead of several.  A tile of such a product spends most of its life in its prologue and
 // epilogue, so what counts is how many tiles a compute unit can hold at once, not the depth of one
-// tile's pipeline.  Two forms: 128 x 128 weight gradients, whose epilogue stages the accumulators in
-// two halves (three workgroups per compute unit), and 128 x 64 forward products / input gradients,
-// whose LDS block is sized for the epilogue's staging tile (four workgroups per compute unit).
-// Both multiply the same chunks in the same order as the regular kernels: the bits are the same.
+// tile's pipeline.  Three forms: 128 x 128 weight gradients, whose epilogue stages the accumulators in
+// two halves (three workgroups per compute unit), 128 x 64 forward products / input gradients,
+// whose LDS block is sized for the epilogue's staging tile (four workgroups per compute unit), and
+// 64 x 64 weight gradients updated by an optimiser with state (four).
+// All multiply the same chunks in the same order as the regular kernels: the bits are the same.
 //
 // Bytes of the workgroup's LDS block: the operand buffers (two of each, one in the lean forms); the
 // lean forward / input-gradient form, whose epilogue stages the whole fp32 tile, takes the larger of
@@ -580,8 +581,20 @@ __device__ __forceinline__ void finish_tile(const GemmProb& p, const int row0, c
     }
 }
 
-template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false>
-__device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, T* __restrict__ As_, T* __restrict__ Bs_, float lrk) {
+// what a kernel gets of the step's rates: weight gradients the table (OPT: with the optimisers), the others nothing
+struct NoLr {};
+template <int MODE, bool OPT>
+using LrArg = typename std::conditional<MODE == LIN_DW || MODE == CONV_DW, typename std::conditional<OPT, OptArgs, LrTable>::type, NoLr>::type;
+
+// OPT (dense weight gradients of packs in which some member's optimiser keeps state): F_UPDATE applies the member's own
+// optimiser, whose state lies like the weights.
+template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false, bool OPT = false>
+__device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, T* __restrict__ As_, T* __restrict__ Bs_, const LrArg<MODE, OPT>& rates) {
+    static_assert(!OPT || MODE == LIN_DW, "dense weight gradients");
+    float lrk = 0.f;
+    if constexpr ((MODE == LIN_DW || MODE == CONV_DW) && !OPT) lrk = rates.lr[p.member];
+    OptRef opt{};
+    if constexpr (OPT) opt = opt_ref(rates.tab, rates.params, p.member);
     constexpr int V = ET<T>::V, BK = ET<T>::BK * BKM;
     typedef TileGeom<T, BM, BK> GA;
     typedef TileGeom<T, BN, BK> GB;
@@ -592,7 +605,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     // in flight per workgroup; a skinny layer has too few workgroups per compute unit to hide that
     // latency by occupancy alone.
     constexpr int ST = LEAN ? 1 : StageCount<BM, BN, BKM, VEC>::value;
-    static_assert(!LEAN || (VEC && BM == 128 && (IS_DW ? BN == 128 : BN == 64)), "lean form: aligned operands, 128x128 weight gradients or 128x64 forward / input gradients");
+    static_assert(!LEAN || (VEC && BM == 128 && (IS_DW ? BN == 128 : BN == 64)) || (VEC && OPT && BM == 64 && BN == 64), "lean form: aligned operands, 128x128 weight gradients or 128x64 forward / input gradients");
     T(*As)[BM][GA::LDS_LD] = reinterpret_cast<T(*)[BM][GA::LDS_LD]>(As_);
     T(*Bs)[BN][GB::LDS_LD] = reinterpret_cast<T(*)[BN][GB::LDS_LD]>(Bs_);
 
@@ -851,7 +864,10 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
         if (do_bias_grad && threadIdx.x < BM && row0 + (int)threadIdx.x < p.R) {
             const int r = row0 + threadIdx.x;
             if (keep_g) p.dbias[(size_t)tr.ks * p.R + r] = bias_grad;
-            if (upd) p.upd_b[r] = sgd_apply(p.upd_b[r], bias_grad, lrk);
+            if (upd) {
+                if constexpr (OPT) p.upd_b[r] = opt_apply_one(opt, p.upd_b[r], bias_grad, rates.m, rates.v, (size_t)(p.upd_b - rates.master) + r);
+                else p.upd_b[r] = sgd_apply(p.upd_b[r], bias_grad, lrk);
+            }
         }
     }
 
@@ -863,9 +879,77 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     constexpr int SLD = BN + 8;   // 4 rows apart = 32 banks apart: the two half-waves do not collide
     // the lean weight-gradient form has one operand buffer: room for half the tile at a time; the lean
     // forward / input-gradient form sizes its LDS block for the whole staging tile (LeanLds below)
-    constexpr int HALVES = (LEAN && IS_DW) ? 2 : 1;
+    constexpr int HALVES = (LEAN && IS_DW && BM == 128) ? 2 : 1;
     static_assert((size_t)(BM / HALVES) * SLD * 4 <= LdsBytes<T, BM, BN, BK, LEAN, IS_DW>::value, "staging tile must fit");
     float(*stage)[SLD] = reinterpret_cast<float(*)[SLD]>(As_);
+    if constexpr (OPT) {
+        // The tile's weights and their state, four rows of a thread at a time (three vectors a row under Adam); the first
+        // request runs under the staging of the accumulators.  Against a product that stores the gradient and a launch that
+        // streams it back in: the gradient is not read, a launch less, and the matrix instructions of some workgroups run
+        // under the streams of others.  Bound by those streams: on 128 x 128 tiles, three workgroups to a compute unit and
+        // few of them, it lost (8 members of 1.6 M, mixed optimisers, bf16: 60 us apart, 67 fused); on 64 x 64 tiles in the
+        // lean form 49.  6 x 0.4 M, momentum, bf16: 27 -> 18; 3 x 14.9 M, Adam, fp32 over 256 rows: 406 -> 378.
+        constexpr int PER = DW_NIT / HALVES, OB = PER < 4 ? PER : 4;
+        static_assert(PER % OB == 0, "whole batches");
+        const bool has_m = upd && opt.o.kind != OPT_SGD, has_v = upd && opt.o.kind == OPT_ADAM;
+        const int col = col0 + dw_lc;
+        const size_t state0 = upd ? (size_t)(p.upd_w - rates.master) : 0;
+        float* const gf = (float*)p.C + (size_t)tr.ks * p.split_stride;
+        f32x4_t w[OB], m[OB], v[OB];
+        auto request = [&](int n0) {
+#pragma unroll
+            for (int j = 0; j < OB; ++j) {
+                const int row = row0 + dw_lr0 + (n0 + j) * DW_RSTEP;
+                const size_t off = (size_t)row * p.ldc + col;
+                const bool live = dw_live && row < p.R;
+                if (live && upd) w[j] = *reinterpret_cast<const f32x4_t*>(p.upd_w + off);
+                if (live && has_m) m[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(rates.m + state0 + off));
+                if (live && has_v) v[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(rates.v + state0 + off));
+            }
+        };
+#pragma unroll
+        for (int part = 0; part < HALVES; ++part) {
+            request(part * PER);
+            lds_barrier();   // operand tiles (part 0) or the previous part's staging no longer read
+            if (HALVES == 1 || wm == part) {
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            stage[(HALVES == 1 ? wm * (BM / 2) : 0) + a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)][wn * (BN / 2) + b * 32 + (lane & 31)] = acc[a][b][e];
+            }
+            lds_barrier();
+#pragma unroll
+            for (int n0 = part * PER; n0 < (part + 1) * PER; n0 += OB) {
+                if (n0 != part * PER) request(n0);
+#pragma unroll
+                for (int j = 0; j < OB; ++j) {
+                    const int lr = dw_lr0 + (n0 + j) * DW_RSTEP, row = row0 + lr;
+                    if (!dw_live || row >= p.R) continue;
+                    const size_t off = (size_t)row * p.ldc + col;
+                    f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr - part * (BM / HALVES)][dw_lc]);
+                    if (dw_pad) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if ((dw_pad >> e) & 1u) g[e] = 0.f;
+                    }
+                    if (keep_g) __builtin_nontemporal_store(g, reinterpret_cast<f32x4_t*>(gf + off));
+                    if (!upd) continue;
+                    opt_apply(opt, w[j], g, m[j], v[j]);
+                    if (has_m) __builtin_nontemporal_store(m[j], reinterpret_cast<f32x4_t*>(rates.m + state0 + off));
+                    if (has_v) __builtin_nontemporal_store(v[j], reinterpret_cast<f32x4_t*>(rates.v + state0 + off));
+                    *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w[j];
+                    if (p.upd_shadow) {
+                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+                        *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[j][0], w[j][1]), pack2bf(w[j][2], w[j][3])};
+                    }
+                }
+            }
+        }
+        return;
+    }
     // the weights of the tile: their round trip runs under the staging of the accumulators
     if constexpr (IS_DW) {
         if (upd && dw_live) {
@@ -876,7 +960,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
             }
         }
     }
-    if constexpr (LEAN && IS_DW) {
+    if constexpr (LEAN && IS_DW && !OPT) {
         // two passes: the waves that own the upper (then the lower) half of the rows stage their
         // accumulators, then all threads apply that half
         float* const gf = (float*)p.C + (size_t)tr.ks * p.split_stride;
@@ -1167,19 +1251,14 @@ __global__ __launch_bounds__(256, 2) void conv_rows_halo_kernel(const GemmProb* 
     finish_tile<MODE, T, BM, BN, 8>(p, row0, col0, stage, bias_v, vec_out, fill_stage);
 }
 
-// weight-gradient kernels also take the step's learning rates (by value), the others nothing
-struct NoLr {};
-template <int MODE>
-using LrArg = typename std::conditional<MODE == LIN_DW || MODE == CONV_DW, LrTable, NoLr>::type;
-
 // VEC = true: every problem of the launch has both operands aligned for 16-byte loads (the planner
 // sorts problems into launches by that); VEC = false: the element-by-element gather for any size.
 // They are separate kernels because the gather needs many more registers, which would halve the
 // occupancy of the aligned path if both lived in one kernel.
-template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false>
+template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false, bool OPT = false>
 __global__ __launch_bounds__(256) void gemm_kernel(const GemmProb* __restrict__ probs,
                                                    const TileRef* __restrict__ tiles,
-                                                   const void* __restrict__ x, char* __restrict__ ws, LrArg<MODE> lr) {
+                                                   const void* __restrict__ x, char* __restrict__ ws, LrArg<MODE, OPT> lr) {
     constexpr int BK = ET<T>::BK * BKM;
     const TileRef tr = tiles[blockIdx.x];
     if (tr.prob < 0) return;
@@ -1201,14 +1280,27 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmProb* __restrict__ 
     __shared__ __attribute__((aligned(16))) T lds[LdsBytes<T, BM, BN, BK, LEAN, (MODE == LIN_DW || MODE == CONV_DW)>::value / sizeof(T)];
     T* const As = lds;
     T* const Bs = lds + NBUF * BM * TileGeom<T, BM, BK>::LDS_LD;
-    float lrk = 0.f;
-    if constexpr (MODE == LIN_DW || MODE == CONV_DW) lrk = lr.lr[p.member];
-    gemm_body<MODE, T, BM, BN, BKM, VEC, LEAN, GEN>(p, tr, As, Bs, lrk);
+    gemm_body<MODE, T, BM, BN, BKM, VEC, LEAN, GEN, OPT>(p, tr, As, Bs, lr);
+}
+
+// dense weight gradients of packs with other optimisers than SGD
+template <typename T>
+static void launch_lin_dw_opt(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const OptArgs& oa, hipStream_t st) {
+    switch (tile_cfg) {
+        case 0: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 128, 128, 1, true, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
+        case 1: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 128, 64, 1, true, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
+        case 2: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 64, 64, 1, true, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
+        case GEMM_CFG_LEAN_OPT: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 64, 64, 1, true, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
+        default: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 64, 64, 1, false, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
+    }
 }
 
 template <int MODE, typename T>
 static void launch_gemm_tile(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const LrTable& lr, hipStream_t st) {
-    LrArg<MODE> la;
+    if constexpr (MODE == LIN_DW) {
+        if (lr.opt) { launch_lin_dw_opt<T>(tile_cfg, probs, tiles, n, x, ws, *lr.opt, st); return; }
+    }
+    LrArg<MODE, false> la;
     if constexpr (MODE == LIN_DW || MODE == CONV_DW) la = lr;
     switch (tile_cfg) {
         case 0: hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
@@ -1280,13 +1372,24 @@ hipError_t launch_gemm(int mode, bool bf16, int tile_cfg, const GemmProb* probs,
     }
 }
 
-// out[e] = sum over S partials, in order
+// out[e] = sum over S partials, in order; then the update, by SGD or (OPT) the member's own optimiser
+template <bool OPT>
 __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restrict__ probs, const int2* __restrict__ map,
-                                                     const char* __restrict__ ws, LrTable lr) {
+                                                     const char* __restrict__ ws, LrArg<LIN_DW, OPT> lr) {
     const int2 m = map[blockIdx.x];
     ReduceProb p = probs[m.x];
-    p.in = (const float*)(ws + (size_t)p.in);   // the partial sums lie in the workspace this launch was given
-    const float lrk = p.upd_w ? lr.lr[p.member] : 0.f;
+    if (!p.stored) p.in = (const float*)(ws + (size_t)p.in);   // the partial sums lie in the workspace this launch was given
+    float lrk = 0.f;
+    OptRef opt{};
+    size_t state0 = 0;
+    if (p.upd_w) {
+        if constexpr (OPT) {
+            opt = opt_ref(lr.tab, lr.params, p.member);
+            state0 = (size_t)(p.upd_w - lr.master);
+        } else {
+            lrk = lr.lr[p.member];
+        }
+    }
     // Partials are added in split order.  Whole vectors (weights; only a bias can have an odd length): a thread owns four
     // consecutive elements and requests sixteen splits before it adds them, since a layer with few weights has few threads
     // and many splits and takes as long as its rounds of reads.  (Against eight splits of 4-byte reads: 48 -> 42 us on four
@@ -1296,8 +1399,13 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restric
         if (e >= p.n) return;
         constexpr int DEEP = 16;
         const float* const in = p.in + e;
-        f32x4_t w{}, s = {0.f, 0.f, 0.f, 0.f};
-        if (p.upd_w) w = *reinterpret_cast<const f32x4_t*>(p.upd_w + e);   // its round trip runs under the partials'
+        f32x4_t w{}, s = {0.f, 0.f, 0.f, 0.f}, sm{}, sv{};
+        if (p.upd_w) w = *reinterpret_cast<const f32x4_t*>(p.upd_w + e);   // its round trip runs under the partials', and that of the state
+        const bool has_m = OPT && p.upd_w && opt.o.kind != OPT_SGD, has_v = OPT && p.upd_w && opt.o.kind == OPT_ADAM;
+        if constexpr (OPT) {
+            if (has_m) sm = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(lr.m + state0 + e));
+            if (has_v) sv = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(lr.v + state0 + e));
+        }
         int k = 0;
         for (; k + DEEP <= p.S; k += DEEP) {
             f32x4_t v[DEEP];
@@ -1321,8 +1429,14 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restric
                 }
         }
         if (p.upd_w) {   // fused update: the summed gradient goes straight into the weights
+            if constexpr (OPT) {
+                opt_apply(opt, w, s, sm, sv);
+                if (has_m) __builtin_nontemporal_store(sm, reinterpret_cast<f32x4_t*>(lr.m + state0 + e));
+                if (has_v) __builtin_nontemporal_store(sv, reinterpret_cast<f32x4_t*>(lr.v + state0 + e));
+            } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = sgd_apply(w[i], s[i], lrk);
+                for (int i = 0; i < 4; ++i) w[i] = sgd_apply(w[i], s[i], lrk);
+            }
             *reinterpret_cast<f32x4_t*>(p.upd_w + e) = w;
             if (p.upd_shadow) {
                 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
@@ -1352,7 +1466,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restric
         const int e = e0 + i * 256;
         if (e < p.n) {
             if (p.upd_w) {   // fused update: the summed gradient goes straight into the weights
-                const float w = sgd_apply(p.upd_w[e], s[i], lrk);
+                float w;
+                if constexpr (OPT) w = opt_apply_one(opt, p.upd_w[e], s[i], lr.m, lr.v, state0 + e);
+                else w = sgd_apply(p.upd_w[e], s[i], lrk);
                 p.upd_w[e] = w;
                 if (p.upd_shadow) ((bf16_t*)p.upd_shadow)[e] = ET<bf16_t>::from_f(w);
             }
@@ -1363,7 +1479,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restric
 
 hipError_t launch_reduce(const ReduceProb* probs, const int2* map, int n, const char* ws, const LrTable& lr, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(reduce_kernel, dim3(n), dim3(256), 0, st, probs, map, ws, lr);
+    if (lr.opt) hipLaunchKernelGGL(reduce_kernel<true>, dim3(n), dim3(256), 0, st, probs, map, ws, *lr.opt);
+    else hipLaunchKernelGGL(reduce_kernel<false>, dim3(n), dim3(256), 0, st, probs, map, ws, lr);
     return hipGetLastError();
 }
 
@@ -1726,18 +1843,12 @@ hipError_t launch_sgd(float* master, const float* grad, void* shadow, long long 
 }
 
 // ------------------------------------------------------------------------------------------------
-// The other optimisers of the paper's search space (Table 3), each member with its own kind,
-// hyper-parameters and state (Section 2.2 keeps the optimiser state with the model it belongs to):
-//   momentum  acc <- mu*acc + g;  W <- W - lr*acc
-//   adagrad   acc <- acc + g*g;   W <- W - lr*g/sqrt(acc)
-//   adam      m <- b1*m + (1-b1)*g;  v <- b2*v + (1-b2)*g*g;  W <- W - lr*(m*c1)/(sqrt(v*c2) + eps),
-//             c1 = 1/(1-b1^t), c2 = 1/(1-b2^t) for step number t (computed on the host in double)
-// `m` holds the momentum / Adagrad accumulator or Adam's first moment, `v` Adam's second moment.
-// Streams 20-22 bytes per parameter for momentum and Adagrad, 28-30 for Adam.  Packs whose members
-// all use plain SGD never launch this kernel.
+// The other optimisers of the paper's search space (Table 3), each member with its own kind, hyper-parameters and state
+// (Section 2.2 keeps the optimiser state with the model it belongs to), as a launch of its own over the arena: the yardstick
+// and test partner of the update in the weight-gradient kernels (PACK_NO_FUSED_UPDATE).  `ms` holds the momentum / Adagrad
+// accumulator or Adam's first moment, `vs` Adam's second moment.  Streams 20-22 bytes per parameter for momentum and
+// Adagrad, 28-30 for Adam.
 // ------------------------------------------------------------------------------------------------
-enum OptKind { OPT_SGD = 0, OPT_MOMENTUM = 1, OPT_ADAGRAD = 2, OPT_ADAM = 3 };
-
 template <bool SHADOW>
 __global__ __launch_bounds__(256) void opt_kernel(float* __restrict__ w, const float* __restrict__ g,
                                                   bf16_t* __restrict__ shadow, float* __restrict__ ms,
@@ -1783,38 +1894,11 @@ __global__ __launch_bounds__(256) void opt_kernel(float* __restrict__ w, const f
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
         if (idx[i] >= n) continue;
-        const OptStatic o = s_par[mem[i]];
-        const float lr = s_lr[mem[i]];
+        const OptRef r{s_par[mem[i]], s_lr[mem[i]], s_c1[mem[i]], s_c2[mem[i]]};
         f32x4_t wo = wv[i], a = av[i], b = bv[i];
-        const f32x4_t gg = gv[i];
-        if (o.kind == OPT_SGD) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) wo[e] = sgd_apply(wo[e], gg[e], lr);
-        } else if (o.kind == OPT_MOMENTUM) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[e] = o.mu * a[e] + gg[e];
-                wo[e] = wo[e] - lr * a[e];
-            }
-            __builtin_nontemporal_store(a, reinterpret_cast<f32x4_t*>(ms + idx[i]));
-        } else if (o.kind == OPT_ADAGRAD) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[e] = a[e] + gg[e] * gg[e];
-                wo[e] = wo[e] - lr * (gg[e] / sqrtf(a[e]));
-            }
-            __builtin_nontemporal_store(a, reinterpret_cast<f32x4_t*>(ms + idx[i]));
-        } else {
-            const float c1 = s_c1[mem[i]], c2 = s_c2[mem[i]];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[e] = o.beta1 * a[e] + (1.f - o.beta1) * gg[e];
-                b[e] = o.beta2 * b[e] + (1.f - o.beta2) * (gg[e] * gg[e]);
-                wo[e] = wo[e] - lr * ((a[e] * c1) / (sqrtf(b[e] * c2) + o.eps));
-            }
-            __builtin_nontemporal_store(a, reinterpret_cast<f32x4_t*>(ms + idx[i]));
-            __builtin_nontemporal_store(b, reinterpret_cast<f32x4_t*>(vs + idx[i]));
-        }
+        opt_apply(r, wo, gv[i], a, b);
+        if (r.o.kind != OPT_SGD) __builtin_nontemporal_store(a, reinterpret_cast<f32x4_t*>(ms + idx[i]));
+        if (r.o.kind == OPT_ADAM) __builtin_nontemporal_store(b, reinterpret_cast<f32x4_t*>(vs + idx[i]));
         __builtin_nontemporal_store(wo, reinterpret_cast<f32x4_t*>(w + idx[i]));
         if constexpr (SHADOW) {
             typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;

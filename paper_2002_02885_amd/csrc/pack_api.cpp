@@ -458,10 +458,10 @@ double padded_work(const GemmProb& g, int c) {
 }
 
 void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std::vector<GemmProb>& probs) {
-    const int BMc = GEMM_TILE_M[cfg], BNc = GEMM_TILE_N[cfg];
     std::vector<TileOrder> logical;
     for (size_t i = 0; i < probs.size(); ++i) {
         const GemmProb& g = probs[i];
+        const int BMc = tile_rows(cfg, g), BNc = tile_cols(cfg, g);
         const int tms = (g.R + BMc - 1) / BMc, tns = (g.Q + BNc - 1) / BNc;
         const int S = (g.Kd + g.ksplit - 1) / g.ksplit;
         for (int ks = 0; ks < std::max(S, 1); ++ks) {
@@ -497,7 +497,7 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
         std::vector<double> cost(logical.size());
         for (size_t t = 0; t < logical.size(); ++t) {
             const GemmProb& g = probs[logical[t].prob];
-            const int chunk = p->bf16 ? 64 : 32;
+            const int chunk = p->bf16 ? 64 : 32, BMc = GEMM_TILE_M[cfg], BNc = GEMM_TILE_N[cfg];
             const double rows = std::min(BMc, g.R - logical[t].tm * BMc), cols = std::min(BNc, g.Q - logical[t].tn * BNc);
             cost[t] = 10.0 * rows * cols / ((double)BMc * BNc) + (double)((std::min(g.Kd, g.ksplit) + chunk - 1) / chunk);
         }
@@ -620,7 +620,17 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
         for (const GemmProb& g : probs) ((g.flags & F_SLIM) ? slim : rest).push_back(g);
         if (!slim.empty()) {
             const bool big = p->bf16 && mode == LIN_FWD && count_tiles(slim, GEMM_CFG_SLIM32) >= SLIM64_MIN_TILES32;
-            emit_gemm_launch(p, db, mode, big ? GEMM_CFG_SLIM64 : GEMM_CFG_SLIM32, slim);
+            // those of the same size that keep the staged order ride along (slim_flag; they take longest and start first)
+            std::vector<GemmProb> both, others;
+            if (!p->bf16)
+                for (const GemmProb& g : rest) (slim_ok(g) ? both : others).push_back(g);
+            if (both.empty()) {
+                emit_gemm_launch(p, db, mode, big ? GEMM_CFG_SLIM64 : GEMM_CFG_SLIM32, slim);
+            } else {
+                both.insert(both.end(), slim.begin(), slim.end());
+                emit_gemm_launch(p, db, mode, GEMM_CFG_SLIM_MIXED, both);
+                rest.swap(others);
+            }
         }
         probs.swap(rest);
     }
@@ -660,7 +670,11 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
         std::vector<GemmProb> opt, rest;
         const int chunk = p->bf16 ? 64 : 32;
         for (const GemmProb& g : probs) ((std::min(g.Kd, g.ksplit) + chunk - 1) / chunk <= 8 && g.Kd <= g.ksplit ? opt : rest).push_back(g);
-        if (!opt.empty()) {
+        // (a classifier next to the split gradients of convolutions rides along in their launch: 5.9 us for one of its own)
+        double w_opt = 0, w_rest = 0;
+        for (const GemmProb& g : opt) w_opt += padded_work(g, 2);
+        for (const GemmProb& g : rest) w_rest += padded_work(g, 2);
+        if (w_opt >= 0.15 * w_rest && !opt.empty()) {
             emit_gemm_launch(p, db, mode, GEMM_CFG_LEAN_OPT, opt);
             if (!rest.empty()) add_tiled_launches(p, db, mode, rest, general);
             return;
@@ -1415,8 +1429,10 @@ pack_status build_device(pack_ctx* p) {
         return PACK_OK;
     }
 
-    // everything on the pack's stream, in front of whatever uses it
-    hipError_t e = hipMemcpy(p->desc, db.bytes.data(), db.bytes.size(), hipMemcpyHostToDevice);
+    // everything on the pack's stream, in front of whatever uses it.  A stream that cannot be waited for (one that is being
+    // captured) is refused before anything is enqueued: a failure later on would free buffers that enqueued work still names.
+    hipError_t e = hipStreamSynchronize(p->stream);
+    if (e == hipSuccess) e = hipMemcpy(p->desc, db.bytes.data(), db.bytes.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemsetAsync(p->slab, 0, p->slab_bytes, p->stream);
     if (e == hipSuccess) e = hipMemsetAsync(p->grad, 0, p->arena_elems * 4, p->stream);
     if (e == hipSuccess) e = hipMemsetAsync(p->master, 0, p->arena_elems * 4, p->stream);
@@ -1615,12 +1631,6 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
         release(p);
         return fail(PACK_EDEVICE, "no HIP device is current");
     }
-    // A stream that cannot be waited for (one that is being captured) is refused before anything is allocated or enqueued: a
-    // failure at the end would free buffers that the work enqueued in between still names.
-    if (const hipError_t e = hipStreamSynchronize(p->stream); e != hipSuccess) {
-        release(p);
-        return fail(PACK_EDEVICE, std::string("the pack's stream: ") + hipGetErrorString(e));
-    }
     pack_status s = build_device(p);
     if (s != PACK_OK) { release(p); return s; }
     for (int k = 0; k < K; ++k) {
@@ -1692,7 +1702,6 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
         }
         if (staged) {
             // aligned staged-tile kernels: the fetchers themselves, run on the CPU, against the definition of the operands
-            const int BMc = GEMM_TILE_M[L.tile_cfg], BNc = GEMM_TILE_N[L.tile_cfg];
             std::map<std::vector<int>, int> dealt;
             int n_probs = 0;
             for (int t = 0; t < L.n && err.empty(); ++t) {
@@ -1700,6 +1709,7 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
                 if (tr.prob < 0) continue;
                 n_probs = std::max(n_probs, tr.prob + 1);
                 GemmProb g = probs[tr.prob];
+                const int BMc = tile_rows(L.tile_cfg, g), BNc = tile_cols(L.tile_cfg, g);
                 if (g.flags & F_A_INPUT) g.A = (const char*)x_fake + g.x_off;
                 if (g.flags & F_B_INPUT) g.B = (const char*)x_fake + g.x_off;
                 unsigned long long alo, ahi, blo, bhi;
@@ -1712,7 +1722,7 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
             }
             for (int i = 0; i < n_probs && err.empty(); ++i) {
                 const GemmProb& g = probs[i];
-                const int S = std::max(1, (g.Kd + g.ksplit - 1) / g.ksplit);
+                const int S = std::max(1, (g.Kd + g.ksplit - 1) / g.ksplit), BMc = tile_rows(L.tile_cfg, g), BNc = tile_cols(L.tile_cfg, g);
                 for (int ks = 0; ks < S; ++ks)
                     for (int tm = 0; tm < (g.R + BMc - 1) / BMc; ++tm)
                         for (int tn = 0; tn < (g.Q + BNc - 1) / BNc; ++tn)

@@ -286,8 +286,8 @@ hipError_t launch_gather_rows(const void* data, const int32_t* labels_all, const
 // 6, 7: the halo form of the convolution weight gradient (stride 1, stride 2): a tile is 64 output channels
 // x 64 input channels x all nine taps, i.e. 64 x 576 of the [Cout][9 * Cin] gradient
 // 8: the same with 32 input channels per tile (layers whose input channels are a multiple of 32 only; stride 1)
-constexpr int GEMM_TILE_M[17] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64};
-constexpr int GEMM_TILE_N[17] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64};
+constexpr int GEMM_TILE_M[18] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64, 64};
+constexpr int GEMM_TILE_N[18] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64, 64};
 constexpr int GEMM_CFG_SCALAR = 3;
 constexpr int GEMM_CFG_LEAN = 4;     // weight gradients, 128 x 128, short reductions
 constexpr int GEMM_CFG_LEAN64 = 5;   // forward / input gradients, 128 x 64, short reductions
@@ -302,8 +302,12 @@ constexpr int GEMM_CFG_GATHER0 = 11; // 11..13: configurations 0..2 with the gen
 inline bool is_gather_cfg(int cfg) { return cfg >= GEMM_CFG_GATHER0 && cfg < GEMM_CFG_GATHER0 + 3; }
 constexpr int GEMM_CFG_SLIM32 = 14;  // dense products with few outputs, reduction dealt over the waves, 32 x 32 tiles
 constexpr int GEMM_CFG_SLIM64 = 15;  // likewise, 64 x 64 tiles (bfloat16 forward products)
+constexpr int GEMM_CFG_SLIM_MIXED = 17;  // slim problems (32 x 32) and staged ones (64 x 64) in one launch, fp32
 constexpr int GEMM_CFG_LEAN_OPT = 16;   // dense weight gradients with another optimiser than SGD, short reductions
 inline bool is_slim_cfg(int cfg) { return cfg == GEMM_CFG_SLIM32 || cfg == GEMM_CFG_SLIM64; }
+// side of the tiles a problem of a launch is cut into
+inline int tile_rows(int cfg, const GemmProb& g) { return cfg == GEMM_CFG_SLIM_MIXED && (g.flags & F_SLIM) ? 32 : GEMM_TILE_M[cfg]; }
+inline int tile_cols(int cfg, const GemmProb& g) { return cfg == GEMM_CFG_SLIM_MIXED && (g.flags & F_SLIM) ? 32 : GEMM_TILE_N[cfg]; }
 constexpr int ELEMWISE_PER_BLOCK = 2048;   // elements one block of the elementwise kernels covers
 constexpr int SGD_PER_BLOCK = 2048;        // parameters one block of the update kernel covers (measured best of 1024..8192)
 

@@ -97,12 +97,20 @@ def test_a_change_of_optimiser_changes_the_form_of_a_single_precision_member_and
     b.set_optimizer(0, {"kind": "adam"})
     b.set_optimizer(1, {"kind": "momentum"})
     b.set_optimizer(2, {"kind": "adam"})
-    assert forms(a) == forms(b) == [32, 32, 64, 64]
+    assert forms(a) == forms(b) == [64, 64]     # slim and staged problems in one launch
     for k in range(3):
         b.write_weights(k, a.read_weights(k))
+    solo = [binding.Pack(B, (1, 1, D), "f32", models[:1], seed=1) for _ in range(3)]
+    for k, o in enumerate(("adam", "momentum", "adam")):     # (each alone: one form or the other)
+        solo[k].set_optimizer(0, {"kind": o})
+        solo[k].write_weights(0, a.read_weights(k))
     for _ in range(3):
         for p in (a, b):
             p.step(x.data_ptr(), y.data_ptr(), lr)
+        for k in range(3):
+            solo[k].step(x.data_ptr(), y.data_ptr(), lr[k:k + 1])
+    for k in range(3):
+        assert np.array_equal(a.read_weights(k).view(np.uint32), solo[k].read_weights(0).view(np.uint32)), k
     assert np.array_equal(a.read_loss(), b.read_loss())
     for k in range(3):
         assert np.array_equal(a.read_weights(k).view(np.uint32), b.read_weights(k).view(np.uint32)), k

@@ -709,7 +709,11 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
     const bool lean_ok = (mode == LIN_DW && !(p->any_opt && p->fused)) || mode == CONV_DW;   // (with other optimisers: above)
     // forward products and input gradients on 128 x 64 tiles have a lean form too (one register stage,
     // one operand buffer, four workgroups per compute unit); PACK_LEAN64_CHUNKS sets the longest
-    // reduction, in chunks, that takes it (0: never; a measuring aid)
+    // reduction, in chunks, that takes it (0: never; a measuring aid).  With the general gather every 128 x 64 launch does: its
+    // tiles issue some ten vector instructions per load to find taps and pixels, which other workgroups hide better than one's
+    // own pipeline, whatever the reduction's length.  Measured: 5 CNNs of 24 to 96 channels on 28 x 28 pixels, bf16, forward
+    // 36 -> 28 us, input gradients 49 -> 38; 2 residual networks of 40 to 320, fp32, 5 / 12 / 23 chunks 72 -> 59, 105 -> 98,
+    // 96 -> 84, 704 tiles 54 -> 49.
     int lean64_chunks = LEAN64_MAX_CHUNKS;
     if (const char* v = std::getenv("PACK_LEAN64_CHUNKS")) lean64_chunks = std::atoi(v);
     const bool is_dw = mode == LIN_DW || mode == CONV_DW;
@@ -720,16 +724,16 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
             const int eff = (work[want[i]] < 0.15 * total) ? main_cfg : want[i];
             if (eff != c) continue;
             const int chunks = (std::min(probs[i].Kd, probs[i].ksplit) + chunk_k - 1) / chunk_k;
-            if (general) group.push_back(probs[i]);
+            if (general && is_dw) group.push_back(probs[i]);
             else if (c == 0 && lean_ok && chunks <= 8) lean.push_back(probs[i]);
-            else if (c == 1 && !is_dw && chunks <= lean64_chunks) lean.push_back(probs[i]);
+            else if (c == 1 && !is_dw && (chunks <= lean64_chunks || (general && lean64_chunks > 0))) lean.push_back(probs[i]);
             else group.push_back(probs[i]);
         }
-        if (!is_dw && !lean.empty() && count_tiles(lean, GEMM_CFG_LEAN64) < LEAN64_MIN_TILES && !std::getenv("PACK_LEAN64_CHUNKS")) {
+        if (!is_dw && !general && !lean.empty() && count_tiles(lean, GEMM_CFG_LEAN64) < LEAN64_MIN_TILES && !std::getenv("PACK_LEAN64_CHUNKS")) {
             group.insert(group.end(), lean.begin(), lean.end());   // too few tiles to fill the occupancy
             lean.clear();
         }
-        if (!lean.empty()) emit_gemm_launch(p, db, mode, is_dw ? GEMM_CFG_LEAN : GEMM_CFG_LEAN64, lean);
+        if (!lean.empty()) emit_gemm_launch(p, db, mode, is_dw ? GEMM_CFG_LEAN : general ? GEMM_CFG_GATHER_LEAN64 : GEMM_CFG_LEAN64, lean);
         if (!group.empty()) emit_gemm_launch(p, db, mode, general ? GEMM_CFG_GATHER0 + c : c, group);
     }
 }
@@ -2073,7 +2077,7 @@ pack_status pack_launch_tile(const pack_t* p, int32_t i, int32_t* tile_rows, int
     const bool gemm = L.kind == L_GEMM;
     *tile_rows = gemm ? GEMM_TILE_M[L.tile_cfg] : 0;
     *tile_cols = gemm ? GEMM_TILE_N[L.tile_cfg] : 0;
-    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_LEAN64);
+    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_GATHER_LEAN64 || L.tile_cfg == GEMM_CFG_LEAN64);
     return PACK_OK;
 }
 

@@ -1344,6 +1344,9 @@ static void launch_gemm_tile(int tile_cfg, const GemmProb* probs, const TileRef*
         case GEMM_CFG_GATHER0 + 1:
             if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
+        case GEMM_CFG_GATHER_LEAN64:
+            if constexpr (MODE == CONV_FWD || MODE == CONV_DX) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            break;
         case GEMM_CFG_GATHER0 + 2:
             if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;

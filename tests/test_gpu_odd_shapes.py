@@ -6,6 +6,7 @@ import torch
 
 import workloads as wl
 from paper_2002_02885_amd import binding
+from tests import parity_util as pu
 from tests import test_gpu_parity as tp
 from tests.test_plan_check_host import odd_layers
 
@@ -78,3 +79,19 @@ def test_maps_of_more_than_60000_pixels(shape, widths, dtype):
     layers = [("conv3x3", widths[0], 1), ("relu",), ("conv3x3", widths[1], 1), ("tanh",), ("conv3x3", widths[1], 2), ("relu",), ("gap",), ("linear", 7)]
     w = wl.custom(f"large_map_{shape[0]}", 25, dtype, 1, shape, [layers], n_classes=7, steps=1)
     tp._check_f32(w, trials=1) if dtype == wl.F32 else tp._check_bf16(w, trials=1)
+
+
+@pytest.mark.parametrize("dtype,widths", [("bf16", (24, 40, 48)), ("f32", (20, 24, 40))])
+def test_lean_tiles_of_the_general_gather_give_the_same_bits(dtype, widths, monkeypatch):
+    """Forward passes, input gradients of both strides and shortcuts over maps that are no power of two: the form with four
+    workgroups per compute unit against the one with two, several chunks and partial tiles of rows and columns."""
+    w = wl.config5(K=3, B=9, size=23, widths=widths, n_classes=7, steps=2, dtype=dtype)
+    monkeypatch.setenv("PACK_MIN_TILES", "1")       # 128-row tiles, as a larger pack would have
+    monkeypatch.setenv("PACK_LEAN64_CHUNKS", "0")
+    regular = pu.run_gpu(w, 2)
+    monkeypatch.setenv("PACK_LEAN64_CHUNKS", "100000")
+    lean = pu.run_gpu(w, 2)
+    assert any(t == (128, 64, True) for t in lean["tiles"]) and not any(t == (128, 64, True) for t in regular["tiles"])
+    tp._same_bits(regular, lean)
+    for k in range(w.K):
+        assert np.array_equal(regular["grads"][k], lean["grads"][k])

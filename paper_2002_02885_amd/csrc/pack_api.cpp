@@ -680,6 +680,13 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
             return;
         }
     }
+    if (general && mode == CONV_DW && !p->bf16) {
+        // Single precision multiplies at a sixteenth of the bfloat16 rate, and what counts is that rows of 40 or 80 channels are
+        // padded to 64 instead of 128 and that four workgroups share a compute unit: two residual networks of 40 to 320 channels,
+        // 128 x 128 tiles 592 us, 64 x 64 pipelined 615, lean 511.  (bfloat16, bound by the gather: 60 against 79 lean.)
+        emit_gemm_launch(p, db, mode, GEMM_CFG_GATHER_LEAN_DW, probs);
+        return;
+    }
     // The tile shape only partitions the output; the summation order of an element does not
     // depend on it, so a member's bits do not depend on who else is in the launch.  Each problem
     // prefers the shape that multiplies the fewest padding elements (a 64-channel layer wastes
@@ -2077,7 +2084,7 @@ pack_status pack_launch_tile(const pack_t* p, int32_t i, int32_t* tile_rows, int
     const bool gemm = L.kind == L_GEMM;
     *tile_rows = gemm ? GEMM_TILE_M[L.tile_cfg] : 0;
     *tile_cols = gemm ? GEMM_TILE_N[L.tile_cfg] : 0;
-    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_GATHER_LEAN64 || L.tile_cfg == GEMM_CFG_LEAN64);
+    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_GATHER_LEAN64 || L.tile_cfg == GEMM_CFG_GATHER_LEAN_DW || L.tile_cfg == GEMM_CFG_LEAN64);
     return PACK_OK;
 }
 

@@ -286,8 +286,8 @@ hipError_t launch_gather_rows(const void* data, const int32_t* labels_all, const
 // 6, 7: the halo form of the convolution weight gradient (stride 1, stride 2): a tile is 64 output channels
 // x 64 input channels x all nine taps, i.e. 64 x 576 of the [Cout][9 * Cin] gradient
 // 8: the same with 32 input channels per tile (layers whose input channels are a multiple of 32 only; stride 1)
-constexpr int GEMM_TILE_M[19] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64, 64, 128};
-constexpr int GEMM_TILE_N[19] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64, 64, 64};
+constexpr int GEMM_TILE_M[20] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64, 64, 128, 64};
+constexpr int GEMM_TILE_N[20] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64, 64, 64, 64};
 constexpr int GEMM_CFG_SCALAR = 3;
 constexpr int GEMM_CFG_LEAN = 4;     // weight gradients, 128 x 128, short reductions
 constexpr int GEMM_CFG_LEAN64 = 5;   // forward / input gradients, 128 x 64, short reductions
@@ -300,7 +300,8 @@ constexpr int GEMM_CFG_ROWS32 = 10;  // likewise, 256 pixels x 32 columns
 inline bool is_rows_cfg(int cfg) { return cfg == GEMM_CFG_ROWS64 || cfg == GEMM_CFG_ROWS32; }
 constexpr int GEMM_CFG_GATHER0 = 11; // 11..13: configurations 0..2 with the general gather (convolutions of any channel count and map)
 constexpr int GEMM_CFG_GATHER_LEAN64 = 18;   // the lean 128 x 64 form with the general gather
-inline bool is_gather_cfg(int cfg) { return (cfg >= GEMM_CFG_GATHER0 && cfg < GEMM_CFG_GATHER0 + 3) || cfg == GEMM_CFG_GATHER_LEAN64; }
+constexpr int GEMM_CFG_GATHER_LEAN_DW = 19;  // lean 64 x 64 weight gradients with the general gather, fp32
+inline bool is_gather_cfg(int cfg) { return (cfg >= GEMM_CFG_GATHER0 && cfg < GEMM_CFG_GATHER0 + 3) || cfg == GEMM_CFG_GATHER_LEAN64 || cfg == GEMM_CFG_GATHER_LEAN_DW; }
 constexpr int GEMM_CFG_SLIM32 = 14;  // dense products with few outputs, reduction dealt over the waves, 32 x 32 tiles
 constexpr int GEMM_CFG_SLIM64 = 15;  // likewise, 64 x 64 tiles (bfloat16 forward products)
 constexpr int GEMM_CFG_SLIM_MIXED = 17;  // slim problems (32 x 32) and staged ones (64 x 64) in one launch, fp32

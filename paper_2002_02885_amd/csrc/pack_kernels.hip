@@ -248,7 +248,8 @@ __device__ __forceinline__ long long shortcut_row(const GemmProb& p, int row) {
 // tile's pipeline.  Three forms: 128 x 128 weight gradients, whose epilogue stages the accumulators in
 // two halves (three workgroups per compute unit), 128 x 64 forward products / input gradients,
 // whose LDS block is sized for the epilogue's staging tile (four workgroups per compute unit), and
-// 64 x 64 weight gradients updated by an optimiser with state (four).
+// 64 x 64 weight gradients: those updated by an optimiser with state, and single-precision
+// convolutions' with the general gather (four).
 // All multiply the same chunks in the same order as the regular kernels: the bits are the same.
 //
 // Bytes of the workgroup's LDS block: the operand buffers (two of each, one in the lean forms); the
@@ -606,7 +607,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     // in flight per workgroup; a skinny layer has too few workgroups per compute unit to hide that
     // latency by occupancy alone.
     constexpr int ST = LEAN ? 1 : StageCount<BM, BN, BKM, VEC>::value;
-    static_assert(!LEAN || (VEC && BM == 128 && (IS_DW ? BN == 128 : BN == 64)) || (VEC && OPT && BM == 64 && BN == 64), "lean form: aligned operands, 128x128 weight gradients or 128x64 forward / input gradients");
+    static_assert(!LEAN || (VEC && BM == 128 && (IS_DW ? BN == 128 : BN == 64)) || (VEC && IS_DW && BM == 64 && BN == 64), "lean form: aligned operands, 128x128 weight gradients or 128x64 forward / input gradients");
     T(*As)[BM][GA::LDS_LD] = reinterpret_cast<T(*)[BM][GA::LDS_LD]>(As_);
     T(*Bs)[BN][GB::LDS_LD] = reinterpret_cast<T(*)[BN][GB::LDS_LD]>(Bs_);
 
@@ -961,7 +962,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
             }
         }
     }
-    if constexpr (LEAN && IS_DW && !OPT) {
+    if constexpr (LEAN && IS_DW && !OPT && BM == 128) {
         // two passes: the waves that own the upper (then the lower) half of the rows stage their
         // accumulators, then all threads apply that half
         float* const gf = (float*)p.C + (size_t)tr.ks * p.split_stride;
@@ -1339,16 +1340,19 @@ static void launch_gemm_tile(int tile_cfg, const GemmProb* probs, const TileRef*
                 hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
         case GEMM_CFG_GATHER0:
-            if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            if constexpr (MODE >= CONV_FWD && !(MODE == CONV_DW && sizeof(T) == 4)) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
         case GEMM_CFG_GATHER0 + 1:
-            if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            if constexpr (MODE >= CONV_FWD && !(MODE == CONV_DW && sizeof(T) == 4)) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
         case GEMM_CFG_GATHER_LEAN64:
             if constexpr (MODE == CONV_FWD || MODE == CONV_DX) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
+        case GEMM_CFG_GATHER_LEAN_DW:
+            if constexpr (MODE == CONV_DW && sizeof(T) == 4) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            break;
         case GEMM_CFG_GATHER0 + 2:
-            if constexpr (MODE >= CONV_FWD) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
+            if constexpr (MODE >= CONV_FWD && !(MODE == CONV_DW && sizeof(T) == 4)) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
             break;
         default: hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, false>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
     }

@@ -25,6 +25,7 @@ thread_local std::vector<LoadRec>* g_log = nullptr;
 #define PACK_TID (::packk::g_tid)
 inline int pack_uniform(int v) { return v; }
 inline unsigned pack_umulhi(unsigned a, unsigned b) { return (unsigned)(((unsigned long long)a * b) >> 32); }
+inline int pack_mul24(int a, int b) { return (int)((unsigned)(a & 0xffffff) * (unsigned)(b & 0xffffff)); }
 inline u32x4_t buf_load16(const i32x4_t rsrc, unsigned voff, unsigned soff) {
     g_log->push_back(LoadRec{(unsigned long long)(unsigned)rsrc.x | ((unsigned long long)(unsigned)rsrc.y << 32), (unsigned)rsrc.z, voff, soff});
     return u32x4_t{0u, 0u, 0u, 0u};

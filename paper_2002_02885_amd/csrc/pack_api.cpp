@@ -2058,7 +2058,7 @@ pack_status pack_launch_name(const pack_t* p, int32_t i, char* buf, size_t n) {
     const Launch& L = p->plan[i];
     const char* nm = (L.kind == L_GEMM) ? gemm_names[L.mode] : names[L.kind];
     if (L.kind == L_SGD && p->any_opt) nm = "optimizer_update";
-    const bool with_update = p->fused && (L.kind == L_REDUCE || (L.kind == L_GEMM && (L.mode == LIN_DW || L.mode == CONV_DW)));
+    const bool with_update = p->fused && (L.kind == L_REDUCE || (L.kind == L_GEMM && (L.mode == LIN_DW || (L.mode == CONV_DW && !p->any_opt))));
     std::snprintf(buf, n, "%s%s", nm, !with_update ? "" : p->any_opt ? "+opt" : "+sgd");
     return PACK_OK;
 }

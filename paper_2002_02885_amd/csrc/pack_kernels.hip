@@ -1444,6 +1444,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(const ReduceProb* __restric
             if (has_v) sv = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(lr.v + state0 + e));
         }
         int k = 0;
+        if (OPT && p.S == 1) {   // a gradient that is in place already
+            s = *reinterpret_cast<const f32x4_t*>(in);
+            k = 1;
+        }
         for (; k + DEEP <= p.S; k += DEEP) {
             f32x4_t v[DEEP];
 #pragma unroll

@@ -1939,7 +1939,7 @@ static pack_status step_with_workspace(pack_t* p, const void* x_dev, const int32
             }
         }
         oa.params = p->opt_params; oa.master = p->master; oa.m = p->opt_m; oa.v = p->opt_v;
-        lr.opt = &oa;
+        if (p->fused) lr.opt = &oa;   // (with an update of its own the plain products and reductions run, on any of their tiles)
     }
     const bool bf = p->bf16;
     const bool timed_step = p->profiling && (p->profile_step++ % p->profile_every == 0);

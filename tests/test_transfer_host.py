@@ -55,3 +55,8 @@ def test_pinned_memory_goes_with_the_last_pack(driver):
 
 def test_counted_operations_are_those_of_the_layers_without_padding(driver):
     _run(driver, "work")
+
+
+def test_the_separate_update_takes_the_plain_products_and_reductions(driver):
+    """A pack whose update is a launch of its own tells the kernels that produce its gradients nothing of the optimisers."""
+    _run(driver, "separate_update")

@@ -202,8 +202,13 @@ hipError_t launch_seed_blob(float* arena, void*, const BlobSeg* segs, int n_segs
 }
 hipError_t launch_fill_value(float* d, long long n, float v, hipStream_t st) { return enqueue(st, [=] { for (long long i = 0; i < n; ++i) d[i] = v; }); }
 hipError_t launch_fill_zero(void* d, long long n, hipStream_t st) { return enqueue(st, [=] { std::memset(d, 0, n); }); }
+// what the matrix products and reductions of a step were handed over with
+struct GemmCall { int mode, tile_cfg; bool opt; };
+static std::vector<GemmCall> g_gemms;
+static int g_reduces = 0, g_reduces_opt = 0, g_updates = 0;
 // the fused update adds 1 to every weight it owns, some milliseconds after it was enqueued
-hipError_t launch_gemm(int mode, bool, int, const GemmProb* probs, const TileRef* tiles, int n, const void*, char*, const LrTable&, hipStream_t st) {
+hipError_t launch_gemm(int mode, bool, int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void*, char*, const LrTable& lr, hipStream_t st) {
+    g_gemms.push_back({mode, tile_cfg, lr.opt != nullptr});
     if (mode != LIN_DW) return hipSuccess;
     return enqueue(st, [=] {
         usleep(5000);
@@ -220,7 +225,11 @@ hipError_t launch_gemm(int mode, bool, int, const GemmProb* probs, const TileRef
 int conv_dw_halo_cfg(bool, const GemmProb&) { return -1; }
 int conv_rows_halo_cfg(bool, int, const GemmProb&) { return -1; }
 #define NOTHING(name, ...) hipError_t name(__VA_ARGS__) { return hipSuccess; }
-NOTHING(launch_reduce, const ReduceProb*, const int2*, int, const char*, const LrTable&, hipStream_t)
+hipError_t launch_reduce(const ReduceProb*, const int2*, int, const char*, const LrTable& lr, hipStream_t) {
+    ++g_reduces;
+    g_reduces_opt += lr.opt != nullptr;
+    return hipSuccess;
+}
 NOTHING(static_scratch, char**)
 NOTHING(launch_ce, bool, const CeProb*, const int2*, int, const int32_t*, int*, hipStream_t)
 NOTHING(launch_ce_loss, const CeProb*, int, hipStream_t)
@@ -229,7 +238,10 @@ NOTHING(launch_head_loss, const HeadProb*, int, hipStream_t)
 NOTHING(launch_gap, bool, bool, const GapProb*, const int2*, int, hipStream_t)
 NOTHING(launch_shortcut_bwd, bool, const ShortcutProb*, const int2*, int, hipStream_t)
 NOTHING(launch_sgd, float*, const float*, void*, long long, const long long*, int, const LrTable&, hipStream_t)
-NOTHING(launch_opt, float*, const float*, void*, float*, float*, long long, const long long*, const OptStatic*, int, const OptTable&, hipStream_t)
+hipError_t launch_opt(float*, const float*, void*, float*, float*, long long, const long long*, const OptStatic*, int, const OptTable&, hipStream_t) {
+    ++g_updates;
+    return hipSuccess;
+}
 NOTHING(launch_im2col, bool, const Im2colProb*, const int2*, int, const void*, hipStream_t)
 NOTHING(launch_wtranspose, bool, const TransposeProb*, const int2*, int, hipStream_t)
 NOTHING(launch_ceiling_copy, const void*, void*, long long, hipStream_t)
@@ -418,6 +430,43 @@ static void work() {
     }
 }
 
+// the update as a launch of its own: products and reductions are the plain ones, whatever their tiles, and nothing in them
+// is told of the optimisers; applied where the gradients come from, no launch of its own is left
+static void separate_update() {
+    const pack_layer layers[] = {{PACK_LINEAR, 1024, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 300, 0}};
+    for (int batch : {64, 9000})   // (reductions of a few chunks on large tiles; split ones)
+        for (bool fused : {false, true}) {
+            const pack_model_spec m{layers, 3, batch};
+            const pack_input_spec in{batch, 1, 1, 3072, PACK_BF16};
+            const pack_opt_spec momentum{PACK_OPT_MOMENTUM, 0.9f, 0.f, 0.f, 0.f, 0.f};
+            setenv("PACK_MIN_TILES", "1", 1);
+            if (!fused) setenv("PACK_NO_FUSED_UPDATE", "1", 1);
+            pack_t* p = nullptr;
+            EXPECT(pack_create(&in, &m, 1, 0, nullptr, &p) == PACK_OK);
+            EXPECT(pack_set_optimizer(p, 0, &momentum) == PACK_OK);
+            unsetenv("PACK_MIN_TILES");
+            unsetenv("PACK_NO_FUSED_UPDATE");
+            alignas(16) static float x[1];
+            static int32_t y[1];
+            const float lr = 0.f;
+            g_gemms.clear();
+            g_reduces = g_reduces_opt = g_updates = 0;
+            EXPECT(pack_step(p, x, y, &lr) == PACK_OK);
+            bool large = false;
+            for (const GemmCall& c : g_gemms) {
+                if (c.mode != LIN_DW) continue;
+                large = large || GEMM_TILE_M[c.tile_cfg] == 128;
+                if (!fused) EXPECT(!c.opt);
+            }
+            EXPECT(g_updates == !fused);
+            EXPECT(fused ? g_reduces_opt == g_reduces : g_reduces_opt == 0);
+            EXPECT(fused || large);
+            EXPECT((batch == 9000) == (g_reduces > 0));
+            EXPECT(hipStreamSynchronize(nullptr) == hipSuccess);
+            pack_destroy(p);
+        }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -436,6 +485,8 @@ int main(int argc, char** argv) {
         released();
     } else if (s == "work") {
         work();
+    } else if (s == "separate_update") {
+        separate_update();
     } else if (s == "failures") {
         failures();
     } else {

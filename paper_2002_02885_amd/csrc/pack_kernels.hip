@@ -1308,61 +1308,67 @@ __global__ __launch_bounds__(64 * SLIM_WAVES) void gemm_mixed_kernel(const GemmP
     gemm_body<MODE, float, 64, 64, 1, true>(p, tr, As, As + 2 * 64 * TileGeom<float, 64, BK>::LDS_LD, NoLr{});
 }
 
+// One launch of the staged-tile kernels.  A configuration that has no kernel of this product is refused: its tiles were cut
+// for another shape.
+template <int MODE, typename T, int BM, int BN, bool VEC = true, bool LEAN = false, bool GEN = false, bool OPT = false>
+static hipError_t start_gemm(const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const LrArg<MODE, OPT>& lr, hipStream_t st) {
+    hipLaunchKernelGGL((gemm_kernel<MODE, T, BM, BN, 1, VEC, LEAN, GEN, OPT>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, lr);
+    return hipGetLastError();
+}
+
 // dense weight gradients of packs with other optimisers than SGD
 template <typename T>
-static void launch_lin_dw_opt(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const OptArgs& oa, hipStream_t st) {
+static hipError_t launch_lin_dw_opt(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const OptArgs& oa, hipStream_t st) {
     switch (tile_cfg) {
-        case 0: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 128, 128, 1, true, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
-        case 1: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 128, 64, 1, true, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
-        case 2: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 64, 64, 1, true, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
-        case GEMM_CFG_LEAN_OPT: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 64, 64, 1, true, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
-        default: hipLaunchKernelGGL((gemm_kernel<LIN_DW, T, 64, 64, 1, false, false, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, oa); break;
+        case 0: return start_gemm<LIN_DW, T, 128, 128, true, false, false, true>(probs, tiles, n, x, ws, oa, st);
+        case 1: return start_gemm<LIN_DW, T, 128, 64, true, false, false, true>(probs, tiles, n, x, ws, oa, st);
+        case 2: return start_gemm<LIN_DW, T, 64, 64, true, false, false, true>(probs, tiles, n, x, ws, oa, st);
+        case GEMM_CFG_LEAN_OPT: return start_gemm<LIN_DW, T, 64, 64, true, true, false, true>(probs, tiles, n, x, ws, oa, st);
+        case GEMM_CFG_SCALAR: return start_gemm<LIN_DW, T, 64, 64, false, false, false, true>(probs, tiles, n, x, ws, oa, st);
+        default: return hipErrorInvalidValue;
     }
 }
 
 template <int MODE, typename T>
-static void launch_gemm_tile(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const LrTable& lr, hipStream_t st) {
+static hipError_t launch_gemm_tile(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const LrTable& lr, hipStream_t st) {
+    constexpr bool IS_DW = MODE == LIN_DW || MODE == CONV_DW, ROWS = MODE == CONV_FWD || MODE == CONV_DX;
     if constexpr (MODE == LIN_DW) {
-        if (lr.opt) { launch_lin_dw_opt<T>(tile_cfg, probs, tiles, n, x, ws, *lr.opt, st); return; }
+        if (lr.opt) return launch_lin_dw_opt<T>(tile_cfg, probs, tiles, n, x, ws, *lr.opt, st);
     }
     LrArg<MODE, false> la;
-    if constexpr (MODE == LIN_DW || MODE == CONV_DW) la = lr;
+    if constexpr (IS_DW) la = lr;
     switch (tile_cfg) {
-        case 0: hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
-        case 1: hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
-        case 2: hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
-        case GEMM_CFG_LEAN:
-            if constexpr (MODE == LIN_DW || MODE == CONV_DW)
-                hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        case GEMM_CFG_LEAN64:
-            if constexpr (!(MODE == LIN_DW || MODE == CONV_DW))
-                hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        case GEMM_CFG_GATHER0:
-            if constexpr (MODE >= CONV_FWD && !(MODE == CONV_DW && sizeof(T) == 4)) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 128, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        case GEMM_CFG_GATHER0 + 1:
-            if constexpr (MODE >= CONV_FWD && !(MODE == CONV_DW && sizeof(T) == 4)) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        case GEMM_CFG_GATHER_LEAN64:
-            if constexpr (MODE == CONV_FWD || MODE == CONV_DX) hipLaunchKernelGGL((gemm_kernel<MODE, T, 128, 64, 1, true, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        case GEMM_CFG_GATHER_LEAN_DW:
-            if constexpr (MODE == CONV_DW && sizeof(T) == 4) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, true, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        case GEMM_CFG_GATHER0 + 2:
-            if constexpr (MODE >= CONV_FWD && !(MODE == CONV_DW && sizeof(T) == 4)) hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, true, false, true>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la);
-            break;
-        default: hipLaunchKernelGGL((gemm_kernel<MODE, T, 64, 64, 1, false>), dim3(n), dim3(256), 0, st, probs, tiles, x, ws, la); break;
+        case 0: return start_gemm<MODE, T, 128, 128>(probs, tiles, n, x, ws, la, st);
+        case 1: return start_gemm<MODE, T, 128, 64>(probs, tiles, n, x, ws, la, st);
+        case 2: return start_gemm<MODE, T, 64, 64>(probs, tiles, n, x, ws, la, st);
+        case GEMM_CFG_SCALAR: return start_gemm<MODE, T, 64, 64, false>(probs, tiles, n, x, ws, la, st);
+        default: break;
     }
+    if constexpr (IS_DW) {
+        if (tile_cfg == GEMM_CFG_LEAN) return start_gemm<MODE, T, 128, 128, true, true>(probs, tiles, n, x, ws, la, st);
+    } else {
+        if (tile_cfg == GEMM_CFG_LEAN64) return start_gemm<MODE, T, 128, 64, true, true>(probs, tiles, n, x, ws, la, st);
+    }
+    if constexpr (ROWS || (MODE == CONV_DW && sizeof(T) == 2)) {
+        switch (tile_cfg) {
+            case GEMM_CFG_GATHER0: return start_gemm<MODE, T, 128, 128, true, false, true>(probs, tiles, n, x, ws, la, st);
+            case GEMM_CFG_GATHER0 + 1: return start_gemm<MODE, T, 128, 64, true, false, true>(probs, tiles, n, x, ws, la, st);
+            case GEMM_CFG_GATHER0 + 2: return start_gemm<MODE, T, 64, 64, true, false, true>(probs, tiles, n, x, ws, la, st);
+            default: break;
+        }
+    }
+    if constexpr (ROWS) {
+        if (tile_cfg == GEMM_CFG_GATHER_LEAN64) return start_gemm<MODE, T, 128, 64, true, true, true>(probs, tiles, n, x, ws, la, st);
+    }
+    if constexpr (MODE == CONV_DW && sizeof(T) == 4) {
+        if (tile_cfg == GEMM_CFG_GATHER_LEAN_DW) return start_gemm<MODE, T, 64, 64, true, true, true>(probs, tiles, n, x, ws, la, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int MODE>
 static hipError_t launch_gemm_mode(bool bf16, int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, char* ws, const LrTable& lr, hipStream_t st) {
-    if (bf16) launch_gemm_tile<MODE, bf16_t>(tile_cfg, probs, tiles, n, x, ws, lr, st);
-    else launch_gemm_tile<MODE, float>(tile_cfg, probs, tiles, n, x, ws, lr, st);
-    return hipGetLastError();
+    return bf16 ? launch_gemm_tile<MODE, bf16_t>(tile_cfg, probs, tiles, n, x, ws, lr, st) : launch_gemm_tile<MODE, float>(tile_cfg, probs, tiles, n, x, ws, lr, st);
 }
 
 template <int MODE, typename T>

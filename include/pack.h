@@ -389,7 +389,8 @@ pack_status pack_launch_flops(const pack_t* p, int32_t i, double* flops);
 /* Algorithmic bytes of launch i if it is a matrix-product launch: every operand read once (an operand
  * that several members share, the input batch of Section 3.4 or its im2col copy, once for the whole
  * launch), every result written once, plus, where the update is applied in the same kernel, the
- * weights read and written and their bf16 copy written (0 for other launches).  bytes: host. */
+ * weights and the state of the optimisers now in force read and written and the weights' bf16 copy
+ * written (0 for other launches).  bytes: host. */
 pack_status pack_launch_bytes(const pack_t* p, int32_t i, double* bytes);
 
 /* Tile shape of launch i, for tests and measurements that need to know which kernel form the planner

@@ -18,6 +18,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace packk;
@@ -110,7 +111,9 @@ struct Launch {
     size_t map_off = 0;     // byte offset of the tile / block map
     int n = 0;              // grid size
     double flops = 0.0;     // GEMM launches: 2 * rows * columns * reduction, summed over the launch's problems
-    double bytes = 0.0;     // GEMM launches: operands once + results once (+ the fused update's weight traffic)
+    double bytes = 0.0;     // GEMM launches: operands once + results once (+ the weights and copies a fused update reads and writes)
+    std::vector<std::pair<int, double>> updated;   // weights a fused update of this launch applies to, by member: their state's bytes
+                                                   // depend on the optimiser in force when the bytes are asked for
 };
 
 }  // namespace
@@ -542,8 +545,10 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
         if (mode == LIN_DW || mode == CONV_DW) {
             const double splits = std::max(1, (g.Kd + g.ksplit - 1) / g.ksplit);
             if (!(g.flags & F_UPDATE) || (g.flags & F_KEEP_G)) L.bytes += out * 4.0 * splits;      // gradient (or partials) written
-            if (g.flags & F_UPDATE)                                                                 // W and its state read + written, bf16 copy written
-                L.bytes += out * (8.0 * (1 + (p->opt[g.member].kind != PACK_OPT_SGD) + (p->opt[g.member].kind == PACK_OPT_ADAM)) + (g.upd_shadow ? 2.0 : 0.0));
+            if (g.flags & F_UPDATE) {                                                               // W read + written, bf16 copy written
+                L.bytes += out * (8.0 + (g.upd_shadow ? 2.0 : 0.0));
+                L.updated.emplace_back(g.member, out);
+            }
         }
     }
     for (const auto& kv : shared_a) L.bytes += kv.second * esz;
@@ -2073,7 +2078,12 @@ pack_status pack_launch_flops(const pack_t* p, int32_t i, double* flops) {
 pack_status pack_launch_bytes(const pack_t* p, int32_t i, double* bytes) {
     if (!p || !bytes) return fail(PACK_EINVAL, "null argument");
     if (i < 0 || i >= (int32_t)p->plan.size()) return fail(PACK_EINVAL, "launch index out of range");
-    *bytes = p->plan[i].bytes;
+    const Launch& L = p->plan[i];
+    *bytes = L.bytes;
+    for (const auto& u : L.updated) {   // state read + written
+        const int kind = p->opt[u.first].kind;
+        *bytes += u.second * 8.0 * ((kind != PACK_OPT_SGD) + (kind == PACK_OPT_ADAM));
+    }
     return PACK_OK;
 }
 

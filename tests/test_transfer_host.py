@@ -60,3 +60,7 @@ def test_counted_operations_are_those_of_the_layers_without_padding(driver):
 def test_the_separate_update_takes_the_plain_products_and_reductions(driver):
     """A pack whose update is a launch of its own tells the kernels that produce its gradients nothing of the optimisers."""
     _run(driver, "separate_update")
+
+
+def test_counted_bytes_of_the_update_follow_the_optimisers_in_force(driver):
+    _run(driver, "update_bytes")

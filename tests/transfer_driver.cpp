@@ -467,6 +467,42 @@ static void separate_update() {
         }
 }
 
+// algorithmic bytes of the launch that applies the optimisers: those in force, whatever the order in which they were chosen
+static void update_bytes() {
+    const pack_layer layers[] = {{PACK_LINEAR, 48, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 40, 0}};
+    const double params = 64 * 48 + 48 * 40;   // (weights; biases are not counted)
+    for (int dtype : {PACK_F32, PACK_BF16}) {
+        const pack_model_spec m{layers, 3, 4}, models[3] = {m, m, m};
+        const pack_input_spec in{4, 1, 1, 64, dtype};
+        pack_t* p = nullptr;
+        EXPECT(pack_create(&in, models, 3, 0, nullptr, &p) == PACK_OK);
+        auto bytes = [&] {
+            double sum = 0.0;
+            for (int i = 0; i < pack_num_launches(p); ++i) {
+                char name[64];
+                double b = 0.0;
+                EXPECT(pack_launch_name(p, i, name, sizeof name) == PACK_OK && pack_launch_bytes(p, i, &b) == PACK_OK);
+                if (std::string(name).rfind("gemm_lin_dw", 0) == 0) sum += b;
+            }
+            return sum;
+        };
+        auto choose = [&](int k, int kind) {
+            const pack_opt_spec o{kind, 0.9f, 0.1f, 0.9f, 0.999f, 1e-8f};
+            EXPECT(pack_set_optimizer(p, k, &o) == PACK_OK);
+        };
+        const double sgd = bytes();
+        for (int k : {1, 0, 2}) choose(k, PACK_OPT_MOMENTUM);
+        EXPECT(bytes() == sgd + 3 * params * (4 + 8));     // (packs with such members store their gradients too)
+        for (int k : {2, 0, 1}) choose(k, PACK_OPT_ADAM);
+        EXPECT(bytes() == sgd + 3 * params * (4 + 16));
+        choose(1, PACK_OPT_SGD);
+        EXPECT(bytes() == sgd + 3 * params * 4 + 2 * params * 16);
+        choose(0, PACK_OPT_ADAGRAD);
+        EXPECT(bytes() == sgd + 3 * params * 4 + params * (8 + 16));
+        pack_destroy(p);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -487,6 +523,8 @@ int main(int argc, char** argv) {
         work();
     } else if (s == "separate_update") {
         separate_update();
+    } else if (s == "update_bytes") {
+        update_bytes();
     } else if (s == "failures") {
         failures();
     } else {

@@ -29,7 +29,7 @@ def check_no_spills(report: str) -> int:
         if m:
             name, agprs = m.group(1), None
             continue
-        if name is None or not any(k in name for k in ("gemm_kernel", "gemm_mixed_kernel", "conv_dw_halo_kernel", "conv_rows_halo_kernel")):
+        if name is None or not any(k in name for k in ("gemm_kernel", "gemm_mixed_kernel", "gemm_shares_kernel", "conv_dw_halo_kernel", "conv_rows_halo_kernel")):
             continue
         m = re.search(r"AGPRs: (\d+)", line)
         if m:
@@ -42,7 +42,7 @@ def check_no_spills(report: str) -> int:
             if not t and agprs == 0:
                 want = 0   # these keep their accumulator blocks in ordinary registers (no more than five, or four, per wave)
             r = re.search(r"conv_rows_halo_kernelILi\d+E[tf]Li\d+ELi\d+ELi(\d+)E", name)
-            if "gemm_mixed_kernel" in name:   # (slim form, two blocks, and a staged 64 x 64 tile, one: wherever they lie)
+            if "gemm_mixed_kernel" in name or "gemm_shares_kernel" in name:   # (slim form, two blocks, and a staged 64 x 64 tile, one; sums of shares: wherever they lie)
                 want = agprs
             if r:   # two blocks of pixels x TN blocks of columns per wave, in AGPRs or all in ordinary registers
                 want = 0 if agprs == 0 else 32 * int(r.group(1))

@@ -71,13 +71,13 @@ template <class C> PACK_HD inline int slim_frag_rc16(int lane, int block, int kk
     return (kk + (lane >> 5) * C::V + 4 * h + ((lane & 15) >> 2)) * C::LD_RC + (block * 32 + (((lane >> 4) & 1) ^ (PACK_HALO_PLANT == 12)) * 16 + (lane & 3) * 4) * 2;
 }
 
-// Which dense products take the slim form: those of at most 32 tiles of 64 x 64 (a batch of 256 rows by 512 outputs, say).
-// The rule looks at the problem's own shape only, since the form adds the reduction up in another order than the staged
-// tiles and a member's bits must not depend on who else is in the pack.  Alone or with a few others such a product leaves
-// most compute units idle and its time is the chain of its chunks; with many others both forms take as long.  Measured,
-// slim against staged: 2 x (32 x 128 over 784, fp32) 6.6 against 18.5 us, 3 x (200 x 304 over 784, fp32) 7.6 / 15,
-// 6 x (64 x 504 over 1032, bf16) 4.9 / 11.7, 8 x (48 x 512 over 3072, bf16) 8.0 / 19.9, 32 x (64 x 512 over 3072, bf16)
-// 25 / 25 (64 x 64 tiles); beyond the line 8 x (256 x 1024 over 3072, bf16) 33 / 28.
+// Which dense products are added up in the order of the slim form: those of at most 32 tiles of 64 x 64 (a batch of 256 rows
+// by 512 outputs, say).  The rule looks at the problem's own shape only, since a member's bits must not depend on who else is
+// in the pack; whether the slim form itself runs or staged tiles that follow its order is the launch's choice
+// (add_gemm_launch).  Alone or with a few others such a product leaves most compute units idle and its time is the chain of
+// its chunks.  Measured, slim against plain staged: 2 x (32 x 128 over 784, fp32) 6.6 against 18.5 us, 3 x (200 x 304 over
+// 784, fp32) 7.6 / 15, 6 x (64 x 504 over 1032, bf16) 4.9 / 11.7, 8 x (48 x 512 over 3072, bf16) 8.0 / 19.9; beyond the line
+// 8 x (256 x 1024 over 3072, bf16) 33 / 28.
 constexpr int SLIM_MAX_TILES = 32;
 inline bool slim_ok(const GemmProb& g) {
     if (g.flags & (F_RES_ID | F_RES_DOWN | F_SC_ID | F_SC_DOWN | F_ROWMAP)) return false;

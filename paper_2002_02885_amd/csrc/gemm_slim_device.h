@@ -6,15 +6,18 @@
 // Here a workgroup owns 32 x 32 outputs (64 x 64 where a launch has enough of them) and its eight waves share the chunks of
 // the reduction: a wave loads a chunk of 128 bytes of every row, turns it in its own part of LDS, which
 // no other wave touches, so that no wave waits for another inside the loop, and adds up its chunks in its own accumulators;
-// the eight sums are added in pairs at the end, in a fixed order.  The loads of the next chunk are requested as soon as the registers of
+// the eight sums are added in order at the end.  The loads of the next chunk are requested as soon as the registers of
 // this one are free.  (Operands straight from memory in the layout of the matrix instructions, without LDS, touch 32 lines
 // per load and stop at 30 GB/s per compute unit, against 70 this way.)
-// The order of a sum depends on the reduction's length only, whatever the tile.
+// The order of a sum depends on the reduction's length only, whatever the tile, and staged tiles can follow it (gemm_body, SHARES).
 #pragma once
 #include "gemm_slim.h"
 #include "pack_device.h"
 
 namespace packk {
+
+// accumulators of a wave, dealt the steps of its chunks in turn
+template <typename T> constexpr int SLIM_SETS = sizeof(T) == 4 ? 2 : 1;
 
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s_t* lds_v4s_ptr;
@@ -41,11 +44,11 @@ __device__ __forceinline__ void slim_body(const GemmProb& p, const TileRef& tr, 
 #pragma unroll
     for (int i = 0; i < NB; ++i) vb[i] = slim_b_base<C>(col0, Q, ldb, lane, i);
 
-    // Two sums per wave, of the even and the odd steps of its chunks: half the rounding of one sum, and two independent
-    // chains of matrix instructions.
-    f32x16_t acc[2][TM][TN];
+    // fp32: two sums per wave, of the even and the odd steps of its chunks, which halves the rounding
+    constexpr int SETS = SLIM_SETS<T>;
+    f32x16_t acc[SETS][TM][TN];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < SETS; ++s)
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -75,7 +78,7 @@ __device__ __forceinline__ void slim_body(const GemmProb& p, const TileRef& tr, 
     auto multiply = [&]() {
 #pragma unroll
         for (int kk = 0; kk < C::KC; kk += 2 * V) {
-            f32x16_t(&sum)[TM][TN] = acc[(kk / (2 * V)) & 1];
+            f32x16_t(&sum)[TM][TN] = acc[(kk / (2 * V)) % SETS];
             u32x4_t fa[TM], fb[TN];
 #pragma unroll
             for (int a = 0; a < TM; ++a) fa[a] = *reinterpret_cast<const u32x4_t*>(la + slim_frag_kc<C>(lane, a, kk));
@@ -130,7 +133,7 @@ __device__ __forceinline__ void slim_body(const GemmProb& p, const TileRef& tr, 
 #pragma unroll
         for (int b = 0; b < TN; ++b)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) sum[wave][a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)][b * 32 + (lane & 31)] = acc[0][a][b][e] + acc[1][a][b][e];
+            for (int e = 0; e < 16; ++e) sum[wave][a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)][b * 32 + (lane & 31)] = SETS == 2 ? acc[0][a][b][e] + acc[SETS - 1][a][b][e] : acc[0][a][b][e];
     // what the tail reads from memory comes back under the exchange
     constexpr int G = C::BN / 4, ITEMS = C::BM * G, NIT = (ITEMS + 64 * NW - 1) / (64 * NW);
     const int ldc = p.ldc, cols = stored_cols(p);
@@ -177,13 +180,11 @@ __device__ __forceinline__ void slim_body(const GemmProb& p, const TileRef& tr, 
         f32x4_t part[NW];
 #pragma unroll
         for (int w = 0; w < NW; ++w) part[w] = *reinterpret_cast<const f32x4_t*>(&sum[w][r][c]);
-#pragma unroll
-        for (int d = 1; d < NW; d *= 2)   // in pairs: neighbours, then pairs of them
-#pragma unroll
-            for (int w = 0; w < NW; w += 2 * d)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) part[w][j] += part[w + d][j];
         f32x4_t v = part[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w)   // in order (shares of nothing add zeros)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] += part[w][j];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if constexpr (FWD) {

@@ -558,6 +558,29 @@ void emit_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, int cfg, const std
 
 void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vector<GemmProb>& probs, bool general);
 
+// The staged tiles a launch of problems in the slim form's order takes, or -1 for the slim form itself.  That wins while its
+// 32 x 32 tiles find room at once, two to a compute unit, and with long reductions, where a tile is many round trips of
+// which it makes an eighth, up to 1024.  Step times, slim / staged, us: 4 members 256-512-512 over 784 (512 tiles a
+// product) 44 / 47 (bf16), 69 / 89 (fp32); 5 members 54 / 49, 86 / 91; 8 members 56 / 51, 116 / 108; 24 members 128-256-256
+// (768) 51 / 46, 87 / 81; over 3072 indices 6 members 128-1024 (768) 82 / 85, 156 / 190, 8 (1024) 95 / 96, 194 / 211, 16
+// 210 / 196, 358 / 343.
+// Larger tiles once they fill the units: 64 x 64, lean 128 x 64 and 128 x 128, bf16: 16 members 256-512-512 74, 76, 85; 24:
+// 106, 97, 103; 48: 180, 158, 161; 64: 265, 238, 224; fp32: 24 members 257, 267; 32: 301, 283; 64: 584, 542 (128 x 128 does not
+// fit the registers).  Rows of at most 64 waste half of a 128 x 64 tile: 32 members 64-2048-2048, 607, 644, 592; fp32 815, 1083.
+int shares_cfg(bool bf16, const std::vector<GemmProb>& slim) {
+    const size_t tiles = count_tiles(slim, GEMM_CFG_SLIM32);
+    const int kc = bf16 ? 64 : 32;   // reduction indices per chunk
+    double chunks = 0, work64 = 0, work128x64 = 0;
+    for (const GemmProb& g : slim) {
+        chunks += (double)((g.R + 31) / 32) * ((g.Q + 31) / 32) * ((g.Kd + kc - 1) / kc);
+        work64 += padded_work(g, GEMM_CFG_SHARES64);
+        work128x64 += padded_work(g, GEMM_CFG_SHARES128X64);
+    }
+    if (tiles <= (chunks >= 40.0 * tiles ? 1024 : bf16 ? 512 : 640)) return -1;
+    if (bf16 && count_tiles(slim, GEMM_CFG_SHARES128) >= 512) return GEMM_CFG_SHARES128;
+    return count_tiles(slim, GEMM_CFG_SHARES128X64) >= (bf16 ? 384 : 512) && work128x64 < 1.25 * work64 ? GEMM_CFG_SHARES128X64 : GEMM_CFG_SHARES64;
+}
+
 void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<GemmProb>& all_probs_in) {
     // PACK_GENERAL_TAIL: every forward / input-gradient tile takes the general form of the tail, for the test that
     // compares it bit for bit with the form whole tiles of the plain cases take
@@ -618,12 +641,16 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
     }
     if ((mode == LIN_FWD || mode == LIN_DX) && !std::getenv("PACK_MIN_TILES")) {
         // (PACK_MIN_TILES asks for staged tiles)
-        // products with few outputs: the reduction shared by the waves of a workgroup (whether a problem does: slim_ok).
-        // The tile is the launch's choice, since the order of a sum does not depend on it: 32 x 32 spreads a launch over the
-        // compute units, 64 x 64 reads half as much per product, and is built for the only products that are bound by that.
+        // products with few outputs, in the order of the slim form (whether a problem is: slim_ok).  The kernel and its tile are
+        // the launch's choice, since the order does not depend on them.
         std::vector<GemmProb> slim, rest;
         for (const GemmProb& g : probs) ((g.flags & F_SLIM) ? slim : rest).push_back(g);
-        if (!slim.empty()) {
+        const int shares = shares_cfg(p->bf16, slim);
+        if (shares >= 0) {
+            emit_gemm_launch(p, db, mode, shares, slim);
+        } else if (!slim.empty()) {
+            // 32 x 32 tiles spread a launch over the compute units, 64 x 64 read half as much per product, and are built for
+            // the only products that are bound by that
             const bool big = p->bf16 && mode == LIN_FWD && count_tiles(slim, GEMM_CFG_SLIM32) >= SLIM64_MIN_TILES32;
             // those of the same size that keep the staged order ride along (slim_flag; they take longest and start first)
             std::vector<GemmProb> both, others;
@@ -1726,6 +1753,7 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
                 n_probs = std::max(n_probs, tr.prob + 1);
                 GemmProb g = probs[tr.prob];
                 const int BMc = tile_rows(L.tile_cfg, g), BNc = tile_cols(L.tile_cfg, g);
+                if (is_shares_cfg(L.tile_cfg)) g.flags &= ~F_SLIM;   // (loads like the other staged tiles)
                 if (g.flags & F_A_INPUT) g.A = (const char*)x_fake + g.x_off;
                 if (g.flags & F_B_INPUT) g.B = (const char*)x_fake + g.x_off;
                 unsigned long long alo, ahi, blo, bhi;
@@ -2094,7 +2122,7 @@ pack_status pack_launch_tile(const pack_t* p, int32_t i, int32_t* tile_rows, int
     const bool gemm = L.kind == L_GEMM;
     *tile_rows = gemm ? GEMM_TILE_M[L.tile_cfg] : 0;
     *tile_cols = gemm ? GEMM_TILE_N[L.tile_cfg] : 0;
-    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_GATHER_LEAN64 || L.tile_cfg == GEMM_CFG_GATHER_LEAN_DW || L.tile_cfg == GEMM_CFG_LEAN64);
+    *lean = gemm && (L.tile_cfg == GEMM_CFG_LEAN || L.tile_cfg == GEMM_CFG_LEAN_OPT || L.tile_cfg == GEMM_CFG_GATHER_LEAN64 || L.tile_cfg == GEMM_CFG_GATHER_LEAN_DW || L.tile_cfg == GEMM_CFG_LEAN64 || L.tile_cfg == GEMM_CFG_SHARES128X64);
     return PACK_OK;
 }
 

@@ -65,7 +65,7 @@ enum GemmFlags : int {
                               // that compares it with the form whole tiles of the plain cases take)
     F_GATHER = 262144, // convolution whose chunks of the reduction may straddle taps, images or rows of any width:
                        // operands come through the general gather (GEMM_CFG_GATHER0 ..)
-    F_SLIM = 1048576,  // dense forward product or input gradient in the slim form (GEMM_CFG_SLIM32, GEMM_CFG_SLIM64)
+    F_SLIM = 1048576,  // dense forward product or input gradient in the order of the slim form (GEMM_CFG_SLIM32 .., GEMM_CFG_SHARES64 ..)
     F_PAD_OUT = 524288 // output rows are stored in whole groups of 8 columns (ldc a multiple of 8, at least Q rounded
                        // up): the columns from Q on hold zeros and are written as such
 };
@@ -286,8 +286,8 @@ hipError_t launch_gather_rows(const void* data, const int32_t* labels_all, const
 // 6, 7: the halo form of the convolution weight gradient (stride 1, stride 2): a tile is 64 output channels
 // x 64 input channels x all nine taps, i.e. 64 x 576 of the [Cout][9 * Cin] gradient
 // 8: the same with 32 input channels per tile (layers whose input channels are a multiple of 32 only; stride 1)
-constexpr int GEMM_TILE_M[20] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64, 64, 128, 64};
-constexpr int GEMM_TILE_N[20] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64, 64, 64, 64};
+constexpr int GEMM_TILE_M[23] = {128, 128, 64, 64, 128, 128, 64, 64, 64, 256, 256, 128, 128, 64, 32, 64, 64, 64, 128, 64, 64, 128, 128};
+constexpr int GEMM_TILE_N[23] = {128, 64, 64, 64, 128, 64, 576, 576, 288, 64, 32, 128, 64, 64, 32, 64, 64, 64, 64, 64, 64, 64, 128};
 constexpr int GEMM_CFG_SCALAR = 3;
 constexpr int GEMM_CFG_LEAN = 4;     // weight gradients, 128 x 128, short reductions
 constexpr int GEMM_CFG_LEAN64 = 5;   // forward / input gradients, 128 x 64, short reductions
@@ -306,6 +306,10 @@ constexpr int GEMM_CFG_SLIM32 = 14;  // dense products with few outputs, reducti
 constexpr int GEMM_CFG_SLIM64 = 15;  // likewise, 64 x 64 tiles (bfloat16 forward products)
 constexpr int GEMM_CFG_SLIM_MIXED = 17;  // slim problems (32 x 32) and staged ones (64 x 64) in one launch, fp32
 constexpr int GEMM_CFG_LEAN_OPT = 16;   // dense weight gradients with another optimiser than SGD, short reductions
+constexpr int GEMM_CFG_SHARES64 = 20;   // problems of the slim form on staged tiles of 64 x 64, in the slim form's order
+constexpr int GEMM_CFG_SHARES128X64 = 21;    // likewise, lean tiles of 128 x 64
+constexpr int GEMM_CFG_SHARES128 = 22;       // likewise, 128 x 128, bfloat16
+inline bool is_shares_cfg(int cfg) { return cfg >= GEMM_CFG_SHARES64 && cfg <= GEMM_CFG_SHARES128; }
 inline bool is_slim_cfg(int cfg) { return cfg == GEMM_CFG_SLIM32 || cfg == GEMM_CFG_SLIM64; }
 // side of the tiles a problem of a launch is cut into
 inline int tile_rows(int cfg, const GemmProb& g) { return cfg == GEMM_CFG_SLIM_MIXED && (g.flags & F_SLIM) ? 32 : GEMM_TILE_M[cfg]; }

@@ -590,7 +590,9 @@ using LrArg = typename std::conditional<MODE == LIN_DW || MODE == CONV_DW, typen
 
 // OPT (dense weight gradients of packs in which some member's optimiser keeps state): F_UPDATE applies the member's own
 // optimiser, whose state lies like the weights.
-template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false, bool OPT = false>
+// SHARES (dense forward products and input gradients): the order of the slim form, for its problems in launches large enough
+// to fill the compute units with staged tiles (add_gemm_launch).
+template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false, bool OPT = false, bool SHARES = false>
 __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, T* __restrict__ As_, T* __restrict__ Bs_, const LrArg<MODE, OPT>& rates) {
     static_assert(!OPT || MODE == LIN_DW, "dense weight gradients");
     float lrk = 0.f;
@@ -607,7 +609,9 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     // in flight per workgroup; a skinny layer has too few workgroups per compute unit to hide that
     // latency by occupancy alone.
     constexpr int ST = LEAN ? 1 : StageCount<BM, BN, BKM, VEC>::value;
-    static_assert(!LEAN || (VEC && BM == 128 && (IS_DW ? BN == 128 : BN == 64)) || (VEC && IS_DW && BM == 64 && BN == 64), "lean form: aligned operands, 128x128 weight gradients or 128x64 forward / input gradients");
+    static_assert(!LEAN || (VEC && BM == 128 && (IS_DW ? BN == 128 : BN == 64)) || (VEC && IS_DW && BM == 64 && BN == 64),
+                  "lean form: aligned operands; 128x128 or 64x64 weight gradients, 128x64 forward / input gradients");
+    static_assert(!SHARES || (VEC && BKM == 1 && (MODE == LIN_FWD || MODE == LIN_DX)), "shares: dense products, chunks of 128 bytes");
     T(*As)[BM][GA::LDS_LD] = reinterpret_cast<T(*)[BM][GA::LDS_LD]>(As_);
     T(*Bs)[BN][GB::LDS_LD] = reinterpret_cast<T(*)[BN][GB::LDS_LD]>(Bs_);
 
@@ -627,6 +631,24 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
     float bias_grad = 0.f;
+
+    // SHARES: up to eight shares of neighbouring chunks are summed one after the other (acc; fp32: the odd steps apart, in odd)
+    // and added to total in that order, as the slim form's waves do and its tail does (gemm_slim_device.h).
+    constexpr bool ODD = SHARES && SLIM_SETS<T> == 2;
+    f32x16_t odd[TM][TN], total[TM][TN];
+    const int per = SHARES ? (nk + SLIM_WAVES - 1) / SLIM_WAVES : 0;
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) f(a, b, e);
+    };
+    if constexpr (SHARES) each([&](int a, int b, int e) { total[a][b][e] = odd[a][b][e] = 0.f; });
+    auto add_share = [&]() {
+        each([&](int a, int b, int e) { total[a][b][e] += ODD ? acc[a][b][e] + odd[a][b][e] : acc[a][b][e]; });
+    };
 
     u32x4_t ra[ST][GA::NREG], rb[ST][GB::NREG];
     Fetcher<MODE, T, true, BM, BK, VEC, GEN> fa;
@@ -679,7 +701,8 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
         // registers, multiply
         fa.fetch(p, kbeg, kend, ra[0]);
         fb.fetch(p, kbeg, kend, rb[0]);
-        for (int it = 0; it < nk; ++it) {
+        auto chunk = [&](auto FIRST, const int it) {   // FIRST: the first of a share, whose sums begin with it
+            constexpr bool first = decltype(FIRST)::value;
             wait_stage<0>(ra[0]);
             wait_stage<0>(rb[0]);
             lds_barrier();
@@ -710,6 +733,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
             }
 #pragma unroll
             for (int kk = 0; kk < BK; kk += 2 * V) {
+                f32x16_t(&sum)[TM][TN] = (ODD && ((kk / (2 * V)) & 1)) ? odd : acc;
                 u32x4_t fra[TM], frb[TN];
 #pragma unroll
                 for (int a = 0; a < TM; ++a)
@@ -721,17 +745,29 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
                 for (int a = 0; a < TM; ++a)
 #pragma unroll
                     for (int b = 0; b < TN; ++b) {
+                        const f32x16_t before = (first && kk < (ODD ? 4 : 2) * V) ? f32x16_t{} : sum[a][b];
                         if constexpr (sizeof(T) == 2) {
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(bf16x8_t, fra[a]), __builtin_bit_cast(bf16x8_t, frb[b]), acc[a][b], 0, 0, 0);
+                            sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                __builtin_bit_cast(bf16x8_t, fra[a]), __builtin_bit_cast(bf16x8_t, frb[b]), before, 0, 0, 0);
                         } else {
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].x), __uint_as_float(frb[b].x), acc[a][b], 0, 0, 0);
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].y), __uint_as_float(frb[b].y), acc[a][b], 0, 0, 0);
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].z), __uint_as_float(frb[b].z), acc[a][b], 0, 0, 0);
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].w), __uint_as_float(frb[b].w), acc[a][b], 0, 0, 0);
+                            sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].x), __uint_as_float(frb[b].x), before, 0, 0, 0);
+                            sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].y), __uint_as_float(frb[b].y), sum[a][b], 0, 0, 0);
+                            sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].z), __uint_as_float(frb[b].z), sum[a][b], 0, 0, 0);
+                            sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fra[a].w), __uint_as_float(frb[b].w), sum[a][b], 0, 0, 0);
                         }
                     }
             }
+        };
+        if constexpr (SHARES) {
+            for (int it = 0; it < nk;) {
+                const int end = min(nk, it + per);
+                chunk(std::true_type{}, it);
+                while (++it < end) chunk(std::false_type{}, it);
+                add_share();
+            }
+            each([&](int a, int b, int e) { acc[a][b][e] = total[a][b][e]; });
+        } else {
+            for (int it = 0; it < nk; ++it) chunk(std::false_type{}, it);
         }
         // the request beyond the last chunk still targets the stage registers
         wait_stage<0>(ra[0]);
@@ -761,6 +797,12 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     //     buffer par ^ 1 while those MFMAs run: the wait for global memory and the LDS store
     //     latency hide under the multiplication instead of standing between two barriers;
     //   - the remaining MFMA steps.
+    int left = per;   // SHARES: chunks to come of this share
+    auto end_share = [&]() {
+        add_share();
+        each([&](int a, int b, int e) { acc[a][b][e] = odd[a][b][e] = 0.f; });
+        left = per;
+    };
     auto chunk = [&](auto S, auto PAR, const int it) {
         constexpr int s = decltype(S)::value;
         constexpr int par = decltype(PAR)::value;
@@ -792,6 +834,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
         }
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 2 * V) {
+            f32x16_t(&sum)[TM][TN] = (ODD && ((kk / (2 * V)) & 1)) ? odd : acc;
             u32x4_t fa[TM], fb[TN];
 #pragma unroll
             for (int a = 0; a < TM; ++a)
@@ -804,13 +847,13 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
 #pragma unroll
                 for (int b = 0; b < TN; ++b) {
                     if constexpr (sizeof(T) == 2) {
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            __builtin_bit_cast(bf16x8_t, fa[a]), __builtin_bit_cast(bf16x8_t, fb[b]), acc[a][b], 0, 0, 0);
+                        sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8_t, fa[a]), __builtin_bit_cast(bf16x8_t, fb[b]), sum[a][b], 0, 0, 0);
                     } else {
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].x), __uint_as_float(fb[b].x), acc[a][b], 0, 0, 0);
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].y), __uint_as_float(fb[b].y), acc[a][b], 0, 0, 0);
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].z), __uint_as_float(fb[b].z), acc[a][b], 0, 0, 0);
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].w), __uint_as_float(fb[b].w), acc[a][b], 0, 0, 0);
+                        sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].x), __uint_as_float(fb[b].x), sum[a][b], 0, 0, 0);
+                        sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].y), __uint_as_float(fb[b].y), sum[a][b], 0, 0, 0);
+                        sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].z), __uint_as_float(fb[b].z), sum[a][b], 0, 0, 0);
+                        sum[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[a].w), __uint_as_float(fb[b].w), sum[a][b], 0, 0, 0);
                     }
                 }
             if (kk == 0) {
@@ -821,6 +864,9 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
                 stash_tile<MODE, T, true, BM, BK, VEC>(&As[par ^ 1][0][0], ra[sn]);
                 stash_tile<MODE, T, false, BN, BK, VEC>(&Bs[par ^ 1][0][0], rb[sn]);
             }
+        }
+        if constexpr (SHARES) {
+            if (--left == 0) end_share();
         }
     };
     using std::integral_constant;
@@ -847,6 +893,10 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
         }
     };
     rest(rest, integral_constant<int, 0>{});
+    if constexpr (SHARES) {
+        add_share();   // (the last one; zeros, if it is full)
+        each([&](int a, int b, int e) { acc[a][b][e] = total[a][b][e]; });
+    }
     if constexpr (VEC) {
         // The last chunks prefetched beyond the reduction (reads of the zeros block).
         // Those loads are invisible to the compiler and still target the stage registers, which
@@ -1308,6 +1358,36 @@ __global__ __launch_bounds__(64 * SLIM_WAVES) void gemm_mixed_kernel(const GemmP
     gemm_body<MODE, float, 64, 64, 1, true>(p, tr, As, As + 2 * 64 * TileGeom<float, 64, BK>::LDS_LD, NoLr{});
 }
 
+// Problems of the slim form on staged tiles, in the slim form's order: launches of many outputs, in which a workgroup of the
+// slim form, whose eight waves all read the operands of one small tile and add up in local memory, costs more than the chain
+// of chunks it shortens.  A share ends with 32 to 48 vector instructions per block of 32 x 32, which is what these tiles are
+// behind the plain ones: 8 members, 256 x 512 over 784 and 512, forward: slim 21.6 us, here 20.5, plain 18.5 (bf16); 46.1,
+// 42.2, 38.8 (fp32); 64 members 126, 57.6, 55.0 (bf16) and 285, 196, 186 (fp32).
+template <int MODE, typename T, int BM, int BN, bool LEAN>
+__global__ __launch_bounds__(256, LEAN ? 3 : 2) void gemm_shares_kernel(const GemmProb* __restrict__ probs, const TileRef* __restrict__ tiles,
+                                                                        const void* __restrict__ x) {
+    constexpr int BK = ET<T>::BK;
+    const TileRef tr = tiles[blockIdx.x];
+    if (tr.prob < 0) return;
+    GemmProb p = probs[tr.prob];
+    if (p.flags & F_A_INPUT) p.A = (const char*)x + p.x_off;
+    __shared__ __attribute__((aligned(16))) T lds[LdsBytes<T, BM, BN, BK, LEAN, false>::value / sizeof(T)];
+    gemm_body<MODE, T, BM, BN, 1, true, LEAN, false, false, true>(p, tr, lds, lds + (LEAN ? 1 : 2) * BM * TileGeom<T, BM, BK>::LDS_LD, NoLr{});
+}
+template <int MODE, typename T>
+static hipError_t launch_shares(int tile_cfg, const GemmProb* probs, const TileRef* tiles, int n, const void* x, hipStream_t st) {
+    if (tile_cfg == GEMM_CFG_SHARES64) {
+        hipLaunchKernelGGL((gemm_shares_kernel<MODE, T, 64, 64, false>), dim3(n), dim3(256), 0, st, probs, tiles, x);
+    } else if (tile_cfg == GEMM_CFG_SHARES128X64) {
+        hipLaunchKernelGGL((gemm_shares_kernel<MODE, T, 128, 64, true>), dim3(n), dim3(256), 0, st, probs, tiles, x);
+    } else if constexpr (sizeof(T) == 2) {
+        hipLaunchKernelGGL((gemm_shares_kernel<MODE, T, 128, 128, false>), dim3(n), dim3(256), 0, st, probs, tiles, x);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 // One launch of the staged-tile kernels.  A configuration that has no kernel of this product is refused: its tiles were cut
 // for another shape.
 template <int MODE, typename T, int BM, int BN, bool VEC = true, bool LEAN = false, bool GEN = false, bool OPT = false>
@@ -1401,6 +1481,11 @@ hipError_t launch_gemm(int mode, bool bf16, int tile_cfg, const GemmProb* probs,
         if (mode == LIN_FWD) hipLaunchKernelGGL(gemm_mixed_kernel<LIN_FWD>, dim3(n), dim3(64 * SLIM_WAVES), 0, st, probs, tiles, x);
         else hipLaunchKernelGGL(gemm_mixed_kernel<LIN_DX>, dim3(n), dim3(64 * SLIM_WAVES), 0, st, probs, tiles, x);
         return hipGetLastError();
+    }
+    if (is_shares_cfg(tile_cfg)) {
+        if (mode == LIN_FWD) return bf16 ? launch_shares<LIN_FWD, bf16_t>(tile_cfg, probs, tiles, n, x, st) : launch_shares<LIN_FWD, float>(tile_cfg, probs, tiles, n, x, st);
+        if (mode == LIN_DX) return bf16 ? launch_shares<LIN_DX, bf16_t>(tile_cfg, probs, tiles, n, x, st) : launch_shares<LIN_DX, float>(tile_cfg, probs, tiles, n, x, st);
+        return hipErrorInvalidValue;
     }
     if (is_slim_cfg(tile_cfg)) return launch_slim(mode, bf16, tile_cfg, probs, tiles, n, x, st);
     if (mode == CONV_DW && is_halo_cfg(tile_cfg)) return launch_conv_dw_halo(bf16, tile_cfg, probs, tiles, n, x, ws, lr, st);

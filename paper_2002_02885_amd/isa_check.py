@@ -140,7 +140,7 @@ def check_function(items, max_states=512):
     return n_loads, sorted(bad), overflow
 
 
-def check_assembly(text, pattern=r"gemm_kernel|gemm_mixed_kernel|conv_dw_halo_kernel|conv_rows_halo_kernel"):
+def check_assembly(text, pattern=r"gemm_kernel|gemm_mixed_kernel|gemm_shares_kernel|conv_dw_halo_kernel|conv_rows_halo_kernel"):
     """Checks every kernel whose symbol matches `pattern`; returns the number of kernels checked and raises
     RuntimeError on the first kernel with a violation (or whose walk could not be completed)."""
     n = 0

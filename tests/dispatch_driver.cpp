@@ -29,6 +29,8 @@ int main() {
                 if (mode == CONV_DW && !bf16) has.insert(GEMM_CFG_GATHER_LEAN_DW);
                 if (dense) has.insert(GEMM_CFG_SLIM32);
                 if (mode == LIN_FWD && bf16) has.insert(GEMM_CFG_SLIM64);
+                if (dense) has.insert({GEMM_CFG_SHARES64, GEMM_CFG_SHARES128X64});
+                if (dense && bf16) has.insert(GEMM_CFG_SHARES128);
                 if (dense && !bf16) has.insert(GEMM_CFG_SLIM_MIXED);
                 for (int cfg = -1; cfg <= (int)(sizeof(GEMM_TILE_M) / sizeof(int)); ++cfg) {
                     lr.opt = opt ? &oa : nullptr;

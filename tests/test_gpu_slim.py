@@ -59,17 +59,43 @@ def test_products_of_the_slim_form(B, D, H, classes, dtype):
     pk.destroy()
 
 
+# members of one width: 32 x 32 tiles alone; together, the slim form's 64 x 64 (bfloat16 forward, long reductions) and the
+# staged tiles of 64 x 64, 128 x 64 and (bfloat16) 128 x 128, each with partial tiles and a partial last share
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,D,H,K,tiles", [(33, 2600, 505, 40, ((32, 32), (64, 64))), (250, 140, 230, 20, ((64, 64),) * 2), (200, 784, 500, 32, ((128, 64),) * 2),
+                                           (126, 36, 1000, 64, ((128, 64), (128, 128))), (256, 1030, 500, 70, ((128, 64), (128, 128)))])
+def test_every_tile_of_the_form_gives_a_member_the_same_bits(B, D, H, K, tiles, dtype):
+    rng = np.random.default_rng(B)
+    model = wl.mlp([H], 17)
+    x, y = _dev(rng.standard_normal((B, D)).astype(np.float32), dtype), _dev(rng.integers(0, 17, B).astype(np.int32), dtype)
+    batch = [B] + [B - int(k % 3) for k in range(1, K)]
+    pk = binding.Pack(B, (1, 1, D), dtype, [model] * K, batch, seed=2)
+    assert pk.launch_tile([pk.launch_name(i) for i in range(pk.num_launches())].index("gemm_lin_fwd"))[:2] == tiles[dtype == "bf16"]
+    solo = {}
+    for k in (0, K - 1):
+        solo[k] = binding.Pack(batch[k], (1, 1, D), dtype, [model], seed=2)
+        solo[k].write_weights(0, pk.read_weights(k))
+    for _ in range(2):
+        pk.step(x.data_ptr(), y.data_ptr(), np.full(K, 0.01, np.float32))
+        for p in solo.values():
+            p.step(x.data_ptr(), y.data_ptr(), np.full(1, 0.01, np.float32))
+    for k, p in solo.items():
+        assert np.array_equal(pk.read_weights(k).view(np.uint32), p.read_weights(0).view(np.uint32)), k
+        assert np.array_equal(pk.read_logits(k).view(np.uint32), p.read_logits(0).view(np.uint32)), k
+        p.destroy()
+    pk.destroy()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_both_tiles_and_any_company_give_a_member_the_same_bits(dtype):
-    """Forty members of unlike width take 64 x 64 tiles in bfloat16 forward products, one alone takes 32 x 32."""
+    """Forty members of unlike width take staged tiles in the order of the slim form, one alone takes 32 x 32."""
     rng = np.random.default_rng(4)
     B, D, K = 96, 700, 40
     models = [wl.mlp([int(rng.integers(200, 400)), int(rng.integers(8, 300))], 21) for _ in range(K)]
     batch = [B if k == 0 else int(rng.integers(1, B + 1)) for k in range(K)]
     x, y = _dev(rng.standard_normal((B, D)).astype(np.float32), dtype), _dev(rng.integers(0, 21, B).astype(np.int32), dtype)
     pk = binding.Pack(B, (1, 1, D), dtype, models, batch, seed=2)
-    big = any(pk.launch_name(i) == "gemm_lin_fwd" and pk.launch_tile(i)[:2] == (64, 64) for i in range(pk.num_launches()))
-    assert big == (dtype == "bf16")
+    assert any(pk.launch_name(i) == "gemm_lin_fwd" and pk.launch_tile(i)[:2] == (64, 64) for i in range(pk.num_launches()))
     solo = {}
     for k in (0, 7, 39):
         solo[k] = binding.Pack(batch[k], (1, 1, D), dtype, [models[k]], seed=2)

@@ -64,3 +64,7 @@ def test_the_separate_update_takes_the_plain_products_and_reductions(driver):
 
 def test_counted_bytes_of_the_update_follow_the_optimisers_in_force(driver):
     _run(driver, "update_bytes")
+
+
+def test_products_with_few_outputs_take_larger_tiles_in_packs_of_many_members(driver):
+    _run(driver, "slim_tiles")

@@ -503,6 +503,36 @@ static void update_bytes() {
     }
 }
 
+// rows and columns of the tiles of the launches of a kind, in the order of the step
+static std::vector<std::pair<int, int>> tiles_of(const pack_t* p, const char* kind) {
+    std::vector<std::pair<int, int>> out;
+    for (int i = 0; i < pack_num_launches(p); ++i) {
+        char name[64];
+        int rows = 0, cols = 0, lean = 0;
+        EXPECT(pack_launch_name(p, i, name, sizeof name) == PACK_OK && pack_launch_tile(p, i, &rows, &cols, &lean) == PACK_OK);
+        if (std::string(name).rfind(kind, 0) == 0) out.emplace_back(rows, cols);
+    }
+    return out;
+}
+
+// the tiles of products with few outputs: small ones in a pack of few members, those that fill the compute units in one of many
+static void slim_tiles() {
+    const pack_layer layers[] = {{PACK_LINEAR, 512, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 512, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 10, 0}};
+    typedef std::vector<std::pair<int, int>> tiles;
+    for (int dtype : {PACK_F32, PACK_BF16})
+        for (int K : {1, 4, 5, 8, 24, 32, 64}) {
+            const pack_model_spec m{layers, 5, 256};
+            const std::vector<pack_model_spec> models(K, m);
+            const pack_input_spec in{256, 1, 1, 784, dtype};
+            pack_t* p = nullptr;
+            EXPECT(pack_create(&in, models.data(), K, 0, nullptr, &p) == PACK_OK);
+            const std::pair<int, int> want = K <= (dtype == PACK_F32 ? 5 : 4) ? std::make_pair(32, 32) : K <= 8 || (K == 24 && dtype == PACK_F32) ? std::make_pair(64, 64) :
+                                             K == 64 && dtype == PACK_BF16 ? std::make_pair(128, 128) : std::make_pair(128, 64);
+            EXPECT(tiles_of(p, "gemm_lin_fwd") == tiles(2, want) && tiles_of(p, "gemm_lin_dx") == tiles(1, want));
+            pack_destroy(p);
+        }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -525,6 +555,8 @@ int main(int argc, char** argv) {
         separate_update();
     } else if (s == "update_bytes") {
         update_bytes();
+    } else if (s == "slim_tiles") {
+        slim_tiles();
     } else if (s == "failures") {
         failures();
     } else {

@@ -380,6 +380,7 @@ constexpr size_t LEAN64_MIN_TILES = 1024;
 // there are compute units (1024 tiles of 32 x 32 are 256: 34 -> 25 us over 3072 indices, 9.0 -> 8.0 over 512; 256 are 64:
 // 8.0 -> 13).
 constexpr size_t SLIM64_MIN_TILES32 = 768;
+constexpr size_t MIXED_MAX_TILES = 256;
 std::vector<TileRef> xcd_order(const std::vector<TileOrder>& logical) {
     const size_t n = align_up(std::max<size_t>(logical.size(), 1), 8 * XCD_RUN);
     std::vector<TileRef> out(n, TileRef{-1, 0, 0, 0});
@@ -652,11 +653,12 @@ void add_gemm_launch(pack_ctx* p, DescBuilder& db, int mode, const std::vector<G
             // 32 x 32 tiles spread a launch over the compute units, 64 x 64 read half as much per product, and are built for
             // the only products that are bound by that
             const bool big = p->bf16 && mode == LIN_FWD && count_tiles(slim, GEMM_CFG_SLIM32) >= SLIM64_MIN_TILES32;
-            // those of the same size that keep the staged order ride along (slim_flag; they take longest and start first)
+            // those of the same size that keep the staged order ride along (slim_flag; they take longest and start first), up
+            // to a tile per compute unit: the launch holds one or two workgroups to a unit, where one of their own holds four
             std::vector<GemmProb> both, others;
             if (!p->bf16)
                 for (const GemmProb& g : rest) (slim_ok(g) ? both : others).push_back(g);
-            if (both.empty()) {
+            if (both.empty() || count_tiles(both, GEMM_CFG_SLIM_MIXED) > MIXED_MAX_TILES) {
                 emit_gemm_launch(p, db, mode, big ? GEMM_CFG_SLIM64 : GEMM_CFG_SLIM32, slim);
             } else {
                 both.insert(both.end(), slim.begin(), slim.end());

@@ -531,6 +531,20 @@ static void slim_tiles() {
             EXPECT(tiles_of(p, "gemm_lin_fwd") == tiles(2, want) && tiles_of(p, "gemm_lin_dx") == tiles(1, want));
             pack_destroy(p);
         }
+    // fp32 members under Adam next to others: in one launch while they are few
+    for (int K : {4, 16}) {
+        const pack_model_spec m{layers, 5, 256};
+        const std::vector<pack_model_spec> models(K, m);
+        const pack_input_spec in{256, 1, 1, 784, PACK_F32};
+        pack_t* p = nullptr;
+        EXPECT(pack_create(&in, models.data(), K, 0, nullptr, &p) == PACK_OK);
+        for (int k = 1; k < K; ++k) {
+            const pack_opt_spec o{PACK_OPT_ADAM, 0.9f, 0.1f, 0.9f, 0.999f, 1e-8f};
+            EXPECT(pack_set_optimizer(p, k, &o) == PACK_OK);
+        }
+        EXPECT(tiles_of(p, "gemm_lin_fwd").size() == (K == 4 ? 2 : 4));
+        pack_destroy(p);
+    }
 }
 
 int main(int argc, char** argv) {

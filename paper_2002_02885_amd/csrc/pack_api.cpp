@@ -714,13 +714,6 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
             return;
         }
     }
-    if (general && mode == CONV_DW && !p->bf16) {
-        // Single precision multiplies at a sixteenth of the bfloat16 rate, and what counts is that rows of 40 or 80 channels are
-        // padded to 64 instead of 128 and that four workgroups share a compute unit: two residual networks of 40 to 320 channels,
-        // 128 x 128 tiles 592 us, 64 x 64 pipelined 615, lean 511.  (bfloat16, bound by the gather: 60 against 79 lean.)
-        emit_gemm_launch(p, db, mode, GEMM_CFG_GATHER_LEAN_DW, probs);
-        return;
-    }
     // The tile shape only partitions the output; the summation order of an element does not
     // depend on it, so a member's bits do not depend on who else is in the launch.  Each problem
     // prefers the shape that multiplies the fewest padding elements (a 64-channel layer wastes
@@ -745,6 +738,24 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
     int main_cfg = 0;
     for (int c = 1; c < 3; ++c)
         if (work[c] > work[main_cfg]) main_cfg = c;
+    auto tile_of = [&](size_t i) { return (work[want[i]] < 0.15 * total) ? main_cfg : want[i]; };
+    const bool lean_dw = general && mode == CONV_DW && !p->bf16;   // (GEMM_CFG_GATHER_LEAN_DW: fp32 has no other 64 x 64 form)
+    if (lean_dw) {
+        // Single precision multiplies at a sixteenth of the bfloat16 rate, and what counts is that rows of 40 or 80 channels are
+        // padded to 64 instead of 128 and that four workgroups share a compute unit: two residual networks of 40 to 320 channels,
+        // 128 x 128 tiles 592 us, 64 x 64 pipelined 615, lean 511; of 64 to 512 607 and 514 (lean).  (bfloat16, bound by the
+        // gather: 60 against 79 lean.)  Larger tiles that are full read less: networks of 128 to 512 channels 541 us on 128 x 128,
+        // 627 lean, and 897, 1047; of 64 to 256 168 on 128 x 64, 180 lean.
+        double planned = 0, real = 0;
+        for (size_t i = 0; i < probs.size(); ++i) {
+            planned += padded_work(probs[i], tile_of(i));
+            real += (double)probs[i].R * probs[i].Q * probs[i].Kd;
+        }
+        if (real < 0.9 * planned || main_cfg == 2) {
+            emit_gemm_launch(p, db, mode, GEMM_CFG_GATHER_LEAN_DW, probs);
+            return;
+        }
+    }
     // weight gradients whose reduction is at most a few chunks long take the lean form of the
     // 128 x 128 kernel (more tiles resident per compute unit)
     const bool lean_ok = (mode == LIN_DW && !(p->any_opt && p->fused)) || mode == CONV_DW;   // (with other optimisers: above)
@@ -762,8 +773,7 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
     for (int c = 0; c < 3; ++c) {
         std::vector<GemmProb> group, lean;
         for (size_t i = 0; i < probs.size(); ++i) {
-            const int eff = (work[want[i]] < 0.15 * total) ? main_cfg : want[i];
-            if (eff != c) continue;
+            if (tile_of(i) != c) continue;
             const int chunks = (std::min(probs[i].Kd, probs[i].ksplit) + chunk_k - 1) / chunk_k;
             if (general && is_dw) group.push_back(probs[i]);
             else if (c == 0 && lean_ok && chunks <= 8) lean.push_back(probs[i]);
@@ -775,7 +785,7 @@ void add_tiled_launches(pack_ctx* p, DescBuilder& db, int mode, const std::vecto
             lean.clear();
         }
         if (!lean.empty()) emit_gemm_launch(p, db, mode, is_dw ? GEMM_CFG_LEAN : general ? GEMM_CFG_GATHER_LEAN64 : GEMM_CFG_LEAN64, lean);
-        if (!group.empty()) emit_gemm_launch(p, db, mode, general ? GEMM_CFG_GATHER0 + c : c, group);
+        if (!group.empty()) emit_gemm_launch(p, db, mode, !general ? c : lean_dw && c == 2 ? GEMM_CFG_GATHER_LEAN_DW : GEMM_CFG_GATHER0 + c, group);
     }
 }
 

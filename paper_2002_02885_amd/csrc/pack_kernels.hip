@@ -1429,13 +1429,12 @@ static hipError_t launch_gemm_tile(int tile_cfg, const GemmProb* probs, const Ti
     } else {
         if (tile_cfg == GEMM_CFG_LEAN64) return start_gemm<MODE, T, 128, 64, true, true>(probs, tiles, n, x, ws, la, st);
     }
+    if constexpr (ROWS || MODE == CONV_DW) {
+        if (tile_cfg == GEMM_CFG_GATHER0) return start_gemm<MODE, T, 128, 128, true, false, true>(probs, tiles, n, x, ws, la, st);
+        if (tile_cfg == GEMM_CFG_GATHER0 + 1) return start_gemm<MODE, T, 128, 64, true, false, true>(probs, tiles, n, x, ws, la, st);
+    }
     if constexpr (ROWS || (MODE == CONV_DW && sizeof(T) == 2)) {
-        switch (tile_cfg) {
-            case GEMM_CFG_GATHER0: return start_gemm<MODE, T, 128, 128, true, false, true>(probs, tiles, n, x, ws, la, st);
-            case GEMM_CFG_GATHER0 + 1: return start_gemm<MODE, T, 128, 64, true, false, true>(probs, tiles, n, x, ws, la, st);
-            case GEMM_CFG_GATHER0 + 2: return start_gemm<MODE, T, 64, 64, true, false, true>(probs, tiles, n, x, ws, la, st);
-            default: break;
-        }
+        if (tile_cfg == GEMM_CFG_GATHER0 + 2) return start_gemm<MODE, T, 64, 64, true, false, true>(probs, tiles, n, x, ws, la, st);
     }
     if constexpr (ROWS) {
         if (tile_cfg == GEMM_CFG_GATHER_LEAN64) return start_gemm<MODE, T, 128, 64, true, true, true>(probs, tiles, n, x, ws, la, st);

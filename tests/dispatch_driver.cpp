@@ -23,7 +23,8 @@ int main() {
                 if (opt) has.insert(GEMM_CFG_LEAN_OPT);
                 else if (dw) has.insert(GEMM_CFG_LEAN);
                 else has.insert(GEMM_CFG_LEAN64);
-                if (rows || (mode == CONV_DW && bf16)) has.insert({GEMM_CFG_GATHER0, GEMM_CFG_GATHER0 + 1, GEMM_CFG_GATHER0 + 2});
+                if (rows || mode == CONV_DW) has.insert({GEMM_CFG_GATHER0, GEMM_CFG_GATHER0 + 1});
+                if (rows || (mode == CONV_DW && bf16)) has.insert(GEMM_CFG_GATHER0 + 2);
                 if (rows) has.insert({GEMM_CFG_GATHER_LEAN64, GEMM_CFG_ROWS64, GEMM_CFG_ROWS32});
                 if (mode == CONV_DW) has.insert({GEMM_CFG_HALO_S1, GEMM_CFG_HALO_S2, GEMM_CFG_HALO32_S1});
                 if (mode == CONV_DW && !bf16) has.insert(GEMM_CFG_GATHER_LEAN_DW);

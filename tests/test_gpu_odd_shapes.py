@@ -95,3 +95,26 @@ def test_lean_tiles_of_the_general_gather_give_the_same_bits(dtype, widths, monk
     tp._same_bits(regular, lean)
     for k in range(w.K):
         assert np.array_equal(regular["grads"][k], lean["grads"][k])
+
+
+def test_every_tile_of_single_precision_weight_gradients_of_the_general_gather_gives_the_same_bits(monkeypatch):
+    """Full rows of 128 channels, strides 1 and 2, chunks that straddle images: 128 x 128, 128 x 64 and lean 64 x 64 tiles."""
+    layers = [("conv3x3", 128, 1), ("relu",), ("conv3x3", 128, 1), ("relu",), ("conv3x3", 256, 2), ("relu",), ("gap",), ("linear", 7)]
+    w = wl.custom("gather_dw", 31, wl.F32, 11, (7, 9, 3), [layers] * 2, batch=[11, 10], n_classes=7, steps=1)
+    runs = {}
+    for least in (100000, 1, 8, 16, 24, 32, 48, 64, 96, 128, 192, 256):
+        monkeypatch.setenv("PACK_MIN_TILES", str(least))
+        pk = binding.Pack(w.B, w.in_shape, w.dtype, w.models, w.batch)
+        tiles = {pk.launch_tile(i) for i in range(pk.num_launches()) if pk.launch_name(i).startswith("gemm_conv_dw")}
+        pk.destroy()
+        assert len(tiles) == 1
+        runs.setdefault(tiles.pop(), least)
+    assert set(runs) == {(64, 64, True), (128, 128, False), (128, 64, False)}
+    out = []
+    for least in runs.values():
+        monkeypatch.setenv("PACK_MIN_TILES", str(least))
+        out.append(pu.run_gpu(w, 1))
+    for other in out[1:]:
+        tp._same_bits(out[0], other)
+        for k in range(w.K):
+            assert np.array_equal(out[0]["grads"][k], other["grads"][k])

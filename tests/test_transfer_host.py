@@ -68,3 +68,7 @@ def test_counted_bytes_of_the_update_follow_the_optimisers_in_force(driver):
 
 def test_products_with_few_outputs_take_larger_tiles_in_packs_of_many_members(driver):
     _run(driver, "slim_tiles")
+
+
+def test_single_precision_weight_gradients_of_the_general_gather_take_larger_tiles_without_padding_to_save(driver):
+    _run(driver, "gather_tiles")

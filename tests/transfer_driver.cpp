@@ -547,6 +547,23 @@ static void slim_tiles() {
     }
 }
 
+// single-precision weight gradients of convolutions on maps that are no power of two: 64 x 64 tiles where larger ones multiply
+// for padding, larger ones where they do not
+static void gather_tiles() {
+    typedef std::vector<std::pair<int, int>> tiles;
+    for (int width : {24, 40, 64, 128}) {
+        const pack_layer layers[] = {{PACK_CONV3X3, width, 1}, {PACK_RELU, 0, 0}, {PACK_CONV3X3, 2 * width, 1}, {PACK_RELU, 0, 0},
+                                     {PACK_CONV3X3, 4 * width, 2}, {PACK_RELU, 0, 0}, {PACK_GAP, 0, 0}, {PACK_LINEAR, 10, 0}};
+        const pack_model_spec m{layers, 8, 32}, models[2] = {m, m};
+        const pack_input_spec in{32, 28, 28, 3, PACK_F32};
+        pack_t* p = nullptr;
+        EXPECT(pack_create(&in, models, 2, 0, nullptr, &p) == PACK_OK);
+        const std::pair<int, int> want = width == 128 ? std::make_pair(128, 128) : width == 64 ? std::make_pair(128, 64) : std::make_pair(64, 64);
+        EXPECT(tiles_of(p, "gemm_conv_dw") == tiles(1, want));
+        pack_destroy(p);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -571,6 +588,8 @@ int main(int argc, char** argv) {
         update_bytes();
     } else if (s == "slim_tiles") {
         slim_tiles();
+    } else if (s == "gather_tiles") {
+        gather_tiles();
     } else if (s == "failures") {
         failures();
     } else {

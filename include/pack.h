@@ -319,7 +319,10 @@ size_t pack_workspace_bytes(const pack_t* p);
 /* Choose member k's optimiser (default: PACK_OPT_SGD).  Resets the member's optimiser state to its
  * starting values and its step counter to 0; the weights are untouched.  Fields that the chosen
  * kind does not use are ignored.  Waits for the stream.  The learning rate stays the per-step
- * argument of pack_step.
+ * argument of pack_step.  The launches of a step may become others, in number too: when the state
+ * arrays that the pack's members need change (launch timing is switched off then), and in PACK_F32
+ * packs when a member changes to or from Adam, whose dense products are added up in another order
+ * (timing goes on; samples whose launch numbers no longer fit are dropped).
  * Errors: PACK_EINVAL (null, k out of range, unknown kind, parameter outside its range), PACK_ENOMEM. */
 pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec);
 
@@ -396,7 +399,11 @@ pack_status pack_launch_bytes(const pack_t* p, int32_t i, double* bytes);
 /* Tile shape of launch i, for tests and measurements that need to know which kernel form the planner
  * chose: rows and columns of an output tile, and lean != 0 for the forms that keep one operand buffer and
  * one register stage (more workgroups per compute unit).  All three are 0 for launches that are not
- * matrix products.  The choice never changes results.  Outputs: host int32. */
+ * matrix products; a launch that holds tiles of two shapes reports the larger.  Which of its forms a
+ * product takes never changes results, with one exception that depends on the product and its member
+ * alone: dense forward products and input gradients of at most 32 tiles of 64 x 64 are added up in the
+ * order of the 32 x 32 tiles, whatever tiles they take, except those of PACK_F32 members under Adam.
+ * Outputs: host int32. */
 pack_status pack_launch_tile(const pack_t* p, int32_t i, int32_t* tile_rows, int32_t* tile_cols, int32_t* lean);
 
 /* Thread-local text describing the last failing call on this thread ("" if none). */

@@ -1545,9 +1545,13 @@ pack_status replan(pack_ctx* p) {
     p->desc = desc;
     p->device_bytes = bytes - align_up(p->desc_bytes, 256) + align_up(db.bytes.size(), 256);
     p->desc_bytes = db.bytes.size();
-    for (auto& t : p->stamps) { (void)hipEventDestroy(t.t0); (void)hipEventDestroy(t.t1); }   // (launch numbers have changed)
-    p->stamps.clear();
-    p->profiling = false;
+    // timing goes on; what it has gathered is kept where the numbers still name the launches they did
+    bool same = plan.size() == p->plan.size();
+    for (size_t i = 0; same && i < plan.size(); ++i) same = plan[i].kind == p->plan[i].kind && plan[i].mode == p->plan[i].mode;
+    if (!same) {
+        for (auto& t : p->stamps) { (void)hipEventDestroy(t.t0); (void)hipEventDestroy(t.t1); }
+        p->stamps.clear();
+    }
     return PACK_OK;
 }
 

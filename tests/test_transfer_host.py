@@ -72,3 +72,7 @@ def test_products_with_few_outputs_take_larger_tiles_in_packs_of_many_members(dr
 
 def test_single_precision_weight_gradients_of_the_general_gather_take_larger_tiles_without_padding_to_save(driver):
     _run(driver, "gather_tiles")
+
+
+def test_launch_timing_goes_on_when_a_change_of_optimiser_plans_the_launches_again(driver):
+    _run(driver, "timing")

@@ -564,6 +564,39 @@ static void gather_tiles() {
     }
 }
 
+// a change of optimiser that changes the form of a member's products, in a pack whose launches are being timed
+static void timing() {
+    const pack_layer layers[] = {{PACK_LINEAR, 48, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 40, 0}};
+    const pack_model_spec m{layers, 3, 4}, models[3] = {m, m, m};
+    const pack_input_spec in{4, 1, 1, 64, PACK_F32};
+    pack_t* p = nullptr;
+    EXPECT(pack_create(&in, models, 3, 0, nullptr, &p) == PACK_OK);
+    auto choose = [&](int k, int kind) {
+        const pack_opt_spec o{kind, 0.9f, 0.1f, 0.9f, 0.999f, 1e-8f};
+        EXPECT(pack_set_optimizer(p, k, &o) == PACK_OK);
+    };
+    for (int k = 0; k < 3; ++k) choose(k, k == 1 ? PACK_OPT_ADAM : PACK_OPT_MOMENTUM);
+    alignas(16) static float x[4 * 64];
+    static int32_t y[4];
+    const float lr[3] = {0.f, 0.f, 0.f};
+    EXPECT(pack_profile_start(p, -1, 1) == PACK_OK);
+    EXPECT(pack_step(p, x, y, lr) == PACK_OK);
+    choose(0, PACK_OPT_ADAM);       // slim and staged problems share their launches before and after
+    EXPECT(pack_step(p, x, y, lr) == PACK_OK);
+    auto samples = [&] {
+        std::vector<float> ms(pack_num_launches(p));
+        std::vector<int32_t> count(pack_num_launches(p));
+        EXPECT(pack_profile_stop(p, ms.data(), count.data()) == PACK_OK);
+        return count;
+    };
+    EXPECT(samples() == std::vector<int32_t>(pack_num_launches(p), 2));
+    EXPECT(pack_profile_start(p, -1, 1) == PACK_OK);
+    choose(2, PACK_OPT_ADAM);
+    EXPECT(pack_step(p, x, y, lr) == PACK_OK);
+    for (int32_t n : samples()) EXPECT(n == 1);
+    pack_destroy(p);
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -590,6 +623,8 @@ int main(int argc, char** argv) {
         slim_tiles();
     } else if (s == "gather_tiles") {
         gather_tiles();
+    } else if (s == "timing") {
+        timing();
     } else if (s == "failures") {
         failures();
     } else {

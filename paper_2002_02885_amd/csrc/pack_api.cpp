@@ -1514,27 +1514,32 @@ pack_status build_device(pack_ctx* p) {
 // Plans the launches of a pack again whose members' products changed their form: the buffers stay, the tables are new.  The
 // stream is idle.  On failure the pack is what it was.
 pack_status replan(pack_ctx* p) {
-    const std::vector<Launch> plan = p->plan;
+    std::vector<Launch> plan = p->plan;
     const size_t ce_off = p->ce_desc_off, head_off = p->head_desc_off;
     std::vector<size_t> segs_off;
     for (const ModelInfo& m : p->models) segs_off.push_back(m.segs_off);
     const size_t bytes = p->device_bytes;
-    p->plan.clear();
     DescBuilder db;
-    size_t need = 0;
-    build_plan(p, db, need);
-    for (ModelInfo& m : p->models) {
-        const std::vector<BlobSeg> segs = blob_segments(m);
-        m.segs_off = db.add(segs.data(), segs.size() * sizeof(BlobSeg));
-    }
     char* desc = nullptr;
-    pack_status s = need == p->workspace_bytes ? dev_alloc((void**)&desc, db.bytes.size(), p) : fail(PACK_EINVAL, "internal: the workspace changed");
-    if (s == PACK_OK)
-        if (const hipError_t e = hipMemcpy(desc, db.bytes.data(), db.bytes.size(), hipMemcpyHostToDevice); e != hipSuccess)
-            s = fail(PACK_EDEVICE, std::string("launch tables: ") + hipGetErrorString(e));
+    pack_status s = PACK_OK;
+    try {
+        p->plan.clear();
+        size_t need = 0;
+        build_plan(p, db, need);
+        for (ModelInfo& m : p->models) {
+            const std::vector<BlobSeg> segs = blob_segments(m);
+            m.segs_off = db.add(segs.data(), segs.size() * sizeof(BlobSeg));
+        }
+        s = need == p->workspace_bytes ? dev_alloc((void**)&desc, db.bytes.size(), p) : fail(PACK_EINVAL, "internal: the workspace changed");
+        if (s == PACK_OK)
+            if (const hipError_t e = hipMemcpy(desc, db.bytes.data(), db.bytes.size(), hipMemcpyHostToDevice); e != hipSuccess)
+                s = fail(PACK_EDEVICE, std::string("launch tables: ") + hipGetErrorString(e));
+    } catch (const std::bad_alloc&) {
+        s = PACK_ENOMEM;
+    }
     if (s != PACK_OK) {
         if (desc) (void)hipFree(desc);
-        p->plan = plan;
+        p->plan.swap(plan);
         p->ce_desc_off = ce_off;
         p->head_desc_off = head_off;
         for (size_t k = 0; k < segs_off.size(); ++k) p->models[k].segs_off = segs_off[k];
@@ -2188,15 +2193,19 @@ pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec) 
             return st;
         }
     } else if (p->opt_params) {
-        if (!p->bf16 && (old_spec.kind == PACK_OPT_ADAM) != (o.kind == PACK_OPT_ADAM)) {   // the form of the member's dense products (slim_flag)
-            pack_status st = replan(p);
-            if (st != PACK_OK) {
-                p->opt[k] = old_spec;
-                p->opt_t[k] = old_t;
-                return st;
-            }
+        std::vector<OptStatic> par;
+        pack_status st = PACK_OK;
+        try {
+            par.resize(p->K);
+            if (!p->bf16 && (old_spec.kind == PACK_OPT_ADAM) != (o.kind == PACK_OPT_ADAM)) st = replan(p);   // the form of the member's dense products (slim_flag)
+        } catch (const std::bad_alloc&) {
+            st = PACK_ENOMEM;
         }
-        std::vector<OptStatic> par(p->K);
+        if (st != PACK_OK) {
+            p->opt[k] = old_spec;
+            p->opt_t[k] = old_t;
+            return st == PACK_ENOMEM ? fail(PACK_ENOMEM, "no memory for the launch tables") : st;
+        }
         for (int i = 0; i < p->K; ++i)
             par[i] = OptStatic{p->opt[i].kind, p->opt[i].mu, p->opt[i].beta1, p->opt[i].beta2, p->opt[i].eps};
         HIP_TRY(hipMemcpy(p->opt_params, par.data(), par.size() * sizeof(OptStatic), hipMemcpyHostToDevice), PACK_EDEVICE);

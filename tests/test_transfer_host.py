@@ -76,3 +76,7 @@ def test_single_precision_weight_gradients_of_the_general_gather_take_larger_til
 
 def test_launch_timing_goes_on_when_a_change_of_optimiser_plans_the_launches_again(driver):
     _run(driver, "timing")
+
+
+def test_a_change_of_optimiser_that_finds_no_host_memory_leaves_the_pack_unchanged(driver):
+    _run(driver, "no_host_memory")

@@ -51,6 +51,15 @@ extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(
     return real(t, a, f, arg);
 }
 
+static thread_local long long t_new_left = -1;   // allocations of this thread that still succeed (negative: all)
+void* operator new(size_t n) {
+    if (t_new_left >= 0 && t_new_left-- == 0) throw std::bad_alloc();
+    if (void* p = malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 struct Queue {
     std::mutex mu;
     std::condition_variable cv;
@@ -597,6 +606,30 @@ static void timing() {
     pack_destroy(p);
 }
 
+// host memory that ends anywhere while a change of optimiser plans the launches again: the pack is what it was
+static void no_host_memory() {
+    const pack_layer layers[] = {{PACK_LINEAR, 48, 0}, {PACK_RELU, 0, 0}, {PACK_LINEAR, 40, 0}};
+    const pack_model_spec m{layers, 3, 4}, models[2] = {m, m};
+    const pack_input_spec in{4, 1, 1, 64, PACK_F32};
+    pack_t* p = nullptr;
+    EXPECT(pack_create(&in, models, 2, 0, nullptr, &p) == PACK_OK);
+    const pack_opt_spec adam{PACK_OPT_ADAM, 0.9f, 0.1f, 0.9f, 0.999f, 1e-8f}, momentum{PACK_OPT_MOMENTUM, 0.9f, 0.1f, 0.9f, 0.999f, 1e-8f};
+    EXPECT(pack_set_optimizer(p, 0, &adam) == PACK_OK && pack_set_optimizer(p, 1, &momentum) == PACK_OK);
+    const auto forms = tiles_of(p, "");
+    const size_t bytes = pack_device_bytes(p);
+    int n = 0;
+    for (;; ++n) {
+        t_new_left = n;
+        const pack_status st = pack_set_optimizer(p, 1, &adam);
+        const bool reached = t_new_left < 0;
+        t_new_left = -1;
+        if (st == PACK_OK) break;
+        EXPECT(reached && st == PACK_ENOMEM && tiles_of(p, "") == forms && pack_device_bytes(p) == bytes);
+    }
+    EXPECT(n > 20);
+    pack_destroy(p);
+}
+
 int main(int argc, char** argv) {
     if (argc < 2) return 2;
     alarm(100);
@@ -625,6 +658,8 @@ int main(int argc, char** argv) {
         gather_tiles();
     } else if (s == "timing") {
         timing();
+    } else if (s == "no_host_memory") {
+        no_host_memory();
     } else if (s == "failures") {
         failures();
     } else {

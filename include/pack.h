@@ -142,6 +142,8 @@ pack_status pack_create(const pack_input_spec* input, const pack_model_spec* mod
  * its descriptor's window or its allocation, a load of missing elements that is not cut off by construction,
  * an operand slot holding the wrong element, a tile dealt twice or not at all, a reduction of split weight
  * gradients that adds elements no product stores is an error.
+ * The launches that members under other optimisers than plain SGD change are walked too, under momentum and under
+ * Adam and Adagrad in turn; the outputs count the plan of plain SGD.
  * input_mode: pack_input_mode.  Outputs (host, may be null): launches walked, matrix-product launches on the
  * element-by-element kernels for sizes the others do not address (skipped: they load by the definition itself), loads and
  * operand reads checked.

@@ -1665,77 +1665,12 @@ pack_status live_member(const pack_ctx* p, int32_t k) {
 
 }  // namespace
 
-extern "C" {
-
-const char* pack_last_error(void) { return g_err.c_str(); }
-
-pack_status pack_create(const pack_input_spec* input, const pack_model_spec* models, int32_t K,
-                        uint64_t seed, void* hip_stream, pack_t** out) {
-    if (out) *out = nullptr;
-    if (!input || !models || !out) return fail(PACK_EINVAL, "null argument");
-    if (K < 1 || K > PACK_MAX_MODELS) return fail(PACK_EINVAL, "K must be in [1, PACK_MAX_MODELS]");
-    if (input->B < 1 || input->in_h < 1 || input->in_w < 1 || input->in_c < 1) return fail(PACK_EINVAL, "bad input shape");
-    if (input->dtype != PACK_F32 && input->dtype != PACK_BF16) return fail(PACK_EINVAL, "unknown dtype");
-
-    pack_ctx* p = new (std::nothrow) pack_ctx();
-    if (!p) return fail(PACK_ENOMEM, "host allocation failed");
-    p->stream = (hipStream_t)hip_stream;
-    p->bf16 = (input->dtype == PACK_BF16);
-    p->K = K;
-    p->in = *input;
-    p->models.resize(K);
-    p->opt.assign(K, pack_opt_spec{PACK_OPT_SGD, 0.f, 0.f, 0.f, 0.f, 0.f});
-    p->opt_t.assign(K, 0);
-    for (int k = 0; k < K; ++k) {
-        pack_status s = parse_model(*input, models[k], k, p->models[k]);
-        if (s != PACK_OK) { release(p); return s; }
-    }
-    if (hipGetDevice(&p->device) != hipSuccess) {
-        (void)hipGetLastError();
-        release(p);
-        return fail(PACK_EDEVICE, "no HIP device is current");
-    }
-    pack_status s = build_device(p);
-    if (s != PACK_OK) { release(p); return s; }
-    for (int k = 0; k < K; ++k) {
-        s = seed_weights(p, k, seed);
-        if (s != PACK_OK) { release(p); return s; }
-    }
-    if (const hipError_t e = hipStreamSynchronize(p->stream); e != hipSuccess) {
-        release(p);
-        return fail(PACK_EDEVICE, std::string("initial weights: ") + hipGetErrorString(e));
-    }
-    transfer_open();
-    *out = p;
-    return PACK_OK;
-}
-
-pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec* models, int32_t K, int32_t input_mode,
-                            int64_t* launches_walked, int64_t* launches_skipped, int64_t* loads_checked) {
-    if (!input || !models) return fail(PACK_EINVAL, "null argument");
-    if (K < 1 || K > PACK_MAX_MODELS) return fail(PACK_EINVAL, "K must be in [1, PACK_MAX_MODELS]");
-    if (input->B < 1 || input->in_h < 1 || input->in_w < 1 || input->in_c < 1) return fail(PACK_EINVAL, "bad input shape");
-    if (input->dtype != PACK_F32 && input->dtype != PACK_BF16) return fail(PACK_EINVAL, "unknown dtype");
-    if (input_mode != PACK_INPUT_SHARED && input_mode != PACK_INPUT_PER_MEMBER) return fail(PACK_EINVAL, "unknown input mode");
-    pack_ctx* p = new (std::nothrow) pack_ctx();
-    if (!p) return fail(PACK_ENOMEM, "host allocation failed");
-    p->dry = true;
-    p->bf16 = (input->dtype == PACK_BF16);
-    p->K = K;
-    p->in = *input;
-    p->own_input = input_mode == PACK_INPUT_PER_MEMBER;
-    p->models.resize(K);
-    p->opt.assign(K, pack_opt_spec{PACK_OPT_SGD, 0.f, 0.f, 0.f, 0.f, 0.f});
-    p->opt_t.assign(K, 0);
-    for (int k = 0; k < K; ++k) {
-        pack_status s = parse_model(*input, models[k], k, p->models[k]);
-        if (s != PACK_OK) { release(p); return s; }
-    }
-    pack_status s = build_device(p);
-    if (s != PACK_OK) { release(p); return s; }
+// Walks the launches of a made-up pack's plan (all, or those that members with other optimisers than SGD change); "" or what is wrong.
+// counts: launches walked and skipped, loads and operand reads checked.
+static std::string check_plan(pack_ctx* p, bool all, long long (&counts)[4]) {
     // the step's input: one more made-up allocation
     const size_t esz = p->bf16 ? 2 : 4;
-    const size_t x_bytes = (size_t)input->B * input->in_h * input->in_w * input->in_c * esz * (p->own_input ? (size_t)K : 1);
+    const size_t x_bytes = (size_t)p->in.B * p->in.in_h * p->in.in_w * p->in.in_c * esz * (p->own_input ? (size_t)p->K : 1);
     void* x_fake = nullptr;
     (void)dev_alloc(&x_fake, x_bytes, p);
     auto region_holds = [&](const void* ptr, long long bytes) {
@@ -1744,11 +1679,11 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
             if (a >= r.first && a + (uintptr_t)bytes <= r.first + r.second) return true;
         return false;
     };
-    long long walked = 0, skipped = 0, loads = 0, frags = 0;
+    long long &walked = counts[0], &skipped = counts[1], &loads = counts[2], &frags = counts[3];
     std::string err;
     for (size_t li = 0; li < p->plan.size() && err.empty(); ++li) {
         const Launch& L = p->plan[li];
-        if (L.kind != L_GEMM) continue;
+        if (L.kind != L_GEMM || (!all && L.mode != LIN_DW && L.tile_cfg != GEMM_CFG_SLIM_MIXED)) continue;
         const bool halo = L.mode == CONV_DW && is_halo_cfg(L.tile_cfg);
         const bool rows = (L.mode == CONV_FWD || L.mode == CONV_DX) && is_rows_cfg(L.tile_cfg);
         const int ci_t = halo ? GEMM_TILE_N[L.tile_cfg] / 9 : 0;      // input channels per tile
@@ -1854,12 +1789,17 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
     }
     // every element a reduction of split weight gradients reads is one that the products it belongs to store
     std::map<unsigned long long, const GemmProb*> partial_w, partial_b;
+    std::map<const float*, long long> in_place;   // gradients (weights, biases) that a product stores where they belong, and their lengths
     for (const Launch& L : p->plan) {
         if (L.kind != L_GEMM || (L.mode != LIN_DW && L.mode != CONV_DW)) continue;
         const GemmProb* probs = (const GemmProb*)(p->desc_host.data() + L.desc_off);
         const TileRef* tiles = (const TileRef*)(p->desc_host.data() + L.map_off);
         for (int t = 0; t < L.n; ++t)
-            if (tiles[t].prob >= 0 && (probs[tiles[t].prob].flags & F_WS)) {
+            if (tiles[t].prob >= 0 && !(probs[tiles[t].prob].flags & (F_WS | F_UPDATE))) {
+                const GemmProb& g = probs[tiles[t].prob];
+                in_place[(const float*)g.C] = (long long)g.R * g.ldc;
+                in_place[g.dbias] = g.R;
+            } else if (tiles[t].prob >= 0 && (probs[tiles[t].prob].flags & F_WS)) {
                 const GemmProb& g = probs[tiles[t].prob];
                 partial_w[(unsigned long long)(uintptr_t)g.C] = partial_b[(unsigned long long)(uintptr_t)g.dbias] = &g;
             }
@@ -1870,6 +1810,14 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
         const int2* map = (const int2*)(p->desc_host.data() + L.map_off);
         for (int t = 0; t < L.n && err.empty(); ++t) {
             const ReduceProb& r = reds[map[t].x];
+            if (!region_holds(r.out, 4LL * r.n) || (r.upd_w && !region_holds(r.upd_w, 4LL * r.n)) || (r.upd_shadow && !region_holds(r.upd_shadow, 2LL * r.n)))
+                err = "reduction " + std::to_string(map[t].x) + " stores outside its allocations";
+            if (r.stored) {
+                const auto g = in_place.find(r.in);
+                if (err.empty() && (r.in != r.out || r.S != 1 || !r.upd_w || g == in_place.end() || g->second != r.n))
+                    err = "reduction " + std::to_string(map[t].x) + " applies a gradient that no product stores";
+                continue;
+            }
             const auto w = partial_w.find((unsigned long long)(uintptr_t)r.in), b = partial_b.find((unsigned long long)(uintptr_t)r.in);
             const GemmProb* g = w != partial_w.end() ? w->second : b != partial_b.end() ? b->second : nullptr;
             bool written = g && r.S == (g->Kd + g->ksplit - 1) / g->ksplit;
@@ -1878,10 +1826,92 @@ pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec*
             if (!written) err = "reduction " + std::to_string(map[t].x) + " of split weight gradients adds elements that no product stores";
         }
     }
+    return err;
+}
+
+extern "C" {
+
+const char* pack_last_error(void) { return g_err.c_str(); }
+
+pack_status pack_create(const pack_input_spec* input, const pack_model_spec* models, int32_t K,
+                        uint64_t seed, void* hip_stream, pack_t** out) {
+    if (out) *out = nullptr;
+    if (!input || !models || !out) return fail(PACK_EINVAL, "null argument");
+    if (K < 1 || K > PACK_MAX_MODELS) return fail(PACK_EINVAL, "K must be in [1, PACK_MAX_MODELS]");
+    if (input->B < 1 || input->in_h < 1 || input->in_w < 1 || input->in_c < 1) return fail(PACK_EINVAL, "bad input shape");
+    if (input->dtype != PACK_F32 && input->dtype != PACK_BF16) return fail(PACK_EINVAL, "unknown dtype");
+
+    pack_ctx* p = new (std::nothrow) pack_ctx();
+    if (!p) return fail(PACK_ENOMEM, "host allocation failed");
+    p->stream = (hipStream_t)hip_stream;
+    p->bf16 = (input->dtype == PACK_BF16);
+    p->K = K;
+    p->in = *input;
+    p->models.resize(K);
+    p->opt.assign(K, pack_opt_spec{PACK_OPT_SGD, 0.f, 0.f, 0.f, 0.f, 0.f});
+    p->opt_t.assign(K, 0);
+    for (int k = 0; k < K; ++k) {
+        pack_status s = parse_model(*input, models[k], k, p->models[k]);
+        if (s != PACK_OK) { release(p); return s; }
+    }
+    if (hipGetDevice(&p->device) != hipSuccess) {
+        (void)hipGetLastError();
+        release(p);
+        return fail(PACK_EDEVICE, "no HIP device is current");
+    }
+    pack_status s = build_device(p);
+    if (s != PACK_OK) { release(p); return s; }
+    for (int k = 0; k < K; ++k) {
+        s = seed_weights(p, k, seed);
+        if (s != PACK_OK) { release(p); return s; }
+    }
+    if (const hipError_t e = hipStreamSynchronize(p->stream); e != hipSuccess) {
+        release(p);
+        return fail(PACK_EDEVICE, std::string("initial weights: ") + hipGetErrorString(e));
+    }
+    transfer_open();
+    *out = p;
+    return PACK_OK;
+}
+
+pack_status pack_plan_check(const pack_input_spec* input, const pack_model_spec* models, int32_t K, int32_t input_mode,
+                            int64_t* launches_walked, int64_t* launches_skipped, int64_t* loads_checked) {
+    if (!input || !models) return fail(PACK_EINVAL, "null argument");
+    if (K < 1 || K > PACK_MAX_MODELS) return fail(PACK_EINVAL, "K must be in [1, PACK_MAX_MODELS]");
+    if (input->B < 1 || input->in_h < 1 || input->in_w < 1 || input->in_c < 1) return fail(PACK_EINVAL, "bad input shape");
+    if (input->dtype != PACK_F32 && input->dtype != PACK_BF16) return fail(PACK_EINVAL, "unknown dtype");
+    if (input_mode != PACK_INPUT_SHARED && input_mode != PACK_INPUT_PER_MEMBER) return fail(PACK_EINVAL, "unknown input mode");
+    pack_ctx* p = new (std::nothrow) pack_ctx();
+    if (!p) return fail(PACK_ENOMEM, "host allocation failed");
+    p->dry = true;
+    p->bf16 = (input->dtype == PACK_BF16);
+    p->K = K;
+    p->in = *input;
+    p->own_input = input_mode == PACK_INPUT_PER_MEMBER;
+    p->models.resize(K);
+    p->opt.assign(K, pack_opt_spec{PACK_OPT_SGD, 0.f, 0.f, 0.f, 0.f, 0.f});
+    p->opt_t.assign(K, 0);
+    for (int k = 0; k < K; ++k) {
+        pack_status s = parse_model(*input, models[k], k, p->models[k]);
+        if (s != PACK_OK) { release(p); return s; }
+    }
+    pack_status s = build_device(p);
+    if (s != PACK_OK) { release(p); return s; }
+    // As members of plain SGD; then as members under momentum, and under Adam and Adagrad in turn, whose dense products take other
+    // tiles and whose reduction launch applies gradients that are in place: the launches that differ.
+    long long counts[3][4] = {};
+    std::string err = check_plan(p, true, counts[0]);
+    for (int variant = 1; variant < 3 && err.empty(); ++variant) {
+        for (int k = 0; k < K; ++k) p->opt[k].kind = variant == 1 ? PACK_OPT_MOMENTUM : k & 1 ? PACK_OPT_ADAGRAD : PACK_OPT_ADAM;
+        free_device(p);
+        if ((s = build_device(p)) != PACK_OK) { release(p); return s; }
+        err = check_plan(p, false, counts[variant]);
+        if (!err.empty()) err = (variant == 1 ? "under momentum: " : "under Adam and Adagrad: ") + err;
+    }
     release(p);
-    if (launches_walked) *launches_walked = walked;
-    if (launches_skipped) *launches_skipped = skipped;
-    if (loads_checked) *loads_checked = loads + frags;
+    if (launches_walked) *launches_walked = counts[0][0];
+    if (launches_skipped) *launches_skipped = counts[0][1];
+    if (loads_checked) *loads_checked = counts[0][2] + counts[0][3];
     if (!err.empty()) return fail(PACK_EINVAL, "plan check: " + err);
     return PACK_OK;
 }

@@ -1261,7 +1261,7 @@ void build_plan(pack_ctx* p, DescBuilder& db, size_t& ws_need) {
     add_mapped_launch(p, db, L_REDUCE, dw_red, dw_red_blocks);
 
     // ---------------- update ----------------
-    // (plain-SGD packs have applied it in the weight-gradient launches above)
+    // (a fused update has been applied in the weight-gradient and reduction launches above)
     if (p->arena_elems && !p->fused) {
         Launch L;
         L.kind = L_SGD;
@@ -2214,8 +2214,7 @@ pack_status pack_set_optimizer(pack_t* p, int32_t k, const pack_opt_spec* spec) 
         if (q.kind == PACK_OPT_ADAM) need_v = true;
     }
     if (need_m != (p->opt_m != nullptr) || need_v != (p->opt_v != nullptr) || need_m != p->any_opt) {
-        // the set of state arrays, or whether the update is fused into the weight-gradient kernels,
-        // changes: plan the pack again (members keep their weights and state)
+        // the set of state arrays changes: the pack is built again (members keep their weights and state)
         pack_status st = rebuild(p, p->in.B, current_slots(p), 0);
         if (st != PACK_OK) {
             p->opt[k] = old_spec;

@@ -594,7 +594,7 @@ using LrArg = typename std::conditional<MODE == LIN_DW || MODE == CONV_DW, typen
 // to fill the compute units with staged tiles (add_gemm_launch).
 template <int MODE, typename T, int BM, int BN, int BKM, bool VEC, bool LEAN = false, bool GEN = false, bool OPT = false, bool SHARES = false>
 __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, T* __restrict__ As_, T* __restrict__ Bs_, const LrArg<MODE, OPT>& rates) {
-    static_assert(!OPT || MODE == LIN_DW, "dense weight gradients");
+    static_assert(!OPT || (MODE == LIN_DW && !(LEAN && BM == 128)), "dense weight gradients, the whole tile staged at once");
     float lrk = 0.f;
     if constexpr ((MODE == LIN_DW || MODE == CONV_DW) && !OPT) lrk = rates.lr[p.member];
     OptRef opt{};
@@ -929,8 +929,8 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
     // and the result is written as full vectors instead of one element per lane.
     // Accumulator register e of a 32x32 block holds row 8*(e/4) + 4*(lane/32) + e%4, column lane%32.
     constexpr int SLD = BN + 8;   // 4 rows apart = 32 banks apart: the two half-waves do not collide
-    // the lean weight-gradient form has one operand buffer: room for half the tile at a time; the lean
-    // forward / input-gradient form sizes its LDS block for the whole staging tile (LeanLds below)
+    // the lean 128 x 128 weight-gradient form has one operand buffer: room for half the tile at a time; the lean
+    // forward / input-gradient form sizes its LDS block for the whole staging tile (LdsBytes)
     constexpr int HALVES = (LEAN && IS_DW && BM == 128) ? 2 : 1;
     static_assert((size_t)(BM / HALVES) * SLD * 4 <= LdsBytes<T, BM, BN, BK, LEAN, IS_DW>::value, "staging tile must fit");
     float(*stage)[SLD] = reinterpret_cast<float(*)[SLD]>(As_);
@@ -941,8 +941,8 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
         // under the streams of others.  Bound by those streams: on 128 x 128 tiles, three workgroups to a compute unit and
         // few of them, it lost (8 members of 1.6 M, mixed optimisers, bf16: 60 us apart, 67 fused); on 64 x 64 tiles in the
         // lean form 49.  6 x 0.4 M, momentum, bf16: 27 -> 18; 3 x 14.9 M, Adam, fp32 over 256 rows: 406 -> 378.
-        constexpr int PER = DW_NIT / HALVES, OB = PER < 4 ? PER : 4;
-        static_assert(PER % OB == 0, "whole batches");
+        constexpr int OB = DW_NIT < 4 ? DW_NIT : 4;
+        static_assert(DW_NIT % OB == 0, "whole batches");
         const bool has_m = upd && opt.o.kind != OPT_SGD, has_v = upd && opt.o.kind == OPT_ADAM;
         const int col = col0 + dw_lc;
         const size_t state0 = upd ? (size_t)(p.upd_w - rates.master) : 0;
@@ -959,44 +959,39 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
                 if (live && has_v) v[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(rates.v + state0 + off));
             }
         };
+        request(0);
+        lds_barrier();   // operand tiles no longer read
 #pragma unroll
-        for (int part = 0; part < HALVES; ++part) {
-            request(part * PER);
-            lds_barrier();   // operand tiles (part 0) or the previous part's staging no longer read
-            if (HALVES == 1 || wm == part) {
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-                for (int a = 0; a < TM; ++a)
+            for (int b = 0; b < TN; ++b)
 #pragma unroll
-                    for (int b = 0; b < TN; ++b)
+                for (int e = 0; e < 16; ++e)
+                    stage[wm * (BM / 2) + a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)][wn * (BN / 2) + b * 32 + (lane & 31)] = acc[a][b][e];
+        lds_barrier();
 #pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            stage[(HALVES == 1 ? wm * (BM / 2) : 0) + a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)][wn * (BN / 2) + b * 32 + (lane & 31)] = acc[a][b][e];
-            }
-            lds_barrier();
+        for (int n0 = 0; n0 < DW_NIT; n0 += OB) {
+            if (n0 != 0) request(n0);
 #pragma unroll
-            for (int n0 = part * PER; n0 < (part + 1) * PER; n0 += OB) {
-                if (n0 != part * PER) request(n0);
+            for (int j = 0; j < OB; ++j) {
+                const int lr = dw_lr0 + (n0 + j) * DW_RSTEP, row = row0 + lr;
+                if (!dw_live || row >= p.R) continue;
+                const size_t off = (size_t)row * p.ldc + col;
+                f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr][dw_lc]);
+                if (dw_pad) {
 #pragma unroll
-                for (int j = 0; j < OB; ++j) {
-                    const int lr = dw_lr0 + (n0 + j) * DW_RSTEP, row = row0 + lr;
-                    if (!dw_live || row >= p.R) continue;
-                    const size_t off = (size_t)row * p.ldc + col;
-                    f32x4_t g = *reinterpret_cast<const f32x4_t*>(&stage[lr - part * (BM / HALVES)][dw_lc]);
-                    if (dw_pad) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if ((dw_pad >> e) & 1u) g[e] = 0.f;
-                    }
-                    if (keep_g) __builtin_nontemporal_store(g, reinterpret_cast<f32x4_t*>(gf + off));
-                    if (!upd) continue;
-                    opt_apply(opt, w[j], g, m[j], v[j]);
-                    if (has_m) __builtin_nontemporal_store(m[j], reinterpret_cast<f32x4_t*>(rates.m + state0 + off));
-                    if (has_v) __builtin_nontemporal_store(v[j], reinterpret_cast<f32x4_t*>(rates.v + state0 + off));
-                    *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w[j];
-                    if (p.upd_shadow) {
-                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
-                        *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[j][0], w[j][1]), pack2bf(w[j][2], w[j][3])};
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if ((dw_pad >> e) & 1u) g[e] = 0.f;
+                }
+                if (keep_g) __builtin_nontemporal_store(g, reinterpret_cast<f32x4_t*>(gf + off));
+                if (!upd) continue;
+                opt_apply(opt, w[j], g, m[j], v[j]);
+                if (has_m) __builtin_nontemporal_store(m[j], reinterpret_cast<f32x4_t*>(rates.m + state0 + off));
+                if (has_v) __builtin_nontemporal_store(v[j], reinterpret_cast<f32x4_t*>(rates.v + state0 + off));
+                *reinterpret_cast<f32x4_t*>(p.upd_w + off) = w[j];
+                if (p.upd_shadow) {
+                    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+                    *reinterpret_cast<u32x2_t*>((bf16_t*)p.upd_shadow + off) = u32x2_t{pack2bf(w[j][0], w[j][1]), pack2bf(w[j][2], w[j][3])};
                 }
             }
         }
@@ -1012,7 +1007,7 @@ __device__ __forceinline__ void gemm_body(const GemmProb& p, const TileRef& tr, 
             }
         }
     }
-    if constexpr (LEAN && IS_DW && !OPT && BM == 128) {
+    if constexpr (LEAN && IS_DW && BM == 128) {
         // two passes: the waves that own the upper (then the lower) half of the rows stage their
         // accumulators, then all threads apply that half
         float* const gf = (float*)p.C + (size_t)tr.ks * p.split_stride;

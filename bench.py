@@ -38,9 +38,9 @@ HEADLINE = "c5"                # the largest configuration that fits one GPU
 # scaled by a copy kernel of known size; the summary under profiles/ named here), valid only for the
 # kernel source it was measured on (hash of the kernel's text): {workload: {...}}.
 COUNTER_TRAFFIC = {
-    "c2": {"kernel": "gemm_lin_dw+sgd", "bytes": 374.5e6, "kernel_sha": "771a485732957ce7", "sources": "staged",
+    "c2": {"kernel": "gemm_lin_dw+sgd", "bytes": 374.6e6, "kernel_sha": "534e630f42c6d6d6", "sources": "staged",
            "profile": "profiles/c2_weight_gradient_update_hbm_counters.txt"},
-    "c5": {"kernel": "gemm_conv_dw+sgd", "bytes": 1107.9e6, "kernel_sha": "1c45ad4bf0880fd9", "sources": "conv_dw_halo",
+    "c5": {"kernel": "gemm_conv_dw+sgd", "bytes": 1107.8e6, "kernel_sha": "1a7d9184c59ed488", "sources": "conv_dw_halo",
            "profile": "profiles/c5_convolution_weight_gradient_hbm_counters.txt"},
 }
 

@@ -378,7 +378,7 @@ constexpr int LEAN64_MAX_CHUNKS = 18;
 constexpr size_t LEAN64_MIN_TILES = 1024;
 // The slim form's 64 x 64 tiles, one workgroup per compute unit at a time, pay once the launch has about as many of them as
 // there are compute units (1024 tiles of 32 x 32 are 256: 34 -> 25 us over 3072 indices, 9.0 -> 8.0 over 512; 256 are 64:
-// 8.0 -> 13).
+// 8.0 -> 13).  Only long reductions get there (shares_cfg).
 constexpr size_t SLIM64_MIN_TILES32 = 768;
 constexpr size_t MIXED_MAX_TILES = 256;
 std::vector<TileRef> xcd_order(const std::vector<TileOrder>& logical) {
